@@ -1,21 +1,20 @@
 // fft_line.hpp -- register/LDS line FFT building blocks for gfx950.
 //
 // One line of N complex64 points (64 <= N <= 16384, power of two) is held by
-// T = N/E threads, E points per thread (E = 8 or 16), in the "strided"
-// register layout:
+// T = N/16 threads, 16 points per thread, in the "strided" register layout:
 //
 //     thread t, register m  <->  element t + m*T .
 //
-// The transform is a sequence of self-sorting (Stockham) passes: radix-E
-// passes followed by at most one smaller power-of-two pass (N = E^a * r).
+// The transform is a sequence of self-sorting (Stockham) passes: radix-16
+// passes followed by at most one smaller power-of-two pass (N = 16^a * r).
 // A pass with radix R and span Ns (product of the earlier radices) computes,
 // for every butterfly j in [0, N/R),
 //
 //     v_i = x[j + i*N/R] * W_{Ns*R}^{(j mod Ns)*i},   i = 0..R-1
 //     y[(j/Ns)*Ns*R + (j mod Ns) + k*Ns] = DFT_R(v)_k,
 //
-// and thread t owns butterflies j = t + q*T (q < E/R), whose inputs are its
-// own registers q + i*(E/R).  Between passes the data go through LDS once
+// and thread t owns butterflies j = t + q*T (q < 16/R), whose inputs are its
+// own registers q + i*(16/R).  Between passes the data go through LDS once
 // (scatter write, barrier, strided read).  The last pass writes y in natural
 // order straight back to the same registers, so a forward transform ends in
 // the layout in which the next step (filter multiply, inverse transform,
@@ -69,103 +68,71 @@ __device__ __forceinline__ float2 c_mul_w8(float2 a)
                : make_float2(r * (a.x + a.y), r * (a.y - a.x));
 }
 
-// a * exp(-+ j 3pi/4) = a * (-1 -+ j)/sqrt(2)
+// ---------------------------------------------------------- butterflies
+// A thread's 16 points are transformed as radix-2 levels whose twiddles ride
+// inside the fused multiply-adds: (a, b) -> (a + w b, a - w b) takes four FMAs
+// for t = a + w b and two for 2 a - t.  A pass of radix R on inputs
+// v_i = x_i w^i is the evaluation of sum_i x_i z^i at z = w W_R^k, level by
+// level (even and odd powers), so the input twiddles cost nothing of their
+// own: 12 FMAs per point and radix-16 pass, where a radix-16 butterfly after
+// fifteen twiddle multiplies took 10.5 + 3.8 instructions, and eight distinct
+// twiddles per pass instead of fifteen.
 template <bool INV>
-__device__ __forceinline__ float2 c_mul_w8_3(float2 a)
+__device__ __forceinline__ void bfly(float2& a, float2& b, float2 w)
 {
-    constexpr float r = 0.70710678118654752440f;
-    return INV ? make_float2(-r * (a.x + a.y), r * (a.x - a.y))
-               : make_float2(r * (a.y - a.x), -r * (a.x + a.y));
+    if (INV) w.y = -w.y;
+    float2 t, u;
+    t.x = fmaf(-w.y, b.y, fmaf(w.x, b.x, a.x));
+    t.y = fmaf(w.y, b.x, fmaf(w.x, b.y, a.y));
+    u.x = fmaf(2.0f, a.x, -t.x);
+    u.y = fmaf(2.0f, a.y, -t.y);
+    a = t;
+    b = u;
 }
 
-// a * (c, -+ s)
+// The same with the twiddle -j w (forward; +j conj(w) inverse).
 template <bool INV>
-__device__ __forceinline__ float2 c_mul_cs(float2 a, float c, float s)
+__device__ __forceinline__ void bfly_mj(float2& a, float2& b, float2 w)
 {
-    return c_mul(a, make_float2(c, INV ? s : -s));
-}
-
-// ---------------------------------------------------------- small DFTs
-// All take natural-order input in v[] and leave natural-order output.
-template <bool INV>
-__device__ __forceinline__ void dft2(float2& a, float2& b)
-{
-    float2 t = a;
-    a = c_add(t, b);
-    b = c_sub(t, b);
-}
-
-template <bool INV>
-__device__ __forceinline__ void dft4(float2& a0, float2& a1, float2& a2, float2& a3)
-{
-    float2 s0 = c_add(a0, a2), d0 = c_sub(a0, a2);
-    float2 s1 = c_add(a1, a3), d1 = c_mul_mj<INV>(c_sub(a1, a3));
-    a0 = c_add(s0, s1);
-    a2 = c_sub(s0, s1);
-    a1 = c_add(d0, d1);
-    a3 = c_sub(d0, d1);
-}
-
-template <int R, bool INV> struct Dft;
-
-template <bool INV> struct Dft<2, INV> {
-    __device__ __forceinline__ static void run(float2* v) { dft2<INV>(v[0], v[1]); }
-};
-
-template <bool INV> struct Dft<4, INV> {
-    __device__ __forceinline__ static void run(float2* v) { dft4<INV>(v[0], v[1], v[2], v[3]); }
-};
-
-// DFT8 = DFT2 (stride 4) x twiddle W8^{n2 k1} x DFT4.
-template <bool INV> struct Dft<8, INV> {
-    __device__ __forceinline__ static void run(float2* v)
-    {
-        dft2<INV>(v[0], v[4]);
-        dft2<INV>(v[1], v[5]);
-        dft2<INV>(v[2], v[6]);
-        dft2<INV>(v[3], v[7]);
-        v[5] = c_mul_w8<INV>(v[5]);
-        v[6] = c_mul_mj<INV>(v[6]);
-        v[7] = c_mul_w8_3<INV>(v[7]);
-        // y[n2][k1] sits in v[n2 + 4 k1]; DFT4 over n2 gives X[k1 + 2 k2]
-        float2 a0 = v[0], a1 = v[1], a2 = v[2], a3 = v[3];
-        float2 b0 = v[4], b1 = v[5], b2 = v[6], b3 = v[7];
-        dft4<INV>(a0, a1, a2, a3);
-        dft4<INV>(b0, b1, b2, b3);
-        v[0] = a0; v[2] = a1; v[4] = a2; v[6] = a3;
-        v[1] = b0; v[3] = b1; v[5] = b2; v[7] = b3;
+    if (INV) w.y = -w.y;
+    float2 t, u;
+    if (INV) {                                    // a + j w b
+        t.x = fmaf(-w.y, b.x, fmaf(-w.x, b.y, a.x));
+        t.y = fmaf(-w.y, b.y, fmaf(w.x, b.x, a.y));
+    } else {                                      // a - j w b
+        t.x = fmaf(w.y, b.x, fmaf(w.x, b.y, a.x));
+        t.y = fmaf(w.y, b.y, fmaf(-w.x, b.x, a.y));
     }
-};
+    u.x = fmaf(2.0f, a.x, -t.x);
+    u.y = fmaf(2.0f, a.y, -t.y);
+    a = t;
+    b = u;
+}
 
-// DFT16 = DFT4 (stride 4) x twiddle W16^{n2 k1} x DFT4.
-template <bool INV> struct Dft<16, INV> {
-    __device__ __forceinline__ static void run(float2* v)
-    {
-        constexpr float c1 = 0.92387953251128675613f;   // cos(pi/8)
-        constexpr float s1 = 0.38268343236508977173f;   // sin(pi/8)
-#pragma unroll
-        for (int n2 = 0; n2 < 4; ++n2) dft4<INV>(v[n2], v[n2 + 4], v[n2 + 8], v[n2 + 12]);
-        // y[n2][k1] is in v[n2 + 4 k1]
-        v[5] = c_mul_cs<INV>(v[5], c1, s1);     // n2=1 k1=1: W16^1
-        v[9] = c_mul_w8<INV>(v[9]);             // n2=1 k1=2: W16^2
-        v[13] = c_mul_cs<INV>(v[13], s1, c1);   // n2=1 k1=3: W16^3
-        v[6] = c_mul_w8<INV>(v[6]);             // n2=2 k1=1: W16^2
-        v[10] = c_mul_mj<INV>(v[10]);           // n2=2 k1=2: W16^4
-        v[14] = c_mul_w8_3<INV>(v[14]);         // n2=2 k1=3: W16^6
-        v[7] = c_mul_cs<INV>(v[7], s1, c1);     // n2=3 k1=1: W16^3
-        v[11] = c_mul_w8_3<INV>(v[11]);         // n2=3 k1=2: W16^6
-        v[15] = c_mul_cs<INV>(v[15], -c1, -s1); // n2=3 k1=3: W16^9 = (-c1, +s1)
-        float2 o[16];
-#pragma unroll
-        for (int k1 = 0; k1 < 4; ++k1) {
-            float2 a0 = v[4 * k1], a1 = v[4 * k1 + 1], a2 = v[4 * k1 + 2], a3 = v[4 * k1 + 3];
-            dft4<INV>(a0, a1, a2, a3);
-            o[k1] = a0; o[k1 + 4] = a1; o[k1 + 8] = a2; o[k1 + 12] = a3;
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = o[i];
+// Butterfly with the constant twiddle W16^M (M = 0..7): additions only for
+// M = 0 and 4, one rotation by 45 degrees for M = 2 and 6.
+template <bool INV, int M>
+__device__ __forceinline__ void bfly_c(float2& a, float2& b)
+{
+    constexpr float c1 = 0.92387953251128675613f;   // cos(pi/8)
+    constexpr float s1 = 0.38268343236508977173f;   // sin(pi/8)
+    constexpr float r2 = 0.70710678118654752440f;
+    if constexpr (M == 0 || M == 4) {
+        const float2 t = M == 0 ? b : c_mul_mj<INV>(b);
+        b = c_sub(a, t);
+        a = c_add(a, t);
+    } else if constexpr (M == 2 || M == 6) {
+        // W8 b = r2 (x + y, y - x) forward, r2 (x - y, y + x) inverse
+        float2 t = INV ? make_float2(b.x - b.y, b.y + b.x) : make_float2(b.x + b.y, b.y - b.x);
+        if (M == 6) t = c_mul_mj<INV>(t);
+        b = make_float2(fmaf(-r2, t.x, a.x), fmaf(-r2, t.y, a.y));
+        a = make_float2(fmaf(r2, t.x, a.x), fmaf(r2, t.y, a.y));
+    } else if constexpr (M == 1 || M == 3) {
+        bfly<INV>(a, b, M == 1 ? make_float2(c1, -s1) : make_float2(s1, -c1));
+    } else {
+        bfly_mj<INV>(a, b, M == 5 ? make_float2(c1, -s1) : make_float2(s1, -c1));
     }
-};
+}
 
 // ------------------------------------------------------------ pass plan
 __host__ __device__ constexpr int ilog2(int n) { return n <= 1 ? 0 : 1 + ilog2(n / 2); }
@@ -174,17 +141,14 @@ __host__ __device__ constexpr int ilog2(int n) { return n <= 1 ? 0 : 1 + ilog2(n
 // LDS exchange fewer per transform than 8 at N = 4096 and measured faster.
 __host__ __device__ constexpr int line_e(int n) { return n > 0 ? 16 : 16; }
 
-template <int N, int E = line_e(N)> struct LineGeom {
+template <int N> struct LineGeom {
     static_assert(N >= 64 && N <= 16384 && (N & (N - 1)) == 0, "line length");
-    static_assert(E == 8 || E == 16, "points per thread");
-    static_assert(N / E <= 1024, "threads per line");
-    static constexpr int T = N / E;                        // threads per line
+    static constexpr int T = N / 16;                       // threads per line
     static constexpr int LOG = ilog2(N);
-    static constexpr int RLOG = ilog2(E);
-    static constexpr int NFULL = LOG / RLOG;               // radix-E passes
-    static constexpr int REM = 1 << (LOG % RLOG);          // trailing radix (1 = none)
+    static constexpr int NFULL = LOG / 4;                  // radix-16 passes
+    static constexpr int REM = 1 << (LOG % 4);             // trailing radix (1 = none)
     static constexpr int NP = NFULL + (REM > 1 ? 1 : 0);   // number of passes
-    __host__ __device__ static constexpr int radix(int p) { return p < NFULL ? E : REM; }
+    __host__ __device__ static constexpr int radix(int p) { return p < NFULL ? 16 : REM; }
     __host__ __device__ static constexpr int span(int p)   // Ns of pass p
     {
         return p == 0 ? 1 : span(p - 1) * radix(p - 1);
@@ -195,167 +159,197 @@ template <int N, int E = line_e(N)> struct LineGeom {
         return p <= 1 ? 0 : tw_off(p - 1) + (radix(p - 1) - 1) * span(p - 1);
     }
     static constexpr int TW_SIZE = tw_off(NP);
-    // LDS words (float2) per line: one pad slot every 16 entries
+    // LDS words (float2) per line, with up to one pad slot per 16 points
     static constexpr int LDS = N + N / 16;
 };
 
-__device__ __forceinline__ int lds_pad(int i) { return i + (i >> 4); }
+// LDS slot of point i in the exchange after pass P: 1 (P = 0) or 2 (later
+// passes) pad slots every 32.  LDS serves 8-byte accesses 32 lanes at a time
+// from 32 slots' worth of banks.  The reads take 32 consecutive points, which
+// no pad splits, so they are free of conflicts; the writes of pass 0 (16
+// points apart) need an odd pad, those of pass 1 (two runs of 16 points 256
+// apart) an even one.  With one pad every 16 for all passes the reads had a
+// two-way conflict (0.5 conflict cycles per active LDS cycle).
+template <int P> __host__ __device__ constexpr int lds_pads() { return P == 0 ? 1 : 2; }
 
-// Twiddles a thread needs in pass P: for butterfly q (j = t + q*T) and
-// i = 1..R-1, exp(-2 pi i * (j mod Ns) * i / (Ns * R)), read from this N's
-// table (entry tw_off(P) + (i-1)*Ns + (j mod Ns)); passes with Ns == 1 need
-// none.
-template <int N, int P> struct PassTw {
+template <int P> __device__ __forceinline__ int lds_slot(int i)
+{
+    return i + lds_pads<P>() * (i >> 5);
+}
+
+// lds_slot(t + m * T) for t < T, and lds_slot(base + i * NS) for the outputs of
+// radix-16 pass P of span NS (base = 16 t, or 16 NS (t / NS) + t % NS), as one
+// address per thread plus a constant, which becomes the instruction's offset:
+// the sums carry nothing from their low five bits into the pad term.
+template <int T, int P> __device__ __forceinline__ int lds_in(int t, int m)
+{
+    if constexpr (T >= 32) return lds_slot<P>(t) + m * (T + lds_pads<P>() * (T / 32));
+    else return t + (m * T + lds_pads<P>() * (m * T / 32));
+}
+template <int NS, int P> __device__ __forceinline__ int lds_out(int base, int i)
+{
+    return lds_slot<P>(base) + i * NS + lds_pads<P>() * (i * NS / 32);
+}
+
+// The twiddles of one thread in one pass.  The thread's 16 / R butterflies of
+// a radix-R pass (q = 0 .. 16/R - 1, j = t + q T) and their levels need
+// w^e W16^(e r), e a power of two below R, r < 8 / e; with -j factored out
+// (r >= 4 / e) eight values remain: w W16^r, w^2 W8^r, w^4, w^8, where w is
+// the twiddle of butterfly q = 0 (in a trailing pass the span is N / R, so
+// butterfly q's is w W16^q).
+struct TwSet {
+    float2 r[4];         // w, w W16, w W16^2, w W16^3
+    float2 s[2];         // w^2, w^2 W8
+    float2 w4, w8;
+};
+
+__device__ __forceinline__ float2 c_sqr(float2 a)
+{
+    return make_float2(fmaf(a.x, a.x, -a.y * a.y), 2.0f * a.x * a.y);
+}
+
+// The constant multiples of w and w^2 (set r[0], s[0] first).
+template <int R>
+__device__ __forceinline__ void tw_rotate(TwSet& p)
+{
+    constexpr float c1 = 0.92387953251128675613f;
+    constexpr float s1 = 0.38268343236508977173f;
+    const float2 w = p.r[0];
+    p.r[1] = c_mul(w, make_float2(c1, -s1));
+    p.r[2] = c_mul_w8<false>(w);
+    p.r[3] = c_mul(w, make_float2(s1, -c1));
+    if constexpr (R >= 4) p.s[1] = c_mul_w8<false>(p.s[0]);
+}
+
+// Twiddle table reads of pass P of virtual thread t (one of N / 16): w, and
+// for radix 8 and 16 w^4 (TWP: the other powers are squares of these two) or
+// w^2, w^4 and w^8 as well (!TWP: table reads instead of squares).  Row i - 1
+// of the pass's table holds w^i.
+template <int N, int P, bool TWP> struct TwReads {
     using G = LineGeom<N>;
     static constexpr bool ANY = P < G::NP && G::span(P) > 1;
-    static constexpr int COUNT = ANY ? (line_e(N) / G::radix(P)) * (G::radix(P) - 1) : 1;
-    float2 w[COUNT];
+    static constexpr int R = ANY ? G::radix(P) : 1;
+    float2 w1, w2, w4, w8;
 };
 
-// TWP, radix-16 pass: W^1 and W^4 come from the table, the other powers are
-// products (at most four roundings deep, ~3e-7 relative).  Thirteen complex
-// products replace thirteen table reads, for kernels bound by vector-memory
-// issue rather than by VALU.  w[i-1] = W^i, w[0] and w[3] given.
-__device__ __forceinline__ void tw_products16(float2* w)
+template <int N, int P, bool TWP>
+__device__ __forceinline__ void tw_issue(TwReads<N, P, TWP>& a, const float2* __restrict__ tw, int t)
 {
-    w[1] = c_mul(w[0], w[0]);
-    w[2] = c_mul(w[1], w[0]);
-    w[4] = c_mul(w[3], w[0]);
-    w[5] = c_mul(w[3], w[1]);
-    w[6] = c_mul(w[3], w[2]);
-    w[7] = c_mul(w[3], w[3]);
-#pragma unroll
-    for (int i = 8; i < 15; ++i) w[i] = c_mul(w[7], w[i - 8]);
+    using Rd = TwReads<N, P, TWP>;
+    if constexpr (Rd::ANY) {
+        using G = LineGeom<N>;
+        constexpr int NS = G::span(P), OFF = G::tw_off(P), R = Rd::R;
+        const int jm = t & (NS - 1);
+        a.w1 = tw[OFF + jm];
+        if constexpr (R >= 8) a.w4 = tw[OFF + 3 * NS + jm];
+        if constexpr (!TWP && R >= 4) a.w2 = tw[OFF + NS + jm];
+        if constexpr (!TWP && R >= 16) a.w8 = tw[OFF + 7 * NS + jm];
+    }
 }
 
 template <int N, int P, bool TWP>
-__device__ __forceinline__ void load_tw(PassTw<N, P>& pt, const float2* __restrict__ tw, int t)
+__device__ __forceinline__ void tw_form(TwSet& p, const TwReads<N, P, TWP>& a)
+{
+    using Rd = TwReads<N, P, TWP>;
+    if constexpr (Rd::ANY) {
+        constexpr int R = Rd::R;
+        p.r[0] = a.w1;
+        if constexpr (R >= 4) p.s[0] = TWP ? c_sqr(a.w1) : a.w2;
+        if constexpr (R >= 8) p.w4 = a.w4;
+        if constexpr (R >= 16) p.w8 = TWP ? c_sqr(a.w4) : a.w8;
+        tw_rotate<R>(p);
+    }
+}
+
+// Level E (inputs E apart within a butterfly) of a thread's 16 / R butterflies
+// of radix R: point i of butterfly q, partial output k, sits at
+// q + (16 / R) (i + 2 E k) before and q + (16 / R) (i + E k) after.
+template <int R, int E, bool INV, bool TW>
+__device__ __forceinline__ void fft_level(float2 (&v)[16], const TwSet& p)
+{
+    constexpr int B = 16 / R, K = R / (2 * E);
+    float2 o[16];
+#pragma unroll
+    for (int q = 0; q < B; ++q)
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            constexpr int J = 4 / E > 0 ? 4 / E : 1;      // r >= J carries the factor -j
+            const int r = q + k * B;
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                float2 a = v[q + B * (i + 2 * E * k)], b = v[q + B * (i + E + 2 * E * k)];
+                if constexpr (TW) {
+                    const float2 w = E == 8 ? p.w8 : E == 4 ? p.w4 : E == 2 ? p.s[r & 1] : p.r[r & 3];
+                    if (E < 8 && r >= J) bfly_mj<INV>(a, b, w);
+                    else bfly<INV>(a, b, w);
+                } else {
+                    switch (E * r) {
+                    case 0: bfly_c<INV, 0>(a, b); break;
+                    case 1: bfly_c<INV, 1>(a, b); break;
+                    case 2: bfly_c<INV, 2>(a, b); break;
+                    case 3: bfly_c<INV, 3>(a, b); break;
+                    case 4: bfly_c<INV, 4>(a, b); break;
+                    case 5: bfly_c<INV, 5>(a, b); break;
+                    case 6: bfly_c<INV, 6>(a, b); break;
+                    default: bfly_c<INV, 7>(a, b); break;
+                    }
+                }
+                o[q + B * (i + E * k)] = a;
+                o[q + B * (i + E * (k + K))] = b;
+            }
+        }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = o[i];
+}
+
+// All butterflies of pass P of one virtual thread, in registers.
+template <int N, int P, bool INV>
+__device__ __forceinline__ void pass_butterflies(float2 (&x)[16], const TwSet& p)
 {
     using G = LineGeom<N>;
-    if constexpr (TWP && PassTw<N, P>::ANY && G::radix(P) == 16) {
-        constexpr int NS = G::span(P), B = line_e(N) / 16, OFF = G::tw_off(P);
-#pragma unroll
-        for (int q = 0; q < B; ++q) {
-            const int jm = (t + q * G::T) & (NS - 1);
-            float2* w = pt.w + q * 15;
-            w[0] = tw[OFF + jm];
-            w[3] = tw[OFF + 3 * NS + jm];
-            tw_products16(w);
-        }
-    } else if constexpr (PassTw<N, P>::ANY) {
-        constexpr int R = G::radix(P), NS = G::span(P), B = line_e(N) / R, OFF = G::tw_off(P);
-#pragma unroll
-        for (int q = 0; q < B; ++q) {
-            const int jm = (t + q * G::T) & (NS - 1);
-#pragma unroll
-            for (int i = 1; i < R; ++i) pt.w[q * (R - 1) + i - 1] = tw[OFF + (i - 1) * NS + jm];
-        }
-    }
-}
-
-// The table reads of a TWP radix-16 pass (W^1, W^4 per butterfly), issued
-// one pass ahead so that their latency overlaps the previous pass and its
-// LDS exchange; other passes read their twiddles when they start.
-template <int N, int P, bool TWP> struct TwAhead {
-    static constexpr bool ON = TWP && PassTw<N, P>::ANY && LineGeom<N>::radix(P) == 16;
-    static constexpr int B = ON ? line_e(N) / 16 : 1;
-    float2 w1[B], w4[B];
-};
-
-template <int N, int P, bool TWP>
-__device__ __forceinline__ void tw_issue(TwAhead<N, P, TWP>& a, const float2* __restrict__ tw, int t)
-{
-    if constexpr (TwAhead<N, P, TWP>::ON) {
-        using G = LineGeom<N>;
-        constexpr int NS = G::span(P), OFF = G::tw_off(P);
-#pragma unroll
-        for (int q = 0; q < TwAhead<N, P, TWP>::B; ++q) {
-            const int jm = (t + q * G::T) & (NS - 1);
-            a.w1[q] = tw[OFF + jm];
-            a.w4[q] = tw[OFF + 3 * NS + jm];
-        }
-    }
-}
-
-template <int N, int P, bool TWP>
-__device__ __forceinline__ void tw_form(PassTw<N, P>& pt, const TwAhead<N, P, TWP>& a,
-                                        const float2* __restrict__ tw, int t)
-{
-    if constexpr (TwAhead<N, P, TWP>::ON) {
-#pragma unroll
-        for (int q = 0; q < TwAhead<N, P, TWP>::B; ++q) {
-            float2* w = pt.w + q * 15;
-            w[0] = a.w1[q];
-            w[3] = a.w4[q];
-            tw_products16(w);
-        }
-    } else {
-        load_tw<N, P, TWP>(pt, tw, t);
-    }
+    constexpr int R = G::radix(P);
+    constexpr bool TW = G::span(P) > 1;
+    if constexpr (R >= 16) fft_level<R, 8, INV, TW>(x, p);
+    if constexpr (R >= 8) fft_level<R, 4, INV, TW>(x, p);
+    if constexpr (R >= 4) fft_level<R, 2, INV, TW>(x, p);
+    fft_level<R, 1, INV, TW>(x, p);
 }
 
 // One Stockham pass P of an N-point line (see the header comment), with its
-// twiddles already loaded.
+// twiddles already formed.
 // SPLIT: the exchange keeps real and imaginary parts in two float arrays of
 // the line's LDS (re[0, LDS), im[LDS, 2 LDS)), two 4-byte accesses per point
-// instead of one 8-byte access: the layout the MFMA passes need, here with
-// FP32 butterflies, so that the two can be compared at equal layout.
+// instead of one 8-byte access, so that the two layouts can be compared.
 template <int N, int P, bool INV, bool SPLIT = false>
-__device__ __forceinline__ void fft_pass(float2 (&x)[line_e(N)], float2* __restrict__ lds,
-                                         const PassTw<N, P>& pt, int t)
+__device__ __forceinline__ void fft_pass(float2 (&x)[16], float2* __restrict__ lds,
+                                         const TwSet& p, int t)
 {
     using G = LineGeom<N>;
-    constexpr int E = line_e(N);
     constexpr int R = G::radix(P);
     constexpr int NS = G::span(P);
-    constexpr int B = E / R;
-    constexpr bool LAST = (P == G::NP - 1);
-#pragma unroll
-    for (int q = 0; q < B; ++q) {
-        float2 v[R];
-#pragma unroll
-        for (int i = 0; i < R; ++i) v[i] = x[q + i * B];
-        const int j = t + q * G::T;
-        const int jm = j & (NS - 1);
-        if constexpr (NS > 1) {
-#pragma unroll
-            for (int i = 1; i < R; ++i) {
-                float2 w = pt.w[q * (R - 1) + i - 1];
-                if (INV) w.y = -w.y;
-                v[i] = c_mul(v[i], w);
-            }
-        }
-        Dft<R, INV>::run(v);
-        if constexpr (LAST) {
-#pragma unroll
-            for (int i = 0; i < R; ++i) x[q + i * B] = v[i];
-        } else {
-            const int base = (j / NS) * NS * R + jm;
-            if constexpr (SPLIT) {
-                float* re = (float*)lds;
-                float* im = re + G::LDS;
-#pragma unroll
-                for (int i = 0; i < R; ++i) {
-                    re[lds_pad(base + i * NS)] = v[i].x;
-                    im[lds_pad(base + i * NS)] = v[i].y;
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < R; ++i) lds[lds_pad(base + i * NS)] = v[i];
-            }
-        }
-    }
-    if constexpr (!LAST) {
-        wg_barrier();
+    constexpr int B = 16 / R;
+    pass_butterflies<N, P, INV>(x, p);
+    if constexpr (P < G::NP - 1) {
+        static_assert(B == 1, "only the last pass is smaller than radix 16");
+        const int base = (t / NS) * NS * R + (t & (NS - 1));
         if constexpr (SPLIT) {
-            const float* re = (const float*)lds;
-            const float* im = re + G::LDS;
+            float* re = (float*)lds;
+            float* im = re + G::LDS;
 #pragma unroll
-            for (int m = 0; m < E; ++m)
-                x[m] = make_float2(re[lds_pad(t + m * G::T)], im[lds_pad(t + m * G::T)]);
+            for (int i = 0; i < 16; ++i) {
+                re[lds_out<NS, P>(base, i)] = x[i].x;
+                im[lds_out<NS, P>(base, i)] = x[i].y;
+            }
+            wg_barrier();
+#pragma unroll
+            for (int m = 0; m < 16; ++m)
+                x[m] = make_float2(re[lds_in<G::T, P>(t, m)], im[lds_in<G::T, P>(t, m)]);
         } else {
 #pragma unroll
-            for (int m = 0; m < E; ++m) x[m] = lds[lds_pad(t + m * G::T)];
+            for (int i = 0; i < 16; ++i) lds[lds_out<NS, P>(base, i)] = x[i];
+            wg_barrier();
+#pragma unroll
+            for (int m = 0; m < 16; ++m) x[m] = lds[lds_in<G::T, P>(t, m)];
         }
         wg_barrier();
     }
@@ -368,51 +362,56 @@ struct NoOp {
     __device__ __forceinline__ void operator()() const {}
 };
 
-// AHEAD: a TWP radix-16 pass's table reads are issued one pass early, so
-// they are in flight during the previous pass and its exchange (and, for
-// the last pass, ahead of the `before_last` loads).  They cost four
-// registers across the previous pass: the forward / inverse-only, RCMC and
-// long-line fused kernels have them, the shorter fused kernels do not.
-template <int N, bool INV, bool TWP, int P, bool SPLIT, bool AHEAD, class F>
-__device__ __forceinline__ void fft_from(float2 (&x)[line_e(N)], float2* __restrict__ lds,
+// AHEAD: a pass's table reads are issued one pass early, so they are in
+// flight during the previous pass and its exchange (and, for the last pass,
+// ahead of the `before_last` loads), at the cost of a few registers across
+// the previous pass.
+// FRESH: bit P set = pass P's twiddles are read and formed anew even where an
+// earlier transform of the same thread has them (its index is hidden from the
+// compiler); a bit left clear lets the compiler keep them in registers.
+template <int N, bool INV, bool TWP, int P, bool SPLIT, bool AHEAD, int FRESH, class F>
+__device__ __forceinline__ void fft_from(float2 (&x)[16], float2* __restrict__ lds,
                                          const float2* __restrict__ tw, int t, F&& before_last,
-                                         const TwAhead<N, P, TWP>& ahead)
+                                         const TwReads<N, P, TWP>& ahead)
 {
     if constexpr (P < LineGeom<N>::NP) {
         if constexpr (P == LineGeom<N>::NP - 1) before_last();
-        PassTw<N, P> cur;
-        TwAhead<N, P + 1, TWP> next;
+        TwSet cur;
+        TwReads<N, P + 1, TWP> next;
+        int ti = t;
+        constexpr int READ = AHEAD ? P + 1 : P;           // the pass whose reads are issued here
+        if constexpr ((FRESH >> READ) & 1) asm volatile("" : "+v"(ti));
         if constexpr (AHEAD) {
-            tw_form<N, P, TWP>(cur, ahead, tw, t);
-            tw_issue<N, P + 1, TWP>(next, tw, t);
+            tw_form<N, P, TWP>(cur, ahead);
+            tw_issue<N, P + 1, TWP>(next, tw, ti);
         } else {
-            load_tw<N, P, TWP>(cur, tw, t);
+            TwReads<N, P, TWP> now;
+            tw_issue<N, P, TWP>(now, tw, ti);
+            tw_form<N, P, TWP>(cur, now);
         }
         fft_pass<N, P, INV, SPLIT>(x, lds, cur, t);
-        fft_from<N, INV, TWP, P + 1, SPLIT, AHEAD>(x, lds, tw, t, before_last, next);
+        fft_from<N, INV, TWP, P + 1, SPLIT, AHEAD, FRESH>(x, lds, tw, t, before_last, next);
     }
 }
 
 // TWP selects twiddles by products (fewer loads, more VALU) or table reads;
 // SPLIT the split real/imaginary exchange layout (see fft_pass).
-template <int N, bool INV, bool TWP = true, bool SPLIT = false, class F = NoOp>
+template <int N, bool INV, bool TWP = true, bool SPLIT = false, int FRESH = 0, class F = NoOp>
 __device__ __forceinline__ void fft_line(float2 (&x)[line_e(N)], float2* __restrict__ lds,
                                          const float2* __restrict__ tw, int t, F&& before_last = F())
 {
-    TwAhead<N, 0, TWP> first;
-    fft_from<N, INV, TWP, 0, SPLIT, false>(x, lds, tw, t, before_last, first);
+    TwReads<N, 0, TWP> first;
+    fft_from<N, INV, TWP, 0, SPLIT, false, FRESH>(x, lds, tw, t, before_last, first);
 }
 
-// The same transform with every TWP radix-16 pass's table reads issued one
-// pass ahead.
-template <int N, bool INV, bool TWP = true, bool SPLIT = false, class F = NoOp>
+// The same transform with every pass's table reads issued one pass ahead.
+template <int N, bool INV, bool TWP = true, bool SPLIT = false, int FRESH = 0, class F = NoOp>
 __device__ __forceinline__ void fft_line_ahead(float2 (&x)[line_e(N)], float2* __restrict__ lds,
                                                const float2* __restrict__ tw, int t,
                                                F&& before_last = F())
 {
-    TwAhead<N, 0, TWP> first;
-    tw_issue<N, 0, TWP>(first, tw, t);
-    fft_from<N, INV, TWP, 0, SPLIT, true>(x, lds, tw, t, before_last, first);
+    TwReads<N, 0, TWP> first;
+    fft_from<N, INV, TWP, 0, SPLIT, true, FRESH>(x, lds, tw, t, before_last, first);
 }
 
 }  // namespace sar

@@ -194,7 +194,7 @@ __device__ __forceinline__ void fft_line_mfma(float2 (&x)[16], float2* __restric
                                               const float2* __restrict__ tw, int sub, int t,
                                               Pre&& before_last = Pre())
 {
-    using G = LineGeom<N, 16>;
+    using G = LineGeom<N>;
     static_assert(line_e(N) == 16, "the MFMA path uses 16 points per thread");
     constexpr int T = G::T;
     constexpr int LL = G::LDS;                   // float2 per line
@@ -305,8 +305,10 @@ __device__ __forceinline__ void fft_line_mfma(float2 (&x)[16], float2* __restric
     __syncthreads();                              // LDS free for the caller's next use
     if constexpr (G::NP > NMF) {
         // trailing radix-2/4/8 pass in FP32 (its twiddles applied on input)
-        PassTw<N, G::NP - 1> pt;
-        load_tw<N, G::NP - 1, false>(pt, tw, t);
+        TwReads<N, G::NP - 1, false> rd;
+        TwSet pt;
+        tw_issue<N, G::NP - 1, false>(rd, tw, t);
+        tw_form<N, G::NP - 1, false>(pt, rd);
         fft_pass<N, G::NP - 1, INV>(x, (float2*)nullptr, pt, t);
     }
 }

@@ -1,8 +1,9 @@
 // rda_kernels.inl -- gfx950 kernels of the Range Doppler Algorithm and their
-// launchers.  Compiled in four parts (rda_part_*.hip, SAR_PART = 0..3) so that
+// launchers.  Compiled in parts (rda_part_*.hip, SAR_PART = 0..4) so that
 // the template instantiations build in parallel: part 0 holds the table
 // generators, the non-line kernels and the dispatcher, parts 1-3 the line
-// and RCMC kernels for FP32, split-FP16 and split-BF16 butterflies.  Every kernel is written for wave64 CDNA4; lines are kept in
+// and RCMC kernels for FP32, split-FP16 and split-BF16 butterflies, part 4
+// the turn-free strips and the half-storage kernels.  Every kernel is written for wave64 CDNA4; lines are kept in
 // registers (16 complex64 per thread) and LDS between radix passes.
 //
 // Kernels (paper: arXiv 2604.03585):
@@ -27,6 +28,7 @@
 #include <type_traits>
 
 #include "fft_line.hpp"
+#include "fft_line_tw.hpp"
 #include "mfma_fft.hpp"
 #include "rda_internal.h"
 
@@ -125,39 +127,39 @@ template <int N, int X = 1> struct LineLaunch {
     static constexpr int T = LineGeom<N>::T;
     static constexpr int LPW = (T >= 256 ? 1 : 256 / T) * X;   // lines per workgroup
     static constexpr int BLOCK = LPW * T;
-    // Register policy of the fused FFT*H*IFFT kernels (measured on gfx950):
-    // the inverse transform reuses the forward pass's twiddle products when
-    // the compiler can prove the addresses equal, which saves VALU work but
-    // keeps them live across the multiply.  For N = 4096 that reuse pays once
-    // the kernel is held to 128 VGPRs (4 waves per SIMD, as many workgroups
-    // as LDS allows; see line_wpe); for N >= 8192 it spills, so the inverse
-    // recomputes them.
-    static constexpr bool RECOMPUTE_INV_TW = N >= 8192;
+    // Register policy of the fused FFT*H*IFFT kernels: the inverse transform
+    // may keep the forward passes' twiddles (the same eight values per pass)
+    // in registers across the multiply, 16 registers a pass.  Up to 1024
+    // points all of them; at 2048, held to 128 VGPRs by line_wpe, pass 1's
+    // (with pass 2's as well it spills); from 4096 none: with all but pass
+    // 2's the 4096-point kernel (126 VGPRs) took 116 us for 8192 lines, where
+    // reading them anew one pass ahead (74 VGPRs) takes 105.
+    static constexpr int FRESH_INV = N >= 4096 ? 0xf : (N >= 2048 ? 1 << 2 : 0);
     static constexpr int LDS_BYTES = LPW * LineGeom<N>::LDS * (int)sizeof(float2);
 };
 
 // Minimum waves per SIMD requested for the line kernels: 4 for the FP32
-// 4096-point kernels (register reuse above); 2 for the split-precision
+// kernels of 1024 to 4096 points (as many workgroups as LDS allows); 2 for the split-precision
 // (MFMA) kernels (left to itself the fused 4096-point one takes 268 VGPRs,
 // one wave per SIMD); no request otherwise.
 template <int N, int PREC> constexpr int line_wpe()
 {
-    if constexpr (PREC == 0) return N == 4096 ? 4 : 1;
+    if constexpr (PREC == 0) return N >= 1024 && N <= 4096 ? 4 : 1;
     else return 2;     // four waves (128 VGPRs) spill in the split transforms, measured slower
 }
 
 // Line transform in the requested butterfly precision: FP32 VALU passes, or
 // split FP16 / BF16 radix-16 passes on MFMA (twiddles and filters in FP32).
 template <int N, bool INV, int PREC, bool TWP = true, bool SPLIT = false, class F = NoOp,
-          bool AHEAD = false>
+          bool AHEAD = false, int FRESH = 0>
 __device__ __forceinline__ void fft_any(float2 (&x)[line_e(N)], float2* __restrict__ lds,
                                         const float2* __restrict__ tw, int sub, int t,
                                         F&& before_last = F())
 {
     if constexpr (PREC == PREC_FP32 && AHEAD) {
-        fft_line_ahead<N, INV, TWP, SPLIT>(x, lds, tw, t, before_last);
+        fft_line_ahead<N, INV, TWP, SPLIT, FRESH>(x, lds, tw, t, before_last);
     } else if constexpr (PREC == PREC_FP32) {
-        fft_line<N, INV, TWP, SPLIT>(x, lds, tw, t, before_last);
+        fft_line<N, INV, TWP, SPLIT, FRESH>(x, lds, tw, t, before_last);
     } else {
         using L = LineLaunch<N>;
         fft_line_mfma<N, INV, PREC, L::LPW, L::BLOCK>(x, lds - sub * LineGeom<N>::LDS, tw, sub,
@@ -173,20 +175,46 @@ __device__ __forceinline__ int xcd_group(int b, int groups)
     return (b & 7) * (groups >> 3) + (b >> 3);
 }
 
+// Sample at byte offset `off` from a wave-uniform base.
+__device__ __forceinline__ float2 ld_off(const float2* __restrict__ base, uint32_t byte_off)
+{
+    return *(const float2*)((const char*)base + byte_off);
+}
+
+// Buffer resource over `bytes` bytes (less than 4 GiB) from a wave-uniform base:
+// reads beyond its end return zero and writes there are dropped.  A buffer
+// access takes a vector offset plus a scalar one, so the 16 accesses of a line
+// share one address register instead of 16 64-bit sums.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ float2 buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
+{
+    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
+}
+__device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, float2 v)
+{
+    typedef unsigned int u2_t __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2_t, v), r, voff, soff, 0);
+}
+
+// Points t + m*T of a line; `off` is the byte offset of point t from the
+// resource's base.
 template <int N>
-__device__ __forceinline__ void load_line(float2 (&x)[line_e(N)], const float2* __restrict__ src,
-                                          int t)
+__device__ __forceinline__ void load_line(float2 (&x)[line_e(N)], __amdgpu_buffer_rsrc_t src,
+                                          uint32_t off)
 {
 #pragma unroll
-    for (int m = 0; m < line_e(N); ++m) x[m] = src[t + m * LineGeom<N>::T];
+    for (int m = 0; m < line_e(N); ++m) x[m] = buf_ld(src, off, m * LineGeom<N>::T * 8u);
 }
 
 template <int N>
-__device__ __forceinline__ void store_line(const float2 (&x)[line_e(N)], float2* __restrict__ dst,
-                                           int t)
+__device__ __forceinline__ void store_line(const float2 (&x)[line_e(N)], __amdgpu_buffer_rsrc_t dst,
+                                           uint32_t off)
 {
 #pragma unroll
-    for (int m = 0; m < line_e(N); ++m) dst[t + m * LineGeom<N>::T] = x[m];
+    for (int m = 0; m < line_e(N); ++m) buf_st(dst, off, m * LineGeom<N>::T * 8u, x[m]);
 }
 
 // One workgroup per group of LPW lines.
@@ -209,24 +237,17 @@ __device__ __forceinline__ void line_transform(float2 (&x)[line_e(N)], float2* _
     using L = LineLaunch<N>;
     constexpr int E = line_e(N);
     if constexpr (KIND == LK_FUSED) {
-        // the filter is requested just before the last forward pass.  Lines
-        // of 8192 points and more (one or two workgroups per CU) read their
-        // twiddles one pass ahead in both transforms, 4096-point lines in the
-        // forward one (in the inverse too they spill), shorter ones not at
-        // all (registers)
-        constexpr bool AHEAD = N >= 8192;
-        constexpr bool AHEAD_FWD = AHEAD || N == 4096;
+        // the filter is requested just before the last forward pass; lines of
+        // 4096 points and more read their twiddles one pass ahead, shorter
+        // ones keep the forward passes' for the inverse (see FRESH_INV)
+        constexpr bool AHEAD = N >= 4096;
         float2 h[E];
-        auto filter = [&] {
-#pragma unroll
-            for (int m = 0; m < E; ++m) h[m] = H[t + m * L::T];
-        };
-        fft_any<N, false, PREC, TWP, false, decltype(filter)&, AHEAD_FWD>(x, lds, tw, sub, t, filter);
+        const __amdgpu_buffer_rsrc_t hb = buf_rsrc(H, N * 8u);
+        auto filter = [&] { load_line<N>(h, hb, (uint32_t)t * 8u); };
+        fft_any<N, false, PREC, TWP, false, decltype(filter)&, AHEAD>(x, lds, tw, sub, t, filter);
 #pragma unroll
         for (int m = 0; m < E; ++m) x[m] = c_mul(x[m], h[m]);
-        int ti = t;
-        if constexpr (L::RECOMPUTE_INV_TW) asm volatile("" : "+v"(ti));   // hide ti == t
-        fft_any<N, true, PREC, TWP, false, NoOp, AHEAD>(x, lds, tw, sub, ti);
+        fft_any<N, true, PREC, TWP, false, NoOp, AHEAD, L::FRESH_INV>(x, lds, tw, sub, t);
     } else {
         fft_any<N, KIND == LK_INV, PREC, TWP, SPLIT, NoOp, true>(x, lds, tw, sub, t);
         if (scale != 1.0f) {
@@ -245,17 +266,17 @@ __device__ __forceinline__ void line_group(const float2* in, float2* out, int li
     using L = LineLaunch<N, X>;
     constexpr int E = line_e(N);
     const int sub = threadIdx.x / L::T, t = threadIdx.x % L::T;
-    const int line = g * L::LPW + sub;
-    const bool live = line < lines;
+    // the group's lines, the last group's only as far as they go: absent
+    // lines read zeros and are not stored
+    const size_t first = (size_t)g * L::LPW * N;
+    const int here = lines - g * L::LPW;
+    const uint32_t bytes = (uint32_t)((here < L::LPW ? here : L::LPW) * N) * 8u;
+    const uint32_t off = (uint32_t)(sub * N + t) * 8u;
     float2* lds = smem + sub * LineGeom<N>::LDS;
     float2 x[E];
-    if (live) load_line<N>(x, in + (size_t)line * N, t);
-    else {
-#pragma unroll
-        for (int m = 0; m < E; ++m) x[m] = make_float2(0.f, 0.f);
-    }
+    load_line<N>(x, buf_rsrc(in + first, bytes), off);
     line_transform<N, KIND, PREC, TWP, SPLIT>(x, lds, H, tw, scale, sub, t);
-    if (live) store_line<N>(x, out + (size_t)line * N, t);
+    store_line<N>(x, buf_rsrc(out + first, bytes), off);
 }
 
 // ---------------------------------------------------------- column strips
@@ -301,18 +322,18 @@ k_line_strip(const float2* __restrict__ in, float2* __restrict__ out, int cols, 
         const int e = u + p * S::BLOCK;           // pair (row m, columns 2q, 2q+1) of the strip
         const int m = e / (C / 2), q = e % (C / 2);
         const float4 v = *(const float4*)(in + (size_t)m * pitch + n0 + 2 * q);
-        smem[(2 * q) * S::STRIDE + lds_pad(m)] = make_float2(v.x, v.y);
-        smem[(2 * q + 1) * S::STRIDE + lds_pad(m)] = make_float2(v.z, v.w);
+        smem[(2 * q) * S::STRIDE + lds_slot<0>(m)] = make_float2(v.x, v.y);
+        smem[(2 * q + 1) * S::STRIDE + lds_slot<0>(m)] = make_float2(v.z, v.w);
     }
     __syncthreads();
     const int sub = u / T, t = u % T;
     float2* lds = smem + sub * S::STRIDE;
     float2 x[E];
 #pragma unroll
-    for (int m = 0; m < E; ++m) x[m] = lds[lds_pad(t + m * T)];
+    for (int m = 0; m < E; ++m) x[m] = lds[lds_in<T, 0>(t, m)];
     __syncthreads();                              // reads done before the exchanges
     line_transform<N, KIND, PREC_FP32, TWP>(x, lds, H, tw, scale, sub, t);
-    store_line<N>(x, out + (size_t)(n0 + sub) * N, t);
+    store_line<N>(x, buf_rsrc(out + (size_t)n0 * N, C * N * 8u), (uint32_t)(sub * N + t) * 8u);
 }
 
 template <int N, int KIND, int PREC, bool TWP, bool SPLIT = false, int X = 1>
@@ -732,11 +753,6 @@ __device__ __forceinline__ float2 rcmc_combine(float x, const float* __restrict_
     return acc;
 }
 
-__device__ __forceinline__ float2 ld_off(const float2* __restrict__ base, uint32_t byte_off)
-{
-    return *(const float2*)((const char*)base + byte_off);
-}
-
 // RCMC output y[n][k] from range-Doppler A[Nr][Na]:
 //   R0 = r_near + n, s = R0 * stretch_k, i0 = n + floor(s), x = frac(s),
 //   y = sum_t w_t(x) A[i0 + t][k] over t = -3..4 (rows outside [0, Nr) add 0).
@@ -918,7 +934,8 @@ k_rcmc_az(const float2* __restrict__ A, float2* __restrict__ out, RcmcArgs ra,
     }
     if constexpr (TAPS != 0) __syncthreads();     // table reads done before LDS reuse
     fft_any<N, true, PREC>(x, lds, tw, sub, t);
-    if (live) store_line<N>(x, out + (size_t)n * N, t);
+    const uint32_t bytes = (uint32_t)(min(L::LPW, lines - g * L::LPW) * N) * 8u;   // absent lines dropped
+    store_line<N>(x, buf_rsrc(out + (size_t)g * L::LPW * N, bytes), (uint32_t)(sub * N + t) * 8u);
 }
 
 // Two output rows n, n+1 per line slot.  For each column their 8-tap
@@ -1082,9 +1099,13 @@ k_rcmc_az2(const void* __restrict__ A_, float2* __restrict__ out, RcmcArgs ra,
     }
     __syncthreads();                              // table reads done before LDS reuse
     fft_any<N, true, PREC, true, false, NoOp, true>(xa, lds, tw, sub, t);
-    if (live) store_line<N>(xa, out + (size_t)n * N, t);
+    // the group's pairs of rows (absent ones are not stored)
+    const uint32_t bytes = (uint32_t)(min(L::LPW, pairs - g * L::LPW) * 2 * N) * 8u;
+    const __amdgpu_buffer_rsrc_t ob = buf_rsrc(out + (size_t)(2 * g * L::LPW) * N, bytes);
+    const uint32_t off = (uint32_t)(2 * sub * N + t) * 8u;
+    store_line<N>(xa, ob, off);
     fft_any<N, true, PREC, true, false, NoOp, true>(xb, lds, tw, sub, t);
-    if (live) store_line<N>(xb, out + (size_t)(n + 1) * N, t);
+    store_line<N>(xb, ob, off + N * 8u);
 }
 
 // The same two rows per workgroup on 2T threads (FP32, T = N/16 <= 512):
@@ -1121,18 +1142,18 @@ k_rcmc_az2w(const float2* __restrict__ A, float2* __restrict__ out, RcmcArgs ra,
     float2* row_b = smem + G::LDS;
 #pragma unroll
     for (int m = 0; m < C; ++m) {
-        row_a[lds_pad(u + m * S)] = ya[m];
-        row_b[lds_pad(u + m * S)] = yb[m];
+        row_a[lds_in<S, 0>(u, m)] = ya[m];
+        row_b[lds_in<S, 0>(u, m)] = yb[m];
     }
     __syncthreads();
     const int sub = u / T, t = u % T;
     float2* lds = smem + sub * G::LDS;
     float2 x[E];
 #pragma unroll
-    for (int m = 0; m < E; ++m) x[m] = lds[lds_pad(t + m * T)];
+    for (int m = 0; m < E; ++m) x[m] = lds[lds_in<T, 0>(t, m)];
     __syncthreads();                              // reads done before the IFFT writes
     fft_line<N, true>(x, lds, tw, t);
-    store_line<N>(x, out + (size_t)(n + sub) * N, t);
+    store_line<N>(x, buf_rsrc(out + (size_t)n * N, 2 * N * 8u), (uint32_t)(sub * N + t) * 8u);
 }
 
 #if SAR_PART == 0
@@ -1170,7 +1191,7 @@ __global__ __launch_bounds__(256) void k_az_phase(const float2* __restrict__ in,
 
 #endif  // SAR_PART == 0
 
-#if SAR_PART == 1
+#if SAR_PART == 4
 // ===================================================== half storage (FP32 math)
 // Largest |re|, |im| of one line's samples (the line's T threads: aligned
 // lane segments of a wave when T < 64, else whole waves combined through
@@ -1229,62 +1250,68 @@ k_line_hs(const void* __restrict__ in, void* __restrict__ out, int lines,
     const int sub = threadIdx.x / L::T, t = threadIdx.x % L::T;
     const int line = g * L::LPW + sub;
     const bool live = line < lines;
+    const size_t first = (size_t)g * L::LPW * N;                 // uniform
+    const uint32_t off = (uint32_t)(sub * N + t);                // samples from `first`
     float2* lds = smem + sub * LineGeom<N>::LDS;
     float2 x[E];
     if (live) {
         if constexpr (IN_H) {
-            const h2_t* src = (const h2_t*)in + (size_t)line * N;
+            const h2_t* src = (const h2_t*)in + first;
 #pragma unroll
-            for (int m = 0; m < E; ++m) {
-                const int j = t + m * L::T;
-                x[m] = h2_to_f2(src[j], ldexpf(1.0f, ex_in[j]));
-            }
+            for (int m = 0; m < E; ++m)
+                x[m] = h2_to_f2(*(const h2_t*)((const char*)(src + m * L::T) + off * 4u),
+                                ldexpf(1.0f, *(const int*)((const char*)(ex_in + m * L::T) + (uint32_t)t * 4u)));
         } else {
-            load_line<N>(x, (const float2*)in + (size_t)line * N, t);
+            load_line<N>(x, buf_rsrc((const float2*)in + first, L::LPW * N * 8u), off * 8u);
         }
     } else {
 #pragma unroll
         for (int m = 0; m < E; ++m) x[m] = make_float2(0.f, 0.f);
     }
-    // twiddle reads one pass ahead where registers allow, as in line_group
-    // (fused: forward from 4096 points, inverse from 8192)
     if constexpr (KIND == LK_FUSED) {
         float2 h[E];
         auto filter = [&] {
 #pragma unroll
-            for (int m = 0; m < E; ++m) h[m] = H[t + m * L::T];
+            for (int m = 0; m < E; ++m) h[m] = ld_off(H + m * L::T, (uint32_t)t * 8u);
         };
-        if constexpr (N >= 4096) fft_line_ahead<N, false>(x, lds, tw, t, filter);
-        else fft_line<N, false>(x, lds, tw, t, filter);
+        if constexpr (OUT_H) {
+            // twiddle reads one pass ahead where registers allow (forward from
+            // 4096 points, inverse from 8192); from 8192 the inverse forms its
+            // own products (kept ones would spill)
+            if constexpr (N >= 4096) tw_first::fft_line_ahead<N, false>(x, lds, tw, t, filter);
+            else tw_first::fft_line<N, false>(x, lds, tw, t, filter);
 #pragma unroll
-        for (int m = 0; m < E; ++m) x[m] = c_mul(x[m], h[m]);
-        int ti = t;
-        if constexpr (L::RECOMPUTE_INV_TW) asm volatile("" : "+v"(ti));
-        if constexpr (N >= 8192) fft_line_ahead<N, true>(x, lds, tw, ti);
-        else fft_line<N, true>(x, lds, tw, ti);
+            for (int m = 0; m < E; ++m) x[m] = c_mul(x[m], h[m]);
+            int ti = t;
+            if constexpr (N >= 8192) asm volatile("" : "+v"(ti));
+            if constexpr (N >= 8192) tw_first::fft_line_ahead<N, true>(x, lds, tw, ti);
+            else tw_first::fft_line<N, true>(x, lds, tw, ti);
+        } else {
+            line_transform<N, LK_FUSED, PREC_FP32, true>(x, lds, H, tw, 1.0f, sub, t);
+        }
     } else {
-        static_assert(KIND == LK_FWD, "fused or forward");
-        fft_line_ahead<N, false>(x, lds, tw, t);
+        static_assert(KIND == LK_FWD && OUT_H, "fused or forward");
+        tw_first::fft_line_ahead<N, false>(x, lds, tw, t);
     }
     if constexpr (OUT_H) {
         const int e = half_exponent(line_absmax<N>(x, (float*)smem, sub));
         const float sc = ldexpf(1.0f, -e);
         if (live) {
-            h2_t* dst = (h2_t*)out + (size_t)line * N;
+            h2_t* dst = (h2_t*)out + first;
 #pragma unroll
             for (int m = 0; m < E; ++m) {
                 h2_t v;
                 v.x = (_Float16)(x[m].x * sc);
                 v.y = (_Float16)(x[m].y * sc);
-                dst[t + m * L::T] = v;
+                *(h2_t*)((char*)(dst + m * L::T) + off * 4u) = v;
             }
             if (t == 0) ex_out[line] = e;
         }
     } else if (live) {
-        store_line<N>(x, (float2*)out + (size_t)line * N, t);
+        store_line<N>(x, buf_rsrc((float2*)out + first, L::LPW * N * 8u), off * 8u);
     }
 }
-#endif  // SAR_PART == 1
+#endif  // SAR_PART == 4
 
 // ===================================================== launchers
 static RcmcArgs make_rcmc_args(const RcmcHost& rh)
@@ -1571,7 +1598,7 @@ hipError_t launch_line_f16(LineOp, int, const float2*, float2*, int, const float
 hipError_t launch_line_bf16(LineOp, int, const float2*, float2*, int, const float2*, const float2*,
                             float, const RcmcArgs*, int, int, hipStream_t);
 
-#if SAR_PART >= 1
+#if SAR_PART >= 1 && SAR_PART <= 3
 hipError_t SAR_LINE_BATCH_FN(int kind, int n, const LineTask* tasks, int ntasks, int total_groups,
                              float scale, int v, hipStream_t s)
 {
@@ -1586,7 +1613,7 @@ hipError_t launch_line_fp32(LineOp op, int n, const float2* i, float2* o, int li
 {
     return launch_line_prec<PREC_FP32>(op, n, i, o, lines, h, w, scale, ra, taps, v, s);
 }
-
+#elif SAR_PART == 4
 template <int N, int KIND, int CW>
 static hipError_t launch_strip_k(const float2* in, float2* out, int cols, int pitch,
                                  const float2* H, const float2* tw, float scale, hipStream_t s)
