@@ -414,4 +414,83 @@ __device__ __forceinline__ void fft_line_ahead(float2 (&x)[line_e(N)], float2* _
     fft_from<N, INV, TWP, 0, SPLIT, true, FRESH>(x, lds, tw, t, before_last, first);
 }
 
+// The value is in its registers here: a pending load has been waited for, and
+// what is computed from it later is not moved ahead of this point (out of a
+// loop over lines, where it would stay in registers).
+__device__ __forceinline__ void pin(float2& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
+
+__device__ __forceinline__ void pin_line(float2 (&x)[16])
+{
+#pragma unroll
+    for (int m = 0; m < 16; ++m) pin(x[m]);
+}
+
+__device__ __forceinline__ void copy_line(float2 (&to)[16], const float2 (&from)[16])
+{
+#pragma unroll
+    for (int m = 0; m < 16; ++m) to[m] = from[m];
+}
+
+// The same value under a new name: addresses formed from it are formed where
+// they are used instead of staying in registers through a loop.
+__device__ __forceinline__ int fresh(int t)
+{
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+// The twiddle reads of every pass (at most five values), held in registers by a
+// thread that transforms line after line: the transforms between then read
+// nothing from memory, so no wait of theirs covers loads of the next line.
+template <int N> struct TwAll {
+    TwReads<N, 1, true> p1;
+    TwReads<N, 2, true> p2;
+    TwReads<N, 3, true> p3;
+    __device__ __forceinline__ void read(const float2* __restrict__ tw, int t)
+    {
+        tw_issue<N, 1, true>(p1, tw, t);
+        tw_issue<N, 2, true>(p2, tw, t);
+        tw_issue<N, 3, true>(p3, tw, t);
+    }
+    template <int P> static __device__ __forceinline__ void pin_pass(TwReads<N, P, true>& r)
+    {
+        if constexpr (TwReads<N, P, true>::ANY) {
+            pin(r.w1);
+            if constexpr (TwReads<N, P, true>::R >= 8) pin(r.w4);
+        }
+    }
+    __device__ __forceinline__ void hold()
+    {
+        pin_pass<1>(p1);
+        pin_pass<2>(p2);
+        pin_pass<3>(p3);
+    }
+};
+
+template <int N, bool INV, int P, class F>
+__device__ __forceinline__ void fft_held_from(float2 (&x)[16], float2* __restrict__ lds,
+                                              const TwAll<N>& tw, int t, F&& before_last)
+{
+    if constexpr (P < LineGeom<N>::NP) {
+        // ahead of the last radix-16 pass (its butterflies and exchange cover
+        // the latency of the loads; a trailing smaller pass is too short)
+        if constexpr (P == LineGeom<N>::NFULL - 1) before_last();
+        TwSet cur;
+        if constexpr (P == 1) tw_form<N, 1, true>(cur, tw.p1);
+        if constexpr (P == 2) tw_form<N, 2, true>(cur, tw.p2);
+        if constexpr (P == 3) tw_form<N, 3, true>(cur, tw.p3);
+        fft_pass<N, P, INV>(x, lds, cur, t);
+        fft_held_from<N, INV, P + 1>(x, lds, tw, t, before_last);
+    }
+}
+
+// fft_line with held twiddle reads.
+// (before_last runs before the last radix-16 pass)
+template <int N, bool INV, class F = NoOp>
+__device__ __forceinline__ void fft_line_held(float2 (&x)[16], float2* __restrict__ lds,
+                                              const TwAll<N>& tw, int t, F&& before_last = F())
+{
+    fft_held_from<N, INV, 0>(x, lds, tw, t, before_last);
+}
+
 }  // namespace sar

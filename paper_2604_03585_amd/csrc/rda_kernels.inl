@@ -348,6 +348,67 @@ k_line(const float2* in, float2* out, int lines, const float2* __restrict__ H,
     line_group<N, KIND, PREC, TWP, SPLIT, X>(in, out, lines, H, tw, scale, blockIdx.x, smem);
 }
 
+// Persistent form for long lines: a grid of the resident workgroups, each
+// walking lines blockIdx.x, + gridDim.x, ...; the next line's loads are issued
+// before the inverse transform (fused) or the transform of the current one, so
+// they and the previous stores are in flight while it computes.  One 8192- or
+// 16384-point line fills half or all of a CU's LDS, so with one line per
+// workgroup loads, transform and stores run one after another: 64 Mpx of
+// 16384-point fused lines took 315 us where the transform alone needs 176 and
+// a copy 190; this form takes 275 (8192 points: 266 -> 237; with the earlier
+// transform 393 and 305).  What makes it work:
+// nothing in the transforms reads memory (held twiddle reads, see TwAll), so
+// no wait of theirs covers the loads of the next line; the loads share one
+// address register; every value that enters the loop is pinned, so that the
+// loop's first wait does not cover its own stores.
+template <int N, int KIND>
+__global__ __launch_bounds__(LineGeom<N>::T) __attribute__((amdgpu_waves_per_eu(4))) void
+k_line_pipe(const float2* in, float2* out, int lines, const float2* __restrict__ H,
+            const float2* __restrict__ tw, float scale)
+{
+    constexpr uint32_t BYTES = N * 8u;
+    extern __shared__ __align__(16) float2 smem[];
+    const int t = threadIdx.x;
+    const uint32_t off = (uint32_t)t * 8u;
+    TwAll<N> held;
+    held.read(tw, t);
+    int line = blockIdx.x;
+    float2 x[16], nx[16];
+    load_line<N>(x, buf_rsrc(in + (size_t)line * N, BYTES), off);
+    pin_line(x);
+    held.hold();
+    for (;;) {
+        held.hold();
+        const int next = line + (int)gridDim.x;
+        const bool more = next < lines;                          // uniform
+        const __amdgpu_buffer_rsrc_t nb = buf_rsrc(in + (more ? (size_t)next * N : 0), more ? BYTES : 0u);
+        if constexpr (KIND == LK_FUSED) {
+            fft_line_held<N, false>(x, smem, held, fresh(t),
+                                    [&] { load_line<N>(nx, buf_rsrc(H, BYTES), off); });
+#pragma unroll
+            for (int m = 0; m < 16; ++m) x[m] = c_mul(x[m], nx[m]);
+            __builtin_amdgcn_sched_barrier(0);
+            load_line<N>(nx, nb, off);
+            __builtin_amdgcn_sched_barrier(0);
+            fft_line_held<N, true>(x, smem, held, fresh(t));
+        } else {
+            load_line<N>(nx, nb, off);
+            __builtin_amdgcn_sched_barrier(0);
+            fft_line_held<N, KIND == LK_INV>(x, smem, held, fresh(t));
+            if (scale != 1.0f) {
+#pragma unroll
+                for (int m = 0; m < 16; ++m) x[m] = c_scale(x[m], scale);
+            }
+        }
+        store_line<N>(x, buf_rsrc(out + (size_t)line * N, BYTES), off);
+        if (!more) break;
+        line = next;
+        __builtin_amdgcn_sched_barrier(0);
+        pin_line(nx);
+        copy_line(x, nx);
+    }
+}
+
 // Batched form: the line groups of many scenes (tasks) in one launch.  The
 // grid covers min(total groups, resident capacity) workgroups, each walking
 // groups gg = blockIdx.x, + gridDim.x, ...; the task of a group is found by
@@ -1398,6 +1459,31 @@ static hipError_t launch_k_line_x(const float2* in, float2* out, int lines, cons
     return hipGetLastError();
 }
 
+// The persistent kernel is used for fused lines of 8192 points and more and
+// single transforms of 16384 (the others run near the copy rate with one line
+// per workgroup: 8192-point forward 182 us per 64 Mpx against 197, 4096-point
+// fused inside a 4096^2 scene 205.7 us against 207.8 for the scene), once there
+// are more lines than resident workgroups (below that there is no next line to
+// load: 64 lines of 16384 take 16.2 us with k_line, 18.4 with it).
+template <int N> constexpr int pipe_resident() { return 256 * (16384 / N); }
+template <int N> static bool pipe_pays(int lines) { return lines > pipe_resident<N>(); }
+
+template <int N, int KIND>
+static hipError_t launch_pipe(const float2* in, float2* out, int lines, const float2* H,
+                              const float2* tw, float scale, hipStream_t s)
+{
+    using L = LineLaunch<N>;
+    static const hipError_t attr =
+        hipFuncSetAttribute((const void*)k_line_pipe<N, KIND>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, L::LDS_BYTES);
+    if (attr != hipSuccess) return attr;
+    const int rounds = (lines + pipe_resident<N>() - 1) / pipe_resident<N>();
+    const int grid = (lines + rounds - 1) / rounds;
+    SAR_LAUNCH((k_line_pipe<N, KIND>), dim3(grid), dim3(L::BLOCK), L::LDS_BYTES, s, in, out,
+               lines, H, tw, scale);
+    return hipGetLastError();
+}
+
 template <int N, int KIND, int PREC>
 static hipError_t launch_k_line(const float2* in, float2* out, int lines, const float2* H,
                                 const float2* tw, float scale, int variant, hipStream_t s)
@@ -1419,6 +1505,10 @@ static hipError_t launch_k_line(const float2* in, float2* out, int lines, const 
             return tab ? launch_k_line_x<N, KIND, false, false, 2>(in, out, lines, H, tw, scale, s)
                        : launch_k_line_x<N, KIND, true, false, 2>(in, out, lines, H, tw, scale, s);
         }
+    }
+    if constexpr (PREC == PREC_FP32 && (N == 16384 || (N == 8192 && KIND == LK_FUSED))) {
+        if (variant == 0 && pipe_pays<N>(lines))
+            return launch_pipe<N, KIND>(in, out, lines, H, tw, scale, s);
     }
     if constexpr (PREC == PREC_FP32 && KIND != LK_FUSED) {
         if (variant & 2) {
