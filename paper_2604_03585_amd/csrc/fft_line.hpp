@@ -493,4 +493,73 @@ __device__ __forceinline__ void fft_line_held(float2 (&x)[16], float2* __restric
     fft_held_from<N, INV, 0>(x, lds, tw, t, before_last);
 }
 
+// ---------------------------------------------------- half-LDS exchange
+// The same transform with half the LDS: the real parts of a line go through N
+// floats first, then the imaginary parts through the same floats.  It costs
+// four barriers per exchange instead of two and buys twice the lines per CU
+// (with 64 registers per thread, 32 waves): for the column strips, whose loads
+// wait long, that is worth more.
+//
+// Slot of point i after pass P: 4-byte accesses are served 64 lanes at a time
+// from 64 banks; pass 0's writes are 16 points apart (an odd pad every 64
+// points keeps them apart), pass 1's are runs of 16 points 256 apart (a pad of
+// 4 every 64).
+template <int P> __host__ __device__ constexpr int half_pads() { return P == 0 ? 1 : 4; }
+
+template <int P> __device__ __forceinline__ int half_slot(int i)
+{
+    return i + half_pads<P>() * (i >> 6);
+}
+// half_slot(t + m * T), t < T, and half_slot(base + i * NS), as in lds_in / lds_out.
+template <int T, int P> __device__ __forceinline__ int half_in(int t, int m)
+{
+    if constexpr (T >= 64) return half_slot<P>(t) + m * (T + half_pads<P>() * (T / 64));
+    else return t + (m * T + half_pads<P>() * (m * T / 64));
+}
+template <int NS, int P> __device__ __forceinline__ int half_out(int base, int i)
+{
+    return half_slot<P>(base) + i * NS + half_pads<P>() * (i * NS / 64);
+}
+
+template <int N, int P>
+__device__ __forceinline__ void half_exchange(float2 (&x)[16], float* __restrict__ lds, int t)
+{
+    constexpr int NS = LineGeom<N>::span(P), T = LineGeom<N>::T;
+    const int base = (t / NS) * NS * 16 + (t & (NS - 1));
+#pragma unroll
+    for (int i = 0; i < 16; ++i) lds[half_out<NS, P>(base, i)] = x[i].x;
+    wg_barrier();
+#pragma unroll
+    for (int m = 0; m < 16; ++m) x[m].x = lds[half_in<T, P>(t, m)];
+    wg_barrier();
+#pragma unroll
+    for (int i = 0; i < 16; ++i) lds[half_out<NS, P>(base, i)] = x[i].y;
+    wg_barrier();
+#pragma unroll
+    for (int m = 0; m < 16; ++m) x[m].y = lds[half_in<T, P>(t, m)];
+    wg_barrier();
+}
+
+template <int N, bool INV, int P>
+__device__ __forceinline__ void fft_half_from(float2 (&x)[16], float* __restrict__ lds,
+                                              const float2* __restrict__ tw, int t)
+{
+    if constexpr (P < LineGeom<N>::NP) {
+        TwReads<N, P, true> now;
+        tw_issue<N, P, true>(now, tw, fresh(t));
+        TwSet cur;
+        tw_form<N, P, true>(cur, now);
+        pass_butterflies<N, P, INV>(x, cur);
+        if constexpr (P < LineGeom<N>::NP - 1) half_exchange<N, P>(x, lds, t);
+        fft_half_from<N, INV, P + 1>(x, lds, tw, t);
+    }
+}
+
+template <int N, bool INV>
+__device__ __forceinline__ void fft_line_half(float2 (&x)[16], float* __restrict__ lds,
+                                              const float2* __restrict__ tw, int t)
+{
+    fft_half_from<N, INV, 0>(x, lds, tw, t);
+}
+
 }  // namespace sar

@@ -341,23 +341,23 @@ sar_status step_azimuth(const sar_plan_s* P, const void* in, void* out, void* wo
 }
 
 // Turn-free schedule: no corner turn.  The azimuth pass reads strips of
-// adjacent azimuth lines straight from the range pass's [Na][Nr] output.
-//   LFM:        raw -> range -> work [Na][Nr] -> strips FFT*H*IFFT -> img [Nr][Na]
-//   hyperbolic: raw -> range -> img [Na][Nr] -> strips FFT -> work [Nr][Na]
+// adjacent azimuth lines straight from the range pass's output, which is kept
+// in tiles of 32 columns (TileMap in rda_kernels.inl).
+//   LFM:        raw -> range -> work (tiles) -> strips FFT*H*IFFT -> img [Nr][Na]
+//   hyperbolic: raw -> range -> img (tiles) -> strips FFT -> work [Nr][Na]
 //               -> RCMC*phase*IFFT -> img [Nr][Na]
 sar_status execute_turn_free(const sar_plan_s* P, const void* raw, void* img, void* work,
                              hipStream_t s)
 {
     const int Nr = P->p.Nr, Na = P->p.Na;
-    sar_status st;
     if (P->p.az_model == SAR_AZ_LFM) {
-        if ((st = step_range(P, raw, work, s))) return st;
-        HIP_TRY(sar::launch_line_strip(true, Na, work, img, Nr, Nr, P->Ha, P->tw_a, 1.f, P->var_strip, s),
+        HIP_TRY(sar::launch_range_tiled(Nr, raw, work, Na, P->Hr, P->tw_r, s), "range launch (column tiles)");
+        HIP_TRY(sar::launch_line_strip(true, Na, work, img, Nr, P->Ha, P->tw_a, 1.f, P->var_strip, s),
                 "azimuth strip launch");
         return SAR_OK;
     }
-    if ((st = step_range(P, raw, img, s))) return st;
-    HIP_TRY(sar::launch_line_strip(false, Na, img, work, Nr, Nr, nullptr, P->tw_a, 1.f, P->var_strip,
+    HIP_TRY(sar::launch_range_tiled(Nr, raw, img, Na, P->Hr, P->tw_r, s), "range launch (column tiles)");
+    HIP_TRY(sar::launch_line_strip(false, Na, img, work, Nr, nullptr, P->tw_a, 1.f, P->var_strip,
                                    s),
             "azimuth strip FFT launch");
     const sar::RcmcHost rh = rcmc_host(P);

@@ -70,12 +70,16 @@ hipError_t launch_line(LineOp op, int n, const void* in, void* out, int lines, c
                        hipStream_t s);
 int twiddle_table_size(int n);
 
-// Column-strip azimuth pass (turn-free schedule, FP32, n <= 4096): the n-point
-// azimuth lines of range cells 0 .. cols-1, read from in [n][pitch] (the range
-// pass's output), transformed (fused: IFFT(FFT * H); else FFT * scale) and
-// stored as lines out [cols][n].  cols must be a multiple of the strip width
-// min(16, 1024 / (n / 16)).
-hipError_t launch_line_strip(bool fused, int n, const void* in, void* out, int cols, int pitch,
+// Range pass of the turn-free schedules: fused lines [na][n] stored in column
+// tiles (TileMap in rda_kernels.inl; same size as [na][n]), na a multiple of 64.
+hipError_t launch_range_tiled(int n, const void* in, void* out, int na, const void* H, const void* tw,
+                              hipStream_t s);
+
+// Column-strip azimuth pass (turn-free schedules, FP32, n <= 4096): the n-point
+// azimuth lines of range cells 0 .. cols-1, read from the column tiles `in` that
+// launch_range_tiled wrote, transformed (fused: IFFT(FFT * H); else FFT * scale)
+// and stored as lines out [cols][n].  cols must be a multiple of 32.
+hipError_t launch_line_strip(bool fused, int n, const void* in, void* out, int cols,
                              const void* H, const void* tw, float scale, int variant, hipStream_t s);
 
 // Batched launches (kind: 0 fused, 1 forward, 2 inverse; tasks in device memory).

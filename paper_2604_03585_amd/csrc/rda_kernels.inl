@@ -193,6 +193,10 @@ __device__ __forceinline__ float2 buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t voff
 {
     return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
 }
+__device__ __forceinline__ float4 buf_ld4(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
+{
+    return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+}
 __device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, float2 v)
 {
     typedef unsigned int u2_t __attribute__((ext_vector_type(2)));
@@ -215,6 +219,52 @@ __device__ __forceinline__ void store_line(const float2 (&x)[line_e(N)], __amdgp
 {
 #pragma unroll
     for (int m = 0; m < line_e(N); ++m) buf_st(dst, off, m * LineGeom<N>::T * 8u, x[m]);
+}
+
+// Column tiles: the range output between the two passes of the turn-free
+// schedules.  Element (m, n) of [na][nr] sits at
+//     ((n / 32) na + (m ^ (n / 32 & key_mask))) 32 + n % 32 ,
+// i.e. tiles of 32 columns (256-byte rows) one after another.  A strip of
+// adjacent azimuth lines then reads its C * 8-byte runs 256 bytes apart instead
+// of nr * 8 bytes apart, where (nr a power of two) every row of a strip falls
+// into the same few memory channels.  The exclusive or does the same for the
+// range pass, whose pieces of one line are na * 256 bytes apart: it moves
+// neighbouring tiles' rows to different channels (128 of them, 256 bytes each).
+// 4096 x 4096: the strip copy 92 -> 63 us, range + strip FFT 142 -> 114 us,
+// the range pass itself unchanged (57 us).
+struct TileMap {
+    int na;          // rows (azimuth samples)
+    int key_mask;    // min(127, na - 1)
+};
+constexpr int TILE_COLS = 32;
+
+// Store the points t + m*T of line line0 + sub of the [na][N] array in column
+// tiles (LPW lines per workgroup, line0 a multiple of LPW, na one of 64).
+template <int N, int LPW>
+__device__ __forceinline__ void store_line_tiled(const float2 (&x)[16], float2* out, const TileMap& tm,
+                                                 int line0, int sub, int t)
+{
+    constexpr int T = LineGeom<N>::T, TT32 = T / TILE_COLS;
+    const __amdgpu_buffer_rsrc_t ob = buf_rsrc(out, (uint32_t)tm.na * (uint32_t)N * 8u);
+    if constexpr (TT32 >= LPW) {
+        // tile = t / 32 + m TT32: its low bits meet the lane's part of the row
+        // number, the others the workgroup's, so one vector offset serves all m
+        const int lo = ((line0 + sub) & (TT32 - 1)) ^ (t / TILE_COLS);
+        const uint32_t off = (uint32_t)(((t / TILE_COLS) * tm.na + lo) * TILE_COLS + t % TILE_COLS) * 8u;
+        const int hi = line0 & ~(TT32 - 1);
+#pragma unroll
+        for (int m = 0; m < 16; ++m)
+            buf_st(ob, off, (uint32_t)((m * TT32) * tm.na + (hi ^ ((m * TT32) & tm.key_mask))) * (TILE_COLS * 8u),
+                   x[m]);
+    } else {
+        const int line = line0 + sub;
+#pragma unroll
+        for (int m = 0; m < 16; ++m) {
+            const int n = t + m * T, tile = n / TILE_COLS;
+            const uint32_t e = (uint32_t)((tile * tm.na + (line ^ (tile & tm.key_mask))) * TILE_COLS + n % TILE_COLS);
+            buf_st(ob, e * 8u, 0, x[m]);
+        }
+    }
 }
 
 // One workgroup per group of LPW lines.
@@ -279,60 +329,127 @@ __device__ __forceinline__ void line_group(const float2* in, float2* out, int li
     store_line<N>(x, buf_rsrc(out + first, bytes), off);
 }
 
+// The range pass of the turn-free schedules: fused lines stored in column tiles.
+template <int N>
+__global__ __launch_bounds__((LineLaunch<N>::BLOCK))
+__attribute__((amdgpu_waves_per_eu(line_wpe<N, PREC_FP32>()))) void
+k_line_tiled(const float2* in, float2* out, const float2* __restrict__ H,
+             const float2* __restrict__ tw, TileMap tm)
+{
+    using L = LineLaunch<N>;
+    extern __shared__ __align__(16) float2 smem[];
+    const int sub = threadIdx.x / L::T, t = threadIdx.x % L::T, line0 = blockIdx.x * L::LPW;
+    float2 x[16];
+    load_line<N>(x, buf_rsrc(in + (size_t)line0 * N, L::LPW * N * 8u), (uint32_t)(sub * N + t) * 8u);
+    line_transform<N, LK_FUSED, PREC_FP32, true>(x, smem + sub * LineGeom<N>::LDS, H, tw, 1.0f, sub, t);
+    store_line_tiled<N, L::LPW>(x, out, tm, line0, sub, t);
+}
+
 // ---------------------------------------------------------- column strips
-// Turn-free schedule: the azimuth lines of a strip of C adjacent range cells
-// read straight from the range pass's [Na][Nr] output, so no corner turn is
-// needed.  Each row of the strip is C consecutive samples (C * 8 bytes: 32 B
-// at 4096 points, 64 B at 2048, 128 B at 1024 and below); the workgroup
-// reads the C x N strip with consecutive lanes on consecutive sample pairs,
-// regroups it through LDS into one line per slot of T = N/16 threads, runs
-// the same line transform as k_line (so the results are bit-identical to
-// the turned path) and stores each line contiguously: out is [Nr][Na].
-// C = min(16, 1024 / T) lines per workgroup (N <= 4096: 136 KiB of LDS), or
-// CW lines (the autotuner's half-width candidate).
+// Turn-free schedules: the azimuth lines of a strip of C adjacent range cells
+// are read straight from the range output (column tiles), so no corner turn is
+// needed.  Each row of the strip is C consecutive samples; the workgroup reads
+// the C x N strip with consecutive lanes on consecutive sample pairs, regroups
+// it through LDS into one line per slot of T = N/16 threads, runs the same
+// butterflies as k_line (so the results are bit-identical to the turned path)
+// and stores each line contiguously: out is [Nr][Na].
+//
+// What bounds it is how many loads are in flight and what each request brings.
+// The line exchange and the regrouping go through half the LDS (fft_line_half)
+// at 64 registers per thread, so a CU holds 2048 threads: two workgroups of 4
+// lines at 4096 points (one before), which load, transform and store out of
+// step.  C: as many lines as 1024 threads take, up to 8 (64-byte runs; 16 lines
+// were no faster and left fewer workgroups).  4096 x 4096 strip FFT after a
+// range pass: 75 -> 57 us, fused 86 -> 78.
 template <int N, int CW = 0> struct StripLaunch {
     static constexpr int T = LineGeom<N>::T;
-    static constexpr int C_DEFAULT = (1024 / T) < 16 ? 1024 / T : 16;
+    static constexpr int C_DEFAULT = (1024 / T) < 8 ? 1024 / T : (T >= 8 ? 8 : 16);
     static constexpr int C = CW ? CW : C_DEFAULT;
     static constexpr int BLOCK = C * T;
-    // line buffers 16 float2 more than a line's exchange buffer apart, so
-    // the C samples of one row (consecutive lanes) fall into different banks
-    static constexpr int STRIDE = LineGeom<N>::LDS + 16;
-    static constexpr int LDS_BYTES = C * STRIDE * (int)sizeof(float2);
-    static_assert(N <= 4096 && C >= 2 && C <= C_DEFAULT, "strips of two lines or more");
+    // lines 64 / C floats more than a multiple of 64 apart: the C samples of a
+    // row and the rows of a wave fall into different banks
+    static constexpr int STRIDE = (N + N / 16 + 63) / 64 * 64 + 64 / C;
+    static constexpr int LDS_BYTES = C * STRIDE * (int)sizeof(float);
+    static_assert(N <= 8192 && C >= 2 && C <= 16, "strips of two lines or more");
 };
 
-template <int N, int KIND, bool TWP, int CW = 0>
-__global__ __launch_bounds__((StripLaunch<N, CW>::BLOCK)) void
-k_line_strip(const float2* __restrict__ in, float2* __restrict__ out, int cols, int pitch,
+// Source of a strip: rows `row_bytes` apart, row m of it at row m ^ key.
+struct StripSrc {
+    const float2* base;      // sample (row 0, first column) for key = 0
+    uint32_t bytes;          // readable bytes from base
+    int key;
+};
+__device__ __forceinline__ StripSrc strip_source(const float2* in, const TileMap& tm, int cols, int n0)
+{
+    const int tile = n0 / TILE_COLS;
+    StripSrc s;
+    s.base = in + (size_t)tile * tm.na * TILE_COLS + n0 % TILE_COLS;
+    s.bytes = (uint32_t)((cols / TILE_COLS - tile) * tm.na) * (TILE_COLS * 8u) - (uint32_t)(n0 % TILE_COLS) * 8u;
+    s.key = tile & tm.key_mask;
+    return s;
+}
+
+template <int N, int KIND, int CW = 0>
+__global__ __launch_bounds__((StripLaunch<N, CW>::BLOCK))
+__attribute__((amdgpu_waves_per_eu(N == 512 ? 7 : 8))) void      // 512 points spill at 64 registers
+k_line_strip(const float2* __restrict__ in, float2* __restrict__ out, int cols, TileMap tm,
              const float2* __restrict__ H, const float2* __restrict__ tw, float scale)
 {
     using S = StripLaunch<N, CW>;
-    constexpr int T = S::T, C = S::C, E = line_e(N);
-    static_assert(S::BLOCK * E == C * N, "one sample per thread and pass");
-    extern __shared__ __align__(16) float2 smem[];
+    constexpr int T = S::T, C = S::C;
+    constexpr uint32_t ROW = TILE_COLS * 8u;      // bytes between rows of a tile
+    extern __shared__ __align__(16) float2 smem2[];
+    float* smem = (float*)smem2;
     const int g = xcd_group(blockIdx.x, cols / C);
     const int n0 = g * C;
     const int u = threadIdx.x;
-    // 16-byte loads: lanes take pairs of adjacent columns, C / 2 lanes per
-    // row (fewer, wider requests for the same short runs)
+    const StripSrc src = strip_source(in, tm, cols, n0);
+    const __amdgpu_buffer_rsrc_t ib = buf_rsrc(src.base, src.bytes);
+    // 16-byte loads: lanes take pairs of adjacent columns, C / 2 lanes per row,
+    // rows m0 + 2 T p; the row's exclusive or splits into the lane's and the
+    // load's part because m0 < 2 T
     static_assert(C % 2 == 0, "pairs of columns");
+    const int m0 = u / (C / 2), q = u % (C / 2);
+    const uint32_t voff = (uint32_t)(m0 ^ (src.key & (2 * T - 1))) * ROW + (uint32_t)q * 16u;
+    float4 v[8];
 #pragma unroll
-    for (int p = 0; p < E / 2; ++p) {
-        const int e = u + p * S::BLOCK;           // pair (row m, columns 2q, 2q+1) of the strip
-        const int m = e / (C / 2), q = e % (C / 2);
-        const float4 v = *(const float4*)(in + (size_t)m * pitch + n0 + 2 * q);
-        smem[(2 * q) * S::STRIDE + lds_slot<0>(m)] = make_float2(v.x, v.y);
-        smem[(2 * q + 1) * S::STRIDE + lds_slot<0>(m)] = make_float2(v.z, v.w);
-    }
-    __syncthreads();
+    for (int p = 0; p < 8; ++p)
+        v[p] = buf_ld4(ib, voff, (uint32_t)((2 * T * p) ^ (src.key & ~(2 * T - 1))) * ROW);
     const int sub = u / T, t = u % T;
-    float2* lds = smem + sub * S::STRIDE;
-    float2 x[E];
+    float* row0 = smem + 2 * q * S::STRIDE;
+    float* lds = smem + sub * S::STRIDE;
+    float2 x[16];
 #pragma unroll
-    for (int m = 0; m < E; ++m) x[m] = lds[lds_in<T, 0>(t, m)];
-    __syncthreads();                              // reads done before the exchanges
-    line_transform<N, KIND, PREC_FP32, TWP>(x, lds, H, tw, scale, sub, t);
+    for (int p = 0; p < 8; ++p) {
+        row0[half_in<2 * T, 0>(m0, p)] = v[p].x;
+        row0[S::STRIDE + half_in<2 * T, 0>(m0, p)] = v[p].z;
+    }
+    wg_barrier();
+#pragma unroll
+    for (int m = 0; m < 16; ++m) x[m].x = lds[half_in<T, 0>(t, m)];
+    wg_barrier();
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+        row0[half_in<2 * T, 0>(m0, p)] = v[p].y;
+        row0[S::STRIDE + half_in<2 * T, 0>(m0, p)] = v[p].w;
+    }
+    wg_barrier();
+#pragma unroll
+    for (int m = 0; m < 16; ++m) x[m].y = lds[half_in<T, 0>(t, m)];
+    wg_barrier();
+    if constexpr (KIND == LK_FUSED) {
+        fft_line_half<N, false>(x, lds, tw, t);
+        const __amdgpu_buffer_rsrc_t hb = buf_rsrc(H, N * 8u);
+#pragma unroll
+        for (int m = 0; m < 16; ++m) x[m] = c_mul(x[m], buf_ld(hb, (uint32_t)t * 8u, m * T * 8u));
+        fft_line_half<N, true>(x, lds, tw, t);
+    } else {
+        fft_line_half<N, KIND == LK_INV>(x, lds, tw, t);
+        if (scale != 1.0f) {
+#pragma unroll
+            for (int m = 0; m < 16; ++m) x[m] = c_scale(x[m], scale);
+        }
+    }
     store_line<N>(x, buf_rsrc(out + (size_t)n0 * N, C * N * 8u), (uint32_t)(sub * N + t) * 8u);
 }
 
@@ -361,10 +478,11 @@ k_line(const float2* in, float2* out, int lines, const float2* __restrict__ H,
 // no wait of theirs covers the loads of the next line; the loads share one
 // address register; every value that enters the loop is pinned, so that the
 // loop's first wait does not cover its own stores.
-template <int N, int KIND>
+// TILED: stored in column tiles (tm), else line after line.
+template <int N, int KIND, bool TILED = false>
 __global__ __launch_bounds__(LineGeom<N>::T) __attribute__((amdgpu_waves_per_eu(4))) void
 k_line_pipe(const float2* in, float2* out, int lines, const float2* __restrict__ H,
-            const float2* __restrict__ tw, float scale)
+            const float2* __restrict__ tw, float scale, TileMap tm)
 {
     constexpr uint32_t BYTES = N * 8u;
     extern __shared__ __align__(16) float2 smem[];
@@ -400,7 +518,8 @@ k_line_pipe(const float2* in, float2* out, int lines, const float2* __restrict__
                 for (int m = 0; m < 16; ++m) x[m] = c_scale(x[m], scale);
             }
         }
-        store_line<N>(x, buf_rsrc(out + (size_t)line * N, BYTES), off);
+        if constexpr (TILED) store_line_tiled<N, 1>(x, out, tm, line, 0, t);
+        else store_line<N>(x, buf_rsrc(out + (size_t)line * N, BYTES), off);
         if (!more) break;
         line = next;
         __builtin_amdgcn_sched_barrier(0);
@@ -1468,19 +1587,19 @@ static hipError_t launch_k_line_x(const float2* in, float2* out, int lines, cons
 template <int N> constexpr int pipe_resident() { return 256 * (16384 / N); }
 template <int N> static bool pipe_pays(int lines) { return lines > pipe_resident<N>(); }
 
-template <int N, int KIND>
+template <int N, int KIND, bool TILED>
 static hipError_t launch_pipe(const float2* in, float2* out, int lines, const float2* H,
-                              const float2* tw, float scale, hipStream_t s)
+                              const float2* tw, float scale, TileMap tm, hipStream_t s)
 {
     using L = LineLaunch<N>;
     static const hipError_t attr =
-        hipFuncSetAttribute((const void*)k_line_pipe<N, KIND>,
+        hipFuncSetAttribute((const void*)k_line_pipe<N, KIND, TILED>,
                             hipFuncAttributeMaxDynamicSharedMemorySize, L::LDS_BYTES);
     if (attr != hipSuccess) return attr;
     const int rounds = (lines + pipe_resident<N>() - 1) / pipe_resident<N>();
     const int grid = (lines + rounds - 1) / rounds;
-    SAR_LAUNCH((k_line_pipe<N, KIND>), dim3(grid), dim3(L::BLOCK), L::LDS_BYTES, s, in, out,
-               lines, H, tw, scale);
+    SAR_LAUNCH((k_line_pipe<N, KIND, TILED>), dim3(grid), dim3(L::BLOCK), L::LDS_BYTES, s, in, out,
+               lines, H, tw, scale, tm);
     return hipGetLastError();
 }
 
@@ -1508,7 +1627,7 @@ static hipError_t launch_k_line(const float2* in, float2* out, int lines, const 
     }
     if constexpr (PREC == PREC_FP32 && (N == 16384 || (N == 8192 && KIND == LK_FUSED))) {
         if (variant == 0 && pipe_pays<N>(lines))
-            return launch_pipe<N, KIND>(in, out, lines, H, tw, scale, s);
+            return launch_pipe<N, KIND, false>(in, out, lines, H, tw, scale, TileMap{}, s);
     }
     if constexpr (PREC == PREC_FP32 && KIND != LK_FUSED) {
         if (variant & 2) {
@@ -1704,44 +1823,85 @@ hipError_t launch_line_fp32(LineOp op, int n, const float2* i, float2* o, int li
     return launch_line_prec<PREC_FP32>(op, n, i, o, lines, h, w, scale, ra, taps, v, s);
 }
 #elif SAR_PART == 4
+static TileMap tile_map(int na) { return TileMap{na, na < 128 ? na - 1 : 127}; }
+
+template <int N>
+static hipError_t launch_range_tiled_n(const float2* in, float2* out, int na, const float2* H,
+                                       const float2* tw, hipStream_t s)
+{
+    using L = LineLaunch<N>;
+    const TileMap tm = tile_map(na);
+    if constexpr (N >= 8192) {
+        if (pipe_pays<N>(na)) return launch_pipe<N, LK_FUSED, true>(in, out, na, H, tw, 1.0f, tm, s);
+    }
+    static const hipError_t attr =
+        L::LDS_BYTES <= 64 * 1024
+            ? hipSuccess
+            : hipFuncSetAttribute((const void*)k_line_tiled<N>,
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, L::LDS_BYTES);
+    if (attr != hipSuccess) return attr;
+    SAR_LAUNCH((k_line_tiled<N>), dim3(na / L::LPW), dim3(L::BLOCK), L::LDS_BYTES, s, in, out, H, tw, tm);
+    return hipGetLastError();
+}
+
+hipError_t launch_range_tiled(int n, const void* in, void* out, int na, const void* H, const void* tw,
+                              hipStream_t s)
+{
+    if (na < 64 || (na & 63) != 0) return hipErrorInvalidValue;   // whole workgroups and tiles
+    auto i = (const float2*)in;
+    auto o = (float2*)out;
+    auto h = (const float2*)H;
+    auto w = (const float2*)tw;
+    switch (n) {
+    case 64: return launch_range_tiled_n<64>(i, o, na, h, w, s);
+    case 128: return launch_range_tiled_n<128>(i, o, na, h, w, s);
+    case 256: return launch_range_tiled_n<256>(i, o, na, h, w, s);
+    case 512: return launch_range_tiled_n<512>(i, o, na, h, w, s);
+    case 1024: return launch_range_tiled_n<1024>(i, o, na, h, w, s);
+    case 2048: return launch_range_tiled_n<2048>(i, o, na, h, w, s);
+    case 4096: return launch_range_tiled_n<4096>(i, o, na, h, w, s);
+    case 8192: return launch_range_tiled_n<8192>(i, o, na, h, w, s);
+    case 16384: return launch_range_tiled_n<16384>(i, o, na, h, w, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 template <int N, int KIND, int CW>
-static hipError_t launch_strip_k(const float2* in, float2* out, int cols, int pitch,
-                                 const float2* H, const float2* tw, float scale, hipStream_t s)
+static hipError_t launch_strip_k(const float2* in, float2* out, int cols, const float2* H,
+                                 const float2* tw, float scale, hipStream_t s)
 {
     using S = StripLaunch<N, CW>;
     static const hipError_t attr =
         S::LDS_BYTES <= 64 * 1024
             ? hipSuccess
-            : hipFuncSetAttribute((const void*)k_line_strip<N, KIND, true, CW>,
+            : hipFuncSetAttribute((const void*)k_line_strip<N, KIND, CW>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS_BYTES);
     if (attr != hipSuccess) return attr;
-    // whole strips; 16-byte pair loads need an even pitch and an aligned base
-    if (cols % S::C != 0 || (pitch & 1) || ((uintptr_t)in & 15u)) return hipErrorInvalidValue;
+    // whole strips and tiles; 16-byte pair loads need an aligned base
+    if (cols % TILE_COLS != 0 || ((uintptr_t)in & 15u)) return hipErrorInvalidValue;
     if (cols == 0) return hipSuccess;
-    SAR_LAUNCH((k_line_strip<N, KIND, true, CW>), dim3(cols / S::C), dim3(S::BLOCK), S::LDS_BYTES,
-               s, in, out, cols, pitch, H, tw, scale);
+    SAR_LAUNCH((k_line_strip<N, KIND, CW>), dim3(cols / S::C), dim3(S::BLOCK), S::LDS_BYTES,
+               s, in, out, cols, tile_map(N), H, tw, scale);
     return hipGetLastError();
 }
 
-// Twiddles by products only: the strips' 1024-thread workgroups hold 128
-// VGPRs, where the table-twiddle transforms spill.  Variant 1: strips of
-// half the default width (C / 2 lines: half the LDS and threads per
-// workgroup, runs of C / 2 samples).
+// Twiddles by products only.  Variant 1: strips of half the default width (C / 2
+// lines: half the LDS and threads per workgroup, runs of C / 2 samples).
 template <int N>
-static hipError_t launch_strip_n(bool fused, const float2* in, float2* out, int cols, int pitch,
+static hipError_t launch_strip_n(bool fused, const float2* in, float2* out, int cols,
                                  const float2* H, const float2* tw, float scale, int variant,
                                  hipStream_t s)
 {
     constexpr int HALF = StripLaunch<N>::C_DEFAULT / 2;
     if (variant == 1) {
-        if (fused) return launch_strip_k<N, LK_FUSED, HALF>(in, out, cols, pitch, H, tw, 1.f, s);
-        return launch_strip_k<N, LK_FWD, HALF>(in, out, cols, pitch, nullptr, tw, scale, s);
+        if (fused) return launch_strip_k<N, LK_FUSED, HALF>(in, out, cols, H, tw, 1.f, s);
+        return launch_strip_k<N, LK_FWD, HALF>(in, out, cols, nullptr, tw, scale, s);
     }
-    if (fused) return launch_strip_k<N, LK_FUSED, 0>(in, out, cols, pitch, H, tw, 1.f, s);
-    return launch_strip_k<N, LK_FWD, 0>(in, out, cols, pitch, nullptr, tw, scale, s);
+    if (fused) return launch_strip_k<N, LK_FUSED, 0>(in, out, cols, H, tw, 1.f, s);
+    return launch_strip_k<N, LK_FWD, 0>(in, out, cols, nullptr, tw, scale, s);
 }
 
-hipError_t launch_line_strip(bool fused, int n, const void* in, void* out, int cols, int pitch,
+hipError_t launch_line_strip(bool fused, int n, const void* in, void* out, int cols,
                              const void* H, const void* tw, float scale, int variant, hipStream_t s)
 {
     auto i = (const float2*)in;
@@ -1749,13 +1909,13 @@ hipError_t launch_line_strip(bool fused, int n, const void* in, void* out, int c
     auto h = (const float2*)H;
     auto w = (const float2*)tw;
     switch (n) {
-    case 64: return launch_strip_n<64>(fused, i, o, cols, pitch, h, w, scale, variant, s);
-    case 128: return launch_strip_n<128>(fused, i, o, cols, pitch, h, w, scale, variant, s);
-    case 256: return launch_strip_n<256>(fused, i, o, cols, pitch, h, w, scale, variant, s);
-    case 512: return launch_strip_n<512>(fused, i, o, cols, pitch, h, w, scale, variant, s);
-    case 1024: return launch_strip_n<1024>(fused, i, o, cols, pitch, h, w, scale, variant, s);
-    case 2048: return launch_strip_n<2048>(fused, i, o, cols, pitch, h, w, scale, variant, s);
-    case 4096: return launch_strip_n<4096>(fused, i, o, cols, pitch, h, w, scale, variant, s);
+    case 64: return launch_strip_n<64>(fused, i, o, cols, h, w, scale, variant, s);
+    case 128: return launch_strip_n<128>(fused, i, o, cols, h, w, scale, variant, s);
+    case 256: return launch_strip_n<256>(fused, i, o, cols, h, w, scale, variant, s);
+    case 512: return launch_strip_n<512>(fused, i, o, cols, h, w, scale, variant, s);
+    case 1024: return launch_strip_n<1024>(fused, i, o, cols, h, w, scale, variant, s);
+    case 2048: return launch_strip_n<2048>(fused, i, o, cols, h, w, scale, variant, s);
+    case 4096: return launch_strip_n<4096>(fused, i, o, cols, h, w, scale, variant, s);
     default: return hipErrorInvalidValue;
     }
 }
