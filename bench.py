@@ -24,7 +24,7 @@ Besides the headline it measures, each on the same GPU:
                 stream, launched back to back by sar_rda_execute), from HIP
                 events that the kernel's own dispatch records at its start
                 and end (the slowest kernel carries the roofline figure);
-  fused_turned  the same scene through the fused schedule with its corner
+  fused_turned  the same scene through the step entry points with a corner
                 turn (64 B/px), with its kernels, and whether its image
                 equals the turn-free one bit for bit;
   hbm_copy_gbs  a plain device copy of one 128 MiB scene buffer (read + write
@@ -188,7 +188,7 @@ class Timer:
 
 
 N_SETS = 3   # buffer sets the timed steps rotate through (3 x 384 MiB >> the 256 MiB MALL)
-KERNELS = {   # the kernels sar_rda_execute launches for the 4096^2 hyperbolic scene
+KERNELS = {   # the kernels of the 4096^2 hyperbolic scene: in sar_rda_execute, and step by step
     "turn_free": ["range_fused", "azimuth_strip_fft", "rcmc_azimuth"],
     "fused": ["range_fused", "corner_turn", "azimuth_fft", "rcmc_azimuth"],
 }
@@ -216,7 +216,15 @@ def headline(args, torch, sar, cfg, raw, dev):
             i = it[0] % N_SETS
             it[0] += 1
             sar.sar_rda_execute(h, raws[i], imgs[i], works[i], stream)
-        return step
+
+        def turned():      # the same scene through the step entry points, with a corner turn
+            i = it[0] % N_SETS
+            it[0] += 1
+            sar.sar_range_compress(h, raws[i], works[i], stream)
+            sar.sar_corner_turn(h, works[i], imgs[i], Na, Nr, stream)
+            sar.sar_azimuth_fft(h, imgs[i], works[i], stream)
+            sar.sar_rcmc_azimuth(h, works[i], imgs[i], stream)
+        return turned if plan is plans["fused"] else step
 
     def breakdown(plan, names, reps):
         """Per-kernel durations of whole steps: the events of every kernel
@@ -245,7 +253,7 @@ def headline(args, torch, sar, cfg, raw, dev):
     images = {"fp32": imgs[last].cpu().numpy()}
     kern = breakdown(plans["turn_free"], KERNELS["turn_free"], args.kernel_reps)
 
-    # ---- the same scene with the corner turn (fused schedule), timed the
+    # ---- the same scene with the corner turn (step by step), timed the
     # same way; its image must equal the turn-free one bit for bit ----
     ms_turned, _ = timed(stepper(plans["fused"]), args.steps, args.warmup)
     torch.cuda.synchronize()

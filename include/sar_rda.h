@@ -111,7 +111,10 @@ typedef enum { SAR_FUSED = 0, SAR_UNFUSED = 1, SAR_TURN_FREE = 2 } sar_schedule;
  *                  output (FP32, Na <= 4096, transpose_back = 0; else
  *                  SAR_ERR_UNSUPPORTED).  Images are bit-identical to
  *                  SAR_FUSED's; the step entry points behave as for
- *                  SAR_FUSED.
+ *                  SAR_FUSED.  sar_rda_execute runs SAR_FUSED plans the same
+ *                  way where those kernels cover them (FP32, Na <= 4096, no
+ *                  tuned table twiddles): the corner turn then falls away,
+ *                  the image stays the same bit for bit.
  *  transpose_back  0: sar_rda_execute leaves the image as [Nr][Na];
  *                  1: it is turned back to [Na][Nr].
  */
@@ -206,9 +209,9 @@ sar_status sar_rda_execute_noalloc(sar_plan_t plan, const void* raw_dev, void* i
  * hipEvent_t the caller created with timing enabled and keeps alive until
  * they have completed.  n = 0 disarms; n outside 0..16 is SAR_ERR_BAD_SIZE,
  * a NULL array or event SAR_ERR_NULL (nothing armed then).  sar_rda_execute
- * launches 4 kernels for a fused FP32 hyperbolic plan (range, corner turn,
- * azimuth FFT, RCMC), 3 for LFM or for SAR_TURN_FREE hyperbolic, 2 for
- * SAR_TURN_FREE LFM. */
+ * launches 3 kernels for a hyperbolic plan without the corner turn (range,
+ * azimuth strip FFT, RCMC) and 2 for LFM; with the corner turn (see the
+ * schedules above) 4 and 3. */
 sar_status sar_time_next_launches(void* const* start_events, void* const* stop_events, int32_t n);
 
 /* ---- individual steps, for step-by-step testing and the unfused path ---- */
@@ -253,8 +256,7 @@ sar_status sar_plan_get_table(sar_plan_t plan, int32_t which, void* host_dst,
  * other scene (hyperbolic, unfused, half storage, and any scene of 2^22
  * pixels or more, which fills the GPU with its own launches) runs as
  * sar_rda_execute in the same stream, in scene order, after the shared
- * launches; those of 2^22 pixels or more with the fused schedule in FP32,
- * Na <= 4096 and no back-turn run the turn-free kernels (SAR_TURN_FREE).
+ * launches.
  * Each scene's image is bit-identical to its own sar_rda_execute.
  */
 

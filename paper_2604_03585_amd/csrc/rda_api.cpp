@@ -10,6 +10,8 @@
 //   hyperbolic: range [Na][Nr] -> turn -> azimuth FFT -> RCMC*phase*IFFT
 //   optional:   -> turn back to [Na][Nr]
 //
+// Where the strip kernels cover a plan the turn falls away (execute_strips).
+//
 // With SAR_UNFUSED every "FFT*H*IFFT" is three dispatches and RCMC*phase*IFFT
 // is three dispatches as well (the comparator of Sec. II.B, Fig. 1).
 #include "sar_rda.h"
@@ -340,31 +342,55 @@ sar_status step_azimuth(const sar_plan_s* P, const void* in, void* out, void* wo
     return SAR_OK;
 }
 
-// Turn-free schedule: no corner turn.  The azimuth pass reads strips of
-// adjacent azimuth lines straight from the range pass's output, which is kept
-// in tiles of 32 columns (TileMap in rda_kernels.inl).
-//   LFM:        raw -> range -> work (tiles) -> strips FFT*H*IFFT -> img [Nr][Na]
+// Whether sar_rda_execute runs without the corner turn: always for the turn-free
+// schedule, and for the fused one where the strip kernels cover the plan (FP32,
+// azimuth lines of up to 4096) and compute the same bits: they form twiddles by
+// products, so a plan tuned to table twiddles keeps its corner turn.  Long lines
+// over few range cells keep it too: a strip is one workgroup of up to 1024
+// threads, and 256 range cells make only 128 of them (4096 x 256 LFM: 20.8 us
+// turned, 22.2 in strips; 4096 x 512: 30.5 and 27.4).  Elsewhere the strips were
+// faster at every size measured, 64 x 256 to 4096 x 8192 (1.1 to 1.5 times: 4096^2
+// hyperbolic 187 us against 225, 1024 x 2048 LFM 24 against 32).
+bool runs_strips(const sar_plan_s* P)
+{
+    const sar_params& p = P->p;
+    if (p.schedule == SAR_TURN_FREE) return true;
+    const bool lfm = p.az_model == SAR_AZ_LFM;
+    const int least_nr = p.Na < 2048 ? 0 : (lfm && !p.transpose_back ? 512 : 256);
+    return p.schedule == SAR_FUSED && p.precision == SAR_FP32 && p.Na <= 4096 && p.Nr >= least_nr &&
+           !((P->var_r[sar::TK_FUSED] | P->var_a[lfm ? sar::TK_FUSED : sar::TK_FWD]) & 1);
+}
+
+// No corner turn: the azimuth pass reads strips of adjacent azimuth lines
+// straight from the range pass's output, which is kept in tiles of 32 columns
+// (TileMap in rda_kernels.inl).
+//   LFM:        raw -> range -> work (tiles) -> strips FFT*H*IFFT -> img [Nr][Na],
+//               or as rows of img [Na][Nr] with transpose_back
 //   hyperbolic: raw -> range -> img (tiles) -> strips FFT -> work [Nr][Na]
-//               -> RCMC*phase*IFFT -> img [Nr][Na]
-sar_status execute_turn_free(const sar_plan_s* P, const void* raw, void* img, void* work,
-                             hipStream_t s)
+//               -> RCMC*phase*IFFT -> img [Nr][Na]; with transpose_back work
+//               and img change places and a corner turn work -> img follows
+sar_status execute_strips(const sar_plan_s* P, const void* raw, void* img, void* work, hipStream_t s)
 {
     const int Nr = P->p.Nr, Na = P->p.Na;
+    const bool back = P->p.transpose_back != 0;
     if (P->p.az_model == SAR_AZ_LFM) {
         HIP_TRY(sar::launch_range_tiled(Nr, raw, work, Na, P->Hr, P->tw_r, s), "range launch (column tiles)");
-        HIP_TRY(sar::launch_line_strip(true, Na, work, img, Nr, P->Ha, P->tw_a, 1.f, P->var_strip, s),
+        HIP_TRY(sar::launch_line_strip(back ? sar::StripOp::FusedBack : sar::StripOp::Fused, Na, work, img, Nr,
+                                       P->Ha, P->tw_a, 1.f, P->var_strip, s),
                 "azimuth strip launch");
         return SAR_OK;
     }
-    HIP_TRY(sar::launch_range_tiled(Nr, raw, img, Na, P->Hr, P->tw_r, s), "range launch (column tiles)");
-    HIP_TRY(sar::launch_line_strip(false, Na, img, work, Nr, nullptr, P->tw_a, 1.f, P->var_strip,
+    void* a = back ? work : img;
+    void* b = back ? img : work;
+    HIP_TRY(sar::launch_range_tiled(Nr, raw, a, Na, P->Hr, P->tw_r, s), "range launch (column tiles)");
+    HIP_TRY(sar::launch_line_strip(sar::StripOp::Forward, Na, a, b, Nr, nullptr, P->tw_a, 1.f, P->var_strip,
                                    s),
             "azimuth strip FFT launch");
     const sar::RcmcHost rh = rcmc_host(P);
-    HIP_TRY(sar::launch_line(LineOp::RcmcAz, Na, work, img, Nr, nullptr, P->tw_a, 1.f, &rh, arith(P),
+    HIP_TRY(sar::launch_line(LineOp::RcmcAz, Na, b, a, Nr, nullptr, P->tw_a, 1.f, &rh, arith(P),
                              P->var_a[sar::TK_RCMC], s),
             "RCMC+azimuth launch");
-    return SAR_OK;
+    return back ? step_turn(a, img, Nr, Na, P->var_back, s) : SAR_OK;
 }
 
 // Half storage (fused schedule): the intermediates live in the workspace as
@@ -560,7 +586,7 @@ sar_status sar_rda_execute(sar_plan_t P, const void* raw, void* img, void* work,
         return fail(SAR_ERR_ALIAS, "raw, img and work must be pairwise disjoint");
     hipStream_t s = (hipStream_t)stream;
     if (P->p.precision == SAR_FP32_HALF_STORAGE) return execute_half(P, raw, img, work, s);
-    if (P->p.schedule == SAR_TURN_FREE) return execute_turn_free(P, raw, img, work, s);
+    if (runs_strips(P)) return execute_strips(P, raw, img, work, s);
     const int Nr = P->p.Nr, Na = P->p.Na;
     const bool back = P->p.transpose_back != 0;
     // Buffers alternate so that the last step writes img.

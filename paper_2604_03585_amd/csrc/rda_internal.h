@@ -75,11 +75,14 @@ int twiddle_table_size(int n);
 hipError_t launch_range_tiled(int n, const void* in, void* out, int na, const void* H, const void* tw,
                               hipStream_t s);
 
-// Column-strip azimuth pass (turn-free schedules, FP32, n <= 4096): the n-point
-// azimuth lines of range cells 0 .. cols-1, read from the column tiles `in` that
-// launch_range_tiled wrote, transformed (fused: IFFT(FFT * H); else FFT * scale)
-// and stored as lines out [cols][n].  cols must be a multiple of 32.
-hipError_t launch_line_strip(bool fused, int n, const void* in, void* out, int cols,
+// Column-strip azimuth pass (no corner turn; FP32, n <= 4096): the n-point azimuth
+// lines of range cells 0 .. cols-1, read from the column tiles `in` that
+// launch_range_tiled wrote (cols a multiple of 32):
+//  Fused:     out [cols][n] = IFFT(FFT * H) line after line
+//  Forward:   out [cols][n] = FFT * scale
+//  FusedBack: IFFT(FFT * H) as rows of out [n][cols]
+enum class StripOp { Fused, Forward, FusedBack };
+hipError_t launch_line_strip(StripOp op, int n, const void* in, void* out, int cols,
                              const void* H, const void* tw, float scale, int variant, hipStream_t s);
 
 // Batched launches (kind: 0 fused, 1 forward, 2 inverse; tasks in device memory).

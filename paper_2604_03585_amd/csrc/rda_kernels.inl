@@ -203,6 +203,12 @@ __device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, uint32_t voff, 
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2_t, v), r, voff, soff, 0);
 }
 
+__device__ __forceinline__ void buf_st4(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, float4 v)
+{
+    typedef unsigned int u4_t __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, v), r, voff, soff, 0);
+}
+
 // Points t + m*T of a line; `off` is the byte offset of point t from the
 // resource's base.
 template <int N>
@@ -389,7 +395,9 @@ __device__ __forceinline__ StripSrc strip_source(const float2* in, const TileMap
     return s;
 }
 
-template <int N, int KIND, int CW = 0>
+// BACK: the lines leave as they came, C samples of every row of out [N][cols]
+// (the back-turned image), regrouped through LDS once more.
+template <int N, int KIND, int CW = 0, bool BACK = false>
 __global__ __launch_bounds__((StripLaunch<N, CW>::BLOCK))
 __attribute__((amdgpu_waves_per_eu(N == 512 ? 7 : 8))) void      // 512 points spill at 64 registers
 k_line_strip(const float2* __restrict__ in, float2* __restrict__ out, int cols, TileMap tm,
@@ -450,7 +458,30 @@ k_line_strip(const float2* __restrict__ in, float2* __restrict__ out, int cols, 
             for (int m = 0; m < 16; ++m) x[m] = c_scale(x[m], scale);
         }
     }
-    store_line<N>(x, buf_rsrc(out + (size_t)n0 * N, C * N * 8u), (uint32_t)(sub * N + t) * 8u);
+    if constexpr (!BACK) {
+        store_line<N>(x, buf_rsrc(out + (size_t)n0 * N, C * N * 8u), (uint32_t)(sub * N + t) * 8u);
+    } else {
+#pragma unroll
+        for (int m = 0; m < 16; ++m) lds[half_in<T, 0>(t, m)] = x[m].x;
+        wg_barrier();
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            v[p].x = row0[half_in<2 * T, 0>(m0, p)];
+            v[p].z = row0[S::STRIDE + half_in<2 * T, 0>(m0, p)];
+        }
+        wg_barrier();
+#pragma unroll
+        for (int m = 0; m < 16; ++m) lds[half_in<T, 0>(t, m)] = x[m].y;
+        wg_barrier();
+        const __amdgpu_buffer_rsrc_t ob = buf_rsrc(out + n0, (uint32_t)(N * cols - n0) * 8u);
+        const uint32_t off = (uint32_t)(m0 * cols + 2 * q) * 8u;
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            v[p].y = row0[half_in<2 * T, 0>(m0, p)];
+            v[p].w = row0[S::STRIDE + half_in<2 * T, 0>(m0, p)];
+            buf_st4(ob, off, (uint32_t)(2 * T * p * cols) * 8u, v[p]);
+        }
+    }
 }
 
 template <int N, int KIND, int PREC, bool TWP, bool SPLIT = false, int X = 1>
@@ -1866,7 +1897,7 @@ hipError_t launch_range_tiled(int n, const void* in, void* out, int na, const vo
     }
 }
 
-template <int N, int KIND, int CW>
+template <int N, int KIND, int CW, bool BACK = false>
 static hipError_t launch_strip_k(const float2* in, float2* out, int cols, const float2* H,
                                  const float2* tw, float scale, hipStream_t s)
 {
@@ -1874,34 +1905,52 @@ static hipError_t launch_strip_k(const float2* in, float2* out, int cols, const 
     static const hipError_t attr =
         S::LDS_BYTES <= 64 * 1024
             ? hipSuccess
-            : hipFuncSetAttribute((const void*)k_line_strip<N, KIND, CW>,
+            : hipFuncSetAttribute((const void*)k_line_strip<N, KIND, CW, BACK>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, S::LDS_BYTES);
     if (attr != hipSuccess) return attr;
     // whole strips and tiles; 16-byte pair loads need an aligned base
     if (cols % TILE_COLS != 0 || ((uintptr_t)in & 15u)) return hipErrorInvalidValue;
     if (cols == 0) return hipSuccess;
-    SAR_LAUNCH((k_line_strip<N, KIND, CW>), dim3(cols / S::C), dim3(S::BLOCK), S::LDS_BYTES,
+    SAR_LAUNCH((k_line_strip<N, KIND, CW, BACK>), dim3(cols / S::C), dim3(S::BLOCK), S::LDS_BYTES,
                s, in, out, cols, tile_map(N), H, tw, scale);
     return hipGetLastError();
 }
 
-// Twiddles by products only.  Variant 1: strips of half the default width (C / 2
-// lines: half the LDS and threads per workgroup, runs of C / 2 samples).
+template <int N, int CW>
+static hipError_t launch_strip_c(StripOp op, const float2* in, float2* out, int cols, const float2* H,
+                                 const float2* tw, float scale, hipStream_t s)
+{
+    switch (op) {
+    case StripOp::Fused: return launch_strip_k<N, LK_FUSED, CW>(in, out, cols, H, tw, 1.f, s);
+    case StripOp::FusedBack: return launch_strip_k<N, LK_FUSED, CW, true>(in, out, cols, H, tw, 1.f, s);
+    case StripOp::Forward: return launch_strip_k<N, LK_FWD, CW>(in, out, cols, nullptr, tw, scale, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+// Twiddles by products only.  The strip width is the default one where that
+// makes a workgroup per CU, else half of it, else the narrowest of whole waves
+// (two lines from 512 points): with few range cells the chip would stand idle
+// (2048 x 256 scene: 24.0 us with 32 strips of 8, 17.4 with 128 of 2).  Variant
+// 1: half the default width always.
 template <int N>
-static hipError_t launch_strip_n(bool fused, const float2* in, float2* out, int cols,
+static hipError_t launch_strip_n(StripOp op, const float2* in, float2* out, int cols,
                                  const float2* H, const float2* tw, float scale, int variant,
                                  hipStream_t s)
 {
-    constexpr int HALF = StripLaunch<N>::C_DEFAULT / 2;
-    if (variant == 1) {
-        if (fused) return launch_strip_k<N, LK_FUSED, HALF>(in, out, cols, H, tw, 1.f, s);
-        return launch_strip_k<N, LK_FWD, HALF>(in, out, cols, nullptr, tw, scale, s);
+    constexpr int C = StripLaunch<N>::C_DEFAULT, HALF = C / 2;
+    constexpr int LEAST = 64 / StripLaunch<N>::T > 2 ? 64 / StripLaunch<N>::T : 2;
+    if (variant == 1) return launch_strip_c<N, HALF>(op, in, out, cols, H, tw, scale, s);
+    if constexpr (LEAST < HALF) {
+        if (cols / HALF < 256) return launch_strip_c<N, LEAST>(op, in, out, cols, H, tw, scale, s);
     }
-    if (fused) return launch_strip_k<N, LK_FUSED, 0>(in, out, cols, H, tw, 1.f, s);
-    return launch_strip_k<N, LK_FWD, 0>(in, out, cols, nullptr, tw, scale, s);
+    if constexpr (LEAST <= HALF) {
+        if (cols / C < 256) return launch_strip_c<N, HALF>(op, in, out, cols, H, tw, scale, s);
+    }
+    return launch_strip_c<N, C>(op, in, out, cols, H, tw, scale, s);
 }
 
-hipError_t launch_line_strip(bool fused, int n, const void* in, void* out, int cols,
+hipError_t launch_line_strip(StripOp op, int n, const void* in, void* out, int cols,
                              const void* H, const void* tw, float scale, int variant, hipStream_t s)
 {
     auto i = (const float2*)in;
@@ -1909,13 +1958,13 @@ hipError_t launch_line_strip(bool fused, int n, const void* in, void* out, int c
     auto h = (const float2*)H;
     auto w = (const float2*)tw;
     switch (n) {
-    case 64: return launch_strip_n<64>(fused, i, o, cols, h, w, scale, variant, s);
-    case 128: return launch_strip_n<128>(fused, i, o, cols, h, w, scale, variant, s);
-    case 256: return launch_strip_n<256>(fused, i, o, cols, h, w, scale, variant, s);
-    case 512: return launch_strip_n<512>(fused, i, o, cols, h, w, scale, variant, s);
-    case 1024: return launch_strip_n<1024>(fused, i, o, cols, h, w, scale, variant, s);
-    case 2048: return launch_strip_n<2048>(fused, i, o, cols, h, w, scale, variant, s);
-    case 4096: return launch_strip_n<4096>(fused, i, o, cols, h, w, scale, variant, s);
+    case 64: return launch_strip_n<64>(op, i, o, cols, h, w, scale, variant, s);
+    case 128: return launch_strip_n<128>(op, i, o, cols, h, w, scale, variant, s);
+    case 256: return launch_strip_n<256>(op, i, o, cols, h, w, scale, variant, s);
+    case 512: return launch_strip_n<512>(op, i, o, cols, h, w, scale, variant, s);
+    case 1024: return launch_strip_n<1024>(op, i, o, cols, h, w, scale, variant, s);
+    case 2048: return launch_strip_n<2048>(op, i, o, cols, h, w, scale, variant, s);
+    case 4096: return launch_strip_n<4096>(op, i, o, cols, h, w, scale, variant, s);
     default: return hipErrorInvalidValue;
     }
 }

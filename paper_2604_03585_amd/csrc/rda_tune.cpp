@@ -466,7 +466,7 @@ sar_status sar_autotune(const sar_params* p, const char* cache_path)
         st = time_candidates(
             cs,
             [&](int v) {
-                return sar::launch_line_strip(!hyper, Na, in, out, Nr, hyper ? nullptr : tb.Ha,
+                return sar::launch_line_strip(hyper ? sar::StripOp::Forward : sar::StripOp::Fused, Na, in, out, Nr, hyper ? nullptr : tb.Ha,
                                               tb.tw_a, 1.f, v, s);
             },
             s);

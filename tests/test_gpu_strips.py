@@ -13,7 +13,7 @@ from sarsim import config
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(64, 64), (64, 128), (64, 4096), (128, 64), (128, 256), (256, 512), (256, 8192), (512, 64),
-          (512, 1024), (1024, 64), (1024, 256), (1024, 2048), (2048, 128), (2048, 4096), (4096, 64),
+          (512, 1024), (512, 2048), (512, 4096), (1024, 64), (1024, 256), (1024, 2048), (2048, 128), (2048, 4096), (4096, 64),
           (4096, 512), (8192, 64), (8192, 1024), (8192, 2048), (16384, 64), (16384, 128), (16384, 512)]
 
 
@@ -49,4 +49,18 @@ def test_turn_free_equals_steps(nr, na, model):
     want = by_steps(cfg, raw)
     with sar.Plan(cfg, schedule="turn_free") as p:
         got = host(p.execute(raw))
+    assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
+
+
+@pytest.mark.parametrize("nr, na", SHAPES)
+@pytest.mark.parametrize("model", ["lfm", "hyperbolic"])
+@pytest.mark.parametrize("back", [0, 1])
+def test_fused_equals_steps(nr, na, model, back):
+    """The fused schedule drops its corner turn(s) where the strips cover the
+    plan (azimuth lines of up to 4096), with and without the back-turn."""
+    cfg, raw = scene(nr, na, model)
+    want = by_steps(cfg, raw)
+    with sar.Plan(cfg, transpose_back=back) as p:
+        got = host(p.execute(raw))
+    want = np.ascontiguousarray(want.T) if back else want
     assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
