@@ -203,6 +203,12 @@ __device__ __forceinline__ void buf_st(__amdgpu_buffer_rsrc_t r, uint32_t voff, 
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2_t, v), r, voff, soff, 0);
 }
 
+// Non-temporal store: for results that no later kernel reads.
+__device__ __forceinline__ void buf_st_nt(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, float2 v)
+{
+    typedef unsigned int u2_t __attribute__((ext_vector_type(2)));
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2_t, v), r, voff, soff, 2);
+}
 __device__ __forceinline__ void buf_st4(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff, float4 v)
 {
     typedef unsigned int u4_t __attribute__((ext_vector_type(4)));
@@ -225,6 +231,32 @@ __device__ __forceinline__ void store_line(const float2 (&x)[line_e(N)], __amdgp
 {
 #pragma unroll
     for (int m = 0; m < line_e(N); ++m) buf_st(dst, off, m * LineGeom<N>::T * 8u, x[m]);
+}
+
+// The RCMC pass's stores of its image lines pass by the caches (non-temporal):
+// the rows that are still gathered then stay in an XCD's L2 (8192 points: 212 ->
+// 188 us per 32 Mpx, 2048 x 4096 hyperbolic scene 95.8 -> 91.1), and the image is
+// not read again.  CACHED: the exception, see rcmc_image_cached.
+template <int N, bool CACHED = false>
+__device__ __forceinline__ void store_image_line(const float2 (&x)[line_e(N)], __amdgpu_buffer_rsrc_t dst,
+                                                 uint32_t off)
+{
+#pragma unroll
+    for (int m = 0; m < line_e(N); ++m) {
+        if constexpr (CACHED) buf_st(dst, off, m * LineGeom<N>::T * 8u, x[m]);
+        else buf_st_nt(dst, off, m * LineGeom<N>::T * 8u, x[m]);
+    }
+}
+
+// 4096-point lines over FP32 arrays of 64 to 256 MiB: the range output and the
+// range-Doppler data then fill the 256 MiB last-level cache between them, and
+// with the image written past it the next scene's strip FFT took 70 us in place
+// of 52 (4096^2: 195 against 183 us; 4096 x 2048 89 against 92, 4096 x 8192 equal,
+// half storage 170 against 176).
+template <int N> __device__ __forceinline__ constexpr bool rcmc_image_may_be_cached() { return N == 4096; }
+__device__ __forceinline__ bool rcmc_image_cached(uint32_t bytes)
+{
+    return bytes > (64u << 20) && bytes < (256u << 20);
 }
 
 // Column tiles: the range output between the two passes of the turn-free
@@ -885,18 +917,18 @@ struct RcmcArgs {
 
 // The per-bin geometry from the bin index: f_k in fftfreq order,
 // x = lambda f / (2 v), D = sqrt(1 - x^2), stretch = 1/D - 1, rate = 2 D / lambda.
-// r = 1/D comes from the hardware reciprocal square root refined by two
-// Newton steps in FP64 (quadratic convergence: full double precision), so
-// stretch = r - 1 has an absolute error near 1e-16; the RCMC shift
-// R0 * stretch needs it to 1e-12.  The plan's tables use the same function.
+// r = 1/D comes from the hardware reciprocal square root r0 (about 2^-24) refined
+// in FP64 by r = r0 (1 + e/2 + 3 e^2 / 8), e = 1 - D^2 r0^2, whose error is of
+// third order (full double precision), so stretch = r - 1 has an absolute error
+// near 1e-16; the RCMC shift R0 * stretch needs it to 1e-12.  The plan's tables
+// use the same function.
 __device__ __forceinline__ void bin_geometry_x(double x, double two_over_lam, double& stretch,
                                                double& rate)
 {
     const double a = fma(-x, x, 1.0);               // D^2
-    double r = __builtin_amdgcn_rsq(a);
-    const double ha = 0.5 * a;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) r = r * fma(-ha * r, r, 1.5);
+    const double r0 = __builtin_amdgcn_rsq(a);
+    const double e = fma(-a * r0, r0, 1.0);
+    const double r = fma(r0 * e, fma(e, 0.375, 0.5), r0);
     stretch = r - 1.0;
     rate = (a * r) * two_over_lam;                  // D = a / sqrt(a)
 }
@@ -924,23 +956,30 @@ __global__ void k_gen_hyper_tables(double* __restrict__ stretch, double* __restr
 
 // Global table (24 floats per interval) -> LDS (RCMC_LDS_STRIDE floats per
 // interval); lds_tab holds RCMC_LDS_FLOATS floats.
+template <int STRIDE = RCMC_LDS_STRIDE>
 __device__ __forceinline__ void load_rcmc_table(float* __restrict__ lds_tab,
-                                                const float* __restrict__ tab, int tid, int nthreads)
+                                                const float* __restrict__ tab, int tid, int nthreads,
+                                                float scale = 1.0f)
 {
-    static_assert(RCMC_PER_INTERVAL == 24 && RCMC_LDS_STRIDE % 4 == 0, "16-byte copies");
-    constexpr int V = RCMC_PER_INTERVAL / 4, VS = RCMC_LDS_STRIDE / 4;
+    static_assert(RCMC_PER_INTERVAL == 24 && STRIDE % 4 == 0, "16-byte copies");
+    constexpr int V = RCMC_PER_INTERVAL / 4, VS = STRIDE / 4;
     for (int i = tid; i < RCMC_TAB / 4; i += nthreads)
-        ((float4*)lds_tab)[(i / V) * VS + i % V] = ((const float4*)tab)[i];
+    {
+        const float4 v = ((const float4*)tab)[i];
+        ((float4*)lds_tab)[(i / V) * VS + i % V] =
+            make_float4(v.x * scale, v.y * scale, v.z * scale, v.w * scale);
+    }
 }
 
 // sum_t w_t(x) a_t with the weights from the LDS table.
+template <int STRIDE = RCMC_LDS_STRIDE>
 __device__ __forceinline__ float2 rcmc_combine(float x, const float* __restrict__ tab,
                                                const float2 (&a)[8])
 {
     const float xf = x * (float)RCMC_INTERVALS;
     const int b = min((int)xf, RCMC_INTERVALS - 1);
     const float u = xf - (float)b;
-    const float4* p = (const float4*)(tab + b * RCMC_LDS_STRIDE);
+    const float4* p = (const float4*)(tab + __mul24(b, STRIDE));
     float2 acc = make_float2(0.f, 0.f);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {                 // taps 4h .. 4h+3: three vectors
@@ -1013,14 +1052,17 @@ __device__ __forceinline__ float2 rcmc_value(const float2* __restrict__ A, int n
     }
 }
 
-// exp(+j 2 pi frac(R0 * rate)) * scale: the phase in turns is reduced in
-// FP64, then the hardware sine/cosine (argument in turns, max abs error
-// 1.3e-7 on [-1/2, 1/2], measured on gfx950) evaluate it.
+// exp(+j 2 pi ph) * scale: the phase in turns is reduced to [-1/2, 1/2] in FP64,
+// then the hardware sine/cosine (argument in turns, max abs error 1.3e-7 there,
+// measured on gfx950) evaluate it.
+__device__ __forceinline__ float2 turns_to_phasor(double ph)
+{
+    const float f = (float)(ph - rint(ph));
+    return make_float2(__builtin_amdgcn_cosf(f), __builtin_amdgcn_sinf(f));
+}
 __device__ __forceinline__ float2 turns_to_phasor(double ph, float scale)
 {
-    float f = (float)(ph - floor(ph));
-    if (f > 0.5f) f -= 1.0f;
-    return make_float2(__builtin_amdgcn_cosf(f) * scale, __builtin_amdgcn_sinf(f) * scale);
+    return c_scale(turns_to_phasor(ph), scale);
 }
 
 __device__ __forceinline__ float2 az_phase_of(double R0, double rate, float scale)
@@ -1314,9 +1356,210 @@ k_rcmc_az2(const void* __restrict__ A_, float2* __restrict__ out, RcmcArgs ra,
     const uint32_t bytes = (uint32_t)(min(L::LPW, pairs - g * L::LPW) * 2 * N) * 8u;
     const __amdgpu_buffer_rsrc_t ob = buf_rsrc(out + (size_t)(2 * g * L::LPW) * N, bytes);
     const uint32_t off = (uint32_t)(2 * sub * N + t) * 8u;
-    store_line<N>(xa, ob, off);
+    store_image_line<N, N == 4096>(xa, ob, off);
     fft_any<N, true, PREC, true, false, NoOp, true>(xb, lds, tw, sub, t);
-    store_line<N>(xb, ob, off + N * 8u);
+    store_image_line<N, N == 4096>(xb, ob, off + N * 8u);
+}
+
+// Four output rows n .. n + 3 per group of threads (FP32 butterflies), for
+// geometries whose shift changes little from row to row (stretch up to
+// RCMC_ROWS_STRETCH_MAX).  Up to 2048 points the group has 4T threads (T = N/16):
+// a thread interpolates four columns of the four rows, the rows meet in LDS and
+// their IFFTs run side by side.  At 4096 and 8192 points it has 2T threads and
+// works in two rounds: the first two rows' samples go to LDS as they are formed,
+// the others wait in registers.  The FP64 geometry, the gathers and the table
+// reads are shared by four samples:
+//   * twelve rows i0 - 3 .. i0 + 8 cover the four windows;
+//   * the shifts s + j stretch, j < 4, lie within 0.2 table intervals, so one
+//     interval (that of their middle) serves all rows, its quadratics being
+//     evaluated at u in [-0.1, 1.1] (fit error 2.2e-8 there at most x 2.8, the
+//     size of the FP32 rounding of the weights);
+//   * where a shift crosses a cell boundary between the rows (a wave vote; one
+//     wave in ten) the rows take their own windows and intervals.
+// Rows beyond the scene read as zero by the buffer's bounds; only the first
+// rows of the scene have rows before it, and take the EDGE form, where every
+// row's offset is formed by itself (a negative one is beyond the bounds too).
+//
+// Bound by VALU issue, at 8192 points by L2 (the rows in flight of an XCD no
+// longer fit it).  Against two rows per thread with two buffers of gathers
+// (k_rcmc_az2: 157 registers, three waves per SIMD; twice the FP64 work and four
+// times the table reads per sample), alone, from HBM: 4096^2 101 -> 74 us, 8192
+// x 4096 212 -> 162, 2048 x 1024 20.6 -> 11.8, 1024 x 4096 25 -> 17, 256 x 4096
+// 23 -> 7.8.  (At 4096 points one workgroup of 1024 threads per CU took 79.)
+constexpr double RCMC_ROWS_STRETCH_MAX = 5e-4;   // 3 x 5e-4 x 128 = 0.19 intervals
+
+template <int N> struct RcmcRows {
+    static constexpr int T = LineGeom<N>::T;
+    static_assert(N <= 8192, "two lines and the table fit LDS");
+    static constexpr int SIDE = N <= 2048 ? 4 : 2;               // rows whose IFFTs run side by side
+    static constexpr int ROUNDS = 4 / SIDE;
+    static constexpr int R = 4;                                  // rows per group
+    static constexpr int S = SIDE * T;                           // threads per group
+    static constexpr int C = N / S;                              // columns per thread
+    static constexpr int G = S >= 256 ? 1 : 256 / S;             // groups per workgroup
+    static constexpr int BLOCK = S * G;
+    static constexpr int LINES = SIDE * G * LineGeom<N>::LDS * (int)sizeof(float2);
+    // intervals as in the plan (24 floats apart): at 4096 points two workgroups
+    // then take a CU's 160 KiB to the byte
+    static constexpr int STRIDE = RCMC_PER_INTERVAL;
+    static constexpr int TABLE = RCMC_INTERVALS * STRIDE * (int)sizeof(float);
+    // one round: the table shares LDS with the lines, which are written after
+    // its last read; two: the first round's rows go to LDS as they are formed
+    static constexpr int LDS_BYTES = ROUNDS == 2 ? LINES + TABLE : (LINES > TABLE ? LINES : TABLE);
+    static_assert(LDS_BYTES <= 160 * 1024 && (ROUNDS == 1 || G == 1), "one workgroup per CU at least");
+};
+
+// HIN: FP16 rows, row r scaled by 2^-exponent[r].
+template <bool HIN> struct RcmcSrc {
+    __amdgpu_buffer_rsrc_t rows, exponents;
+};
+
+template <int N, int ROWS, bool EDGE, bool HIN>
+__device__ __forceinline__ void rcmc_gather_rows(float2 (&w)[ROWS], const RcmcSrc<HIN>& A, int first, int k)
+{
+    constexpr uint32_t B = HIN ? 4u : 8u, ROW = N * B;
+    const uint32_t off = (uint32_t)(first * N + k) * B;
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+        const uint32_t vo = EDGE ? off + i * ROW : off, so = EDGE ? 0 : i * ROW;
+        if constexpr (HIN) {
+            const h2_t v = __builtin_bit_cast(h2_t, __builtin_amdgcn_raw_buffer_load_b32(A.rows, vo, so, 0));
+            const int e = (int)__builtin_amdgcn_raw_buffer_load_b32(
+                A.exponents, EDGE ? (uint32_t)(first + i) * 4u : (uint32_t)first * 4u, EDGE ? 0 : i * 4u, 0);
+            w[i] = h2_to_f2(v, ldexpf(1.0f, e));
+        } else {
+            w[i] = buf_ld(A.rows, vo, so);
+        }
+    }
+}
+
+// The samples of columns u + m * S: the last SIDE rows' in y, the first round's
+// (of two) in the line buffers `lines`.
+template <int N, bool EDGE, bool HIN>
+__device__ __forceinline__ void rcmc_rows_columns(float2 (&y)[RcmcRows<N>::SIDE][RcmcRows<N>::C],
+                                                  const RcmcSrc<HIN>& A, const RcmcArgs& ra, int n, int u,
+                                                  const float* tab, float2* lines)
+{
+    using L = RcmcRows<N>;
+    constexpr int R = L::R, ROWS = R + 8;
+    const double R0 = ra.r_near + (double)n;
+#pragma unroll
+    for (int m = 0; m < L::C; ++m) {
+        const int k = fresh(u) + m * L::S;
+        double stretch, rate;
+        bin_geometry(ra, k, N, stretch, rate);
+        const double s = R0 * stretch, f = floor(s), ph = R0 * rate;
+        float x[R];                               // fractions against row n's cell
+#pragma unroll
+        for (int j = 0; j < R; ++j) x[j] = (float)(fma((double)j, stretch, s) - f);
+        // cells past the scene's end read nothing wherever they are
+        const int i0 = n + (int)fmin(f, 32768.0);
+        float2 w[ROWS];
+        rcmc_gather_rows<N, ROWS, EDGE, HIN>(w, A, i0 - 3, k);
+        __builtin_amdgcn_sched_barrier(0);
+        if (m == 0) __syncthreads();              // the table is in LDS
+        float2 acc[R];
+        if (__builtin_amdgcn_ballot_w64(x[R - 1] >= 1.0f) == 0) {
+            // one interval for all rows
+            const int b = min((int)(0.5f * (x[0] + x[R - 1]) * (float)RCMC_INTERVALS), RCMC_INTERVALS - 1);
+            const float fb = (float)b;
+            float v[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                v[j] = fmaf(x[j], (float)RCMC_INTERVALS, -fb);
+                acc[j] = make_float2(0.f, 0.f);
+            }
+            const float4* q = (const float4*)(tab + __mul24(b, L::STRIDE));
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {         // taps 4h .. 4h+3: three vectors
+                float cf[12];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const float4 g = q[3 * h + i];
+                    cf[4 * i] = g.x;
+                    cf[4 * i + 1] = g.y;
+                    cf[4 * i + 2] = g.z;
+                    cf[4 * i + 3] = g.w;
+                }
+#pragma unroll
+                for (int j = 0; j < R; ++j)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const float wt = fmaf(fmaf(cf[3 * i + 2], v[j], cf[3 * i + 1]), v[j], cf[3 * i]);
+                        const float2 a = w[4 * h + i + j];
+                        acc[j].x = fmaf(wt, a.x, acc[j].x);
+                        acc[j].y = fmaf(wt, a.y, acc[j].y);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                const bool d = j > 0 && x[j] >= 1.0f;            // the window starts one row later
+                float2 a[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) a[i] = d ? w[i + j + 1 < ROWS ? i + j + 1 : 0] : w[i + j];
+                acc[j] = rcmc_combine<L::STRIDE>(d ? x[j] - 1.0f : x[j], tab, a);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+            const float2 v = c_mul(acc[j], turns_to_phasor(fma((double)j, rate, ph)));
+            if (j < R - L::SIDE) lines[j * LineGeom<N>::LDS + lds_in<L::S, 0>(u, m)] = v;
+            else y[j - (R - L::SIDE)][m] = v;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// HIN: A holds FP16 rows with per-row exponents ra.row_exp (half storage).
+template <int N, bool HIN = false>
+__global__ __launch_bounds__(RcmcRows<N>::BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
+k_rcmc_rows(const void* __restrict__ A, float2* __restrict__ out, RcmcArgs ra,
+            const float2* __restrict__ tw)
+{
+    using L = RcmcRows<N>;
+    constexpr int T = L::T, S = L::S, R = L::R, SIDE = L::SIDE, LL = LineGeom<N>::LDS;
+    extern __shared__ __align__(16) float2 smem[];
+    float* tab = (float*)smem;
+    float2* lines = smem + (L::ROUNDS == 2 ? L::TABLE / (int)sizeof(float2) : 0);
+    const int g = xcd_group(blockIdx.x, ra.nr / (R * L::G));
+    const int gi = threadIdx.x / S, u = threadIdx.x % S;
+    const int n0 = g * L::G * R, n = n0 + gi * R;                // n0 uniform
+    const uint32_t bytes = (uint32_t)ra.nr * N * 8u;
+    RcmcSrc<HIN> ab;
+    ab.rows = buf_rsrc(A, HIN ? bytes / 2 : bytes);
+    if constexpr (HIN) ab.exponents = buf_rsrc(ra.row_exp, (uint32_t)ra.nr * 4u);
+    // the weights carry the IFFT's 1/N (a power of two: exact)
+    load_rcmc_table<L::STRIDE>(tab, ra.table, threadIdx.x, L::BLOCK, 1.0f / (float)N);
+    float2 y[SIDE][L::C];
+    if (n0 >= 4) rcmc_rows_columns<N, false, HIN>(y, ab, ra, n, u, tab, lines);
+    else rcmc_rows_columns<N, true, HIN>(y, ab, ra, n, u, tab, lines);
+    const __amdgpu_buffer_rsrc_t ob = buf_rsrc(out, bytes);
+    const int line = threadIdx.x / T, t = threadIdx.x % T;       // row n0 + line (of a round)
+    float2* lds = lines + line * LL;
+#pragma unroll
+    for (int r = 0; r < L::ROUNDS; ++r) {
+        wg_barrier();                             // table reads, or the first round's writes, done
+        if (r == L::ROUNDS - 1) {
+#pragma unroll
+            for (int j = 0; j < SIDE; ++j)
+#pragma unroll
+                for (int m = 0; m < L::C; ++m) lines[(gi * SIDE + j) * LL + lds_in<S, 0>(u, m)] = y[j][m];
+            wg_barrier();
+        }
+        float2 x[16];
+#pragma unroll
+        for (int m = 0; m < 16; ++m) x[m] = lds[lds_in<T, 0>(t, m)];
+        wg_barrier();
+        fft_line<N, true>(x, lds, tw, fresh(t));
+        const uint32_t off = (uint32_t)((n0 + r * SIDE + line) * N + t) * 8u;
+        if (!HIN && rcmc_image_may_be_cached<N>() && rcmc_image_cached(bytes))
+            store_image_line<N, true>(x, ob, off);
+        else
+            store_image_line<N>(x, ob, off);
+    }
 }
 
 // The same two rows per workgroup on 2T threads (FP32, T = N/16 <= 512):
@@ -1680,6 +1923,17 @@ static hipError_t launch_k_line(const float2* in, float2* out, int lines, const 
     return hipGetLastError();
 }
 
+// k_rcmc_rows takes whole groups of rows and a shift that changes little per row.
+template <int N> static bool rcmc_rows_fit(const RcmcArgs& ra)
+{
+    return ra.stretch_max <= RCMC_ROWS_STRETCH_MAX && ra.nr % (RcmcRows<N>::R * RcmcRows<N>::G) == 0;
+}
+template <int N, bool HIN> static hipError_t allow_rcmc_rows_lds()
+{
+    return hipFuncSetAttribute((const void*)k_rcmc_rows<N, HIN>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               RcmcRows<N>::LDS_BYTES);
+}
+
 template <int N, int PREC>
 static hipError_t launch_line_n(LineOp op, const float2* in, float2* out, int lines,
                                 const float2* H, const float2* tw, float scale,
@@ -1714,6 +1968,19 @@ static hipError_t launch_line_n(LineOp op, const float2* in, float2* out, int li
                 if (wa != hipSuccess) return wa;
                 SAR_LAUNCH((k_rcmc_az2w<N>), dim3(lines / 2), dim3(2 * LineGeom<N>::T), lds2,
                                    s, in, out, *ra, tw);
+                return hipGetLastError();
+            }
+        }
+        // four rows at a time where the geometry allows; at 16384 points one line
+        // takes a CU's LDS and the two-row kernel was faster (208 us against 218
+        // per 32 Mpx for two rows in two rounds)
+        if constexpr (PREC == PREC_FP32 && N <= 8192) {
+            if (two_rows && !(variant & 4) && rcmc_rows_fit<N>(*ra)) {
+                static const hipError_t ga = allow_rcmc_rows_lds<N, false>();
+                if (ga != hipSuccess) return ga;
+                using Q = RcmcRows<N>;
+                SAR_LAUNCH((k_rcmc_rows<N, false>), dim3(lines / (Q::R * Q::G)), dim3(Q::BLOCK),
+                           Q::LDS_BYTES, s, in, out, *ra, tw);
                 return hipGetLastError();
             }
         }
@@ -2041,6 +2308,16 @@ static hipError_t launch_rcmc_half_n(const void* A, const int* ex, void* out, co
     if (attr != hipSuccess) return attr;
     RcmcArgs ra = ra0;
     ra.row_exp = ex;
+    if constexpr (N <= 8192) {
+        if (rcmc_rows_fit<N>(ra)) {
+            static const hipError_t ga = allow_rcmc_rows_lds<N, true>();
+            if (ga != hipSuccess) return ga;
+            using Q = RcmcRows<N>;
+            SAR_LAUNCH((k_rcmc_rows<N, true>), dim3(ra.nr / (Q::R * Q::G)), dim3(Q::BLOCK), Q::LDS_BYTES, s,
+                       A, (float2*)out, ra, (const float2*)tw);
+            return hipGetLastError();
+        }
+    }
     const int g2 = (ra.nr / 2 + L::LPW - 1) / L::LPW;
     if (g2 == 0) return hipSuccess;
     SAR_LAUNCH((k_rcmc_az2<N, PREC_FP32, true>), dim3(g2), dim3(L::BLOCK), L::LDS_BYTES, s,
