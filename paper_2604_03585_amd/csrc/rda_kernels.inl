@@ -648,36 +648,11 @@ __global__ __launch_bounds__(256) void k_rowmul(const float4* in, float4* out, l
 }
 
 // ===================================================== corner turn
-// 64 x 64 complex64 tiles through LDS (one pad column against bank
-// conflicts); reads and writes are 512-byte contiguous row segments.
 constexpr int TT = 64;
-__global__ __launch_bounds__(256) void k_corner_turn(const float2* __restrict__ in,
-                                                     float2* __restrict__ out, int rows, int cols)
-{
-    __shared__ float2 tile[TT][TT + 1];
-    const int tiles_c = (cols + TT - 1) / TT;
-    const int tr = blockIdx.x / tiles_c, tc = blockIdx.x % tiles_c;
-    const int r0 = tr * TT, c0 = tc * TT;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-#pragma unroll
-    for (int i = 0; i < TT / 4; ++i) {
-        const int r = ty + 4 * i;
-        if (r0 + r < rows && c0 + tx < cols)
-            tile[r][tx] = in[(size_t)(r0 + r) * cols + c0 + tx];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < TT / 4; ++i) {
-        const int c = ty + 4 * i;
-        if (c0 + c < cols && r0 + tx < rows)
-            out[(size_t)(c0 + c) * rows + r0 + tx] = tile[tx][c];
-    }
-}
 
 // Batched corner turn: the 64 x 64 tiles of many matrices in one launch.
 // Whole 64 x 64 tiles only (rows and cols multiples of 64): every global
-// access moves 16 bytes (two complex samples), half the instructions of
-// k_corner_turn.
+// access moves 16 bytes (two complex samples).
 // LDS map: element (r, c) of the tile sits at column c ^ ((r >> 1) & 31) of
 // row r (no pad).  A bank holds 4 bytes and 64 banks span 32 samples, so a
 // sample's banks depend on its column mod 32.  The read phase has lane tx
@@ -740,6 +715,66 @@ __global__ __launch_bounds__(256) void k_corner_turn_x2(const float4* __restrict
         turn_tile_to_lds(tile, v, tx, ty);
         wg_barrier();
         gt = next;
+    }
+}
+
+// Any rows and cols (odd ones start rows on 8-byte boundaries): TR x 64 tiles,
+// one workgroup of 4 TR threads each, two samples per access (16 bytes at 8-byte alignment,
+// which global memory instructions take) and turn_swz's conflict-free LDS
+// map; only tiles on the ragged edges test every sample.
+// What bounds it: HBM (3000 x 5001, 240 MB moved: 49 us at the rate of a large
+// copy).  One sample per access in a padded tile took 63.7 us there, this form
+// 51.1; persistent workgroups that load ahead took 54.4 to 56.2 (eight
+// accesses per thread and five workgroups per CU already cover the latency).
+// TR = 128 writes runs of 1 KiB: where the output's rows do not start on
+// 64-byte boundaries each run ends inside a line at both sides, and half as
+// many runs leave half as many torn lines.
+typedef float turn_f4 __attribute__((ext_vector_type(4), aligned(8)));
+template <int TR>
+__global__ __launch_bounds__(4 * TR) void k_corner_turn(const float2* __restrict__ in,
+                                                        float2* __restrict__ out, int rows, int cols)
+{
+    __shared__ float2 tile[TR][TT];
+    constexpr int OP = TR / 2;                    // threads per output run
+    const int tiles_c = (cols + TT - 1) / TT;
+    const int r0 = (int)(blockIdx.x / tiles_c) * TR, c0 = (int)(blockIdx.x % tiles_c) * TT;
+    const bool inside = r0 + TR <= rows && c0 + TT <= cols;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    turn_f4 v[8];
+    if (inside) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            v[i] = *(const turn_f4*)(in + (size_t)(r0 + ty + TR / 8 * i) * cols + c0 + 2 * tx);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int r = r0 + ty + TR / 8 * i, c = c0 + 2 * tx;
+            const float2* p = in + (size_t)r * cols + c;
+            float2 a = make_float2(0.f, 0.f), b = a;
+            if (r < rows && c < cols) a = p[0];
+            if (r < rows && c + 1 < cols) b = p[1];
+            v[i] = turn_f4{a.x, a.y, b.x, b.y};
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int r = ty + TR / 8 * i;
+        tile[r][turn_swz(r, 2 * tx)] = make_float2(v[i].x, v[i].y);
+        tile[r][turn_swz(r, 2 * tx + 1)] = make_float2(v[i].z, v[i].w);
+    }
+    __syncthreads();
+    const int ox = threadIdx.x & (OP - 1), oy = threadIdx.x / OP;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int c = oy + 8 * i;
+        const float2 a = tile[2 * ox][turn_swz(2 * ox, c)], b = tile[2 * ox + 1][turn_swz(2 * ox + 1, c)];
+        float2* p = out + (size_t)(c0 + c) * rows + r0 + 2 * ox;
+        if (inside)
+            *(turn_f4*)p = turn_f4{a.x, a.y, b.x, b.y};
+        else if (c0 + c < cols) {
+            if (r0 + 2 * ox < rows) p[0] = a;
+            if (r0 + 2 * ox + 1 < rows) p[1] = b;
+        }
     }
 }
 
@@ -2466,9 +2501,17 @@ hipError_t launch_corner_turn(const void* in, void* out, int rows, int cols, int
         SAR_LAUNCH(k_corner_turn_x2, dim3((unsigned)grid), dim3(256), 0, s,
                            (const float4*)in, (float4*)out, rows, cols, (int)tiles);
     }
-    else
-        SAR_LAUNCH(k_corner_turn, dim3((unsigned)tiles), dim3(256), 0, s,
-                           (const float2*)in, (float2*)out, rows, cols);
+    // output rows that start on 64-byte boundaries: 64-row tiles (3000 x 5001:
+    // 51.1 us against 52.5 with 128 rows, 1000 x 777: 4.3 against 5.0); others:
+    // 128-row tiles (5001 x 3000: 57.5 against 62.0, 4097 x 4097: 60 against 64)
+    else if (rows % 8 == 0 && ((uintptr_t)out & 63u) == 0)
+        SAR_LAUNCH(k_corner_turn<64>, dim3((unsigned)tiles), dim3(256), 0, s, (const float2*)in,
+                           (float2*)out, rows, cols);
+    else {
+        const long long tall = (long long)((rows + 127) / 128) * ((cols + TT - 1) / TT);
+        SAR_LAUNCH(k_corner_turn<128>, dim3((unsigned)tall), dim3(512), 0, s, (const float2*)in,
+                           (float2*)out, rows, cols);
+    }
     return hipGetLastError();
 }
 
