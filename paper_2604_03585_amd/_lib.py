@@ -133,8 +133,8 @@ def header_functions() -> list[str]:
 
 # ------------------------------------------------------------ marshalling
 def _ptr(x) -> int | None:
-    if x is None:
-        return None
+    if x is None or type(x) is int:
+        return x
     if hasattr(x, "data_ptr"):
         return int(x.data_ptr())
     return int(x)
@@ -142,8 +142,13 @@ def _ptr(x) -> int | None:
 
 def _stream(s) -> int | None:
     if s is None:
-        import torch
+        if torch.cuda.is_initialized():
+            # the handle alone, without a Stream object around it: 0.3 us
+            # against 3.0 us
+            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
         return int(torch.cuda.current_stream().cuda_stream)
+    if type(s) is int:
+        return s
     if hasattr(s, "cuda_stream"):
         return int(s.cuda_stream)
     return int(s)
