@@ -250,9 +250,12 @@ sar_status sar_plan_get_table(sar_plan_t plan, int32_t which, void* host_dst,
 /* ---- batched execution (scenes of uneven size) ----
  *
  * Not in the paper: the batching pattern for many scenes.  Scenes with LFM
- * azimuth and the fused schedule share launches: one line launch per (pass,
- * line length, precision) and one corner-turn launch per turn, each a grid
- * over all scenes' line groups or tiles (task lists in device memory).  Every
+ * azimuth and the fused schedule share launches, each a grid over all their
+ * line groups or tiles (task lists in device memory): FP32 scenes with lines
+ * of 128 to 4096 points and no back-turn two launches in all (range lines into
+ * column tiles, azimuth strips; line lengths tuned to table twiddles excepted),
+ * the rest one line launch per (pass, line length, precision) and one
+ * corner-turn launch per turn.  Every
  * other scene (hyperbolic, unfused, half storage, and any scene of 2^22
  * pixels or more, which fills the GPU with its own launches) runs as
  * sar_rda_execute in the same stream, in scene order, after the shared

@@ -133,8 +133,8 @@ def header_functions() -> list[str]:
 
 # ------------------------------------------------------------ marshalling
 def _ptr(x) -> int | None:
-    if x is None or type(x) is int:
-        return x
+    if x is None:
+        return None
     if hasattr(x, "data_ptr"):
         return int(x.data_ptr())
     return int(x)

@@ -1,19 +1,20 @@
 // rda_batch.cpp -- batched execution of scenes of uneven size.
 //
-// All scenes of a batch share launches: one batched line launch per
-// (stage, line length) covering every scene with that length, one batched
-// corner turn for all scenes, so 64 scenes of 5 x 5 sizes take about a dozen
-// launches instead of ~200, and small scenes fill the GPU together.  Each
-// launch is a grid over the scenes' line groups (task lists in device memory,
-// see LineTask / TurnTask).  On a non-null stream the whole sequence is
-// captured once into a hipGraph per set of buffers and replayed; a new set of
-// buffer pointers rebuilds the tasks and the graph.
+// All scenes of a batch share launches.  FP32 scenes with lines of 128 to 4096
+// points take two for all of them, whatever their lengths (range lines into
+// column tiles, azimuth strips; see SceneTask).  The others (split precisions,
+// shorter and longer lines, turned-back images) take one batched line launch
+// per (stage, line length) and one batched corner turn.  So 64 scenes of 5 x 5
+// sizes take a few launches instead of ~130, and small scenes fill the GPU
+// together.  Each launch is a grid over the scenes' line groups (task lists in
+// device memory, see LineTask / SceneTask / TurnTask).  On a non-null stream
+// the whole sequence is captured once into a hipGraph per set of buffers and
+// replayed; a new set of buffer pointers rebuilds the tasks and the graph.
 //
 // Scenes whose processing the batched launches do not cover (hyperbolic
 // azimuth, the unfused schedule, half storage) and scenes large enough to
 // fill the chip alone (see kShareBelowPx) run through sar_rda_execute inside
-// the same stream (and graph); the large fused FP32 ones that the turn-free
-// kernels cover run those (bit-identical, without the corner turn).
+// the same stream (and graph).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -32,7 +33,7 @@ namespace {
 size_t align256(size_t x) { return (x + 255) / 256 * 256; }
 
 struct Launch {
-    int type;          // 0 line batch, 1 corner-turn batch
+    int type;          // 0 line batch, 1 corner-turn batch, 2 turn-free range, 3 turn-free strips
     int kind;          // line kind (0 fused)
     int n;             // line length
     int prec;
@@ -95,6 +96,21 @@ bool batched(const sar_params& p)
 {
     return p.az_model == SAR_AZ_LFM && p.schedule == SAR_FUSED && p.precision != SAR_FP32_HALF_STORAGE &&
            (long long)p.Na * p.Nr < kShareBelowPx;
+}
+
+// Batched scenes that run without the corner turn: two launches for all of
+// them, the range lines into column tiles and the azimuth strips (the kernels of
+// sar_rda_execute's own turn-free schedule, so the same bits).  FP32 lines of
+// BATCH_STRIP_MIN to BATCH_STRIP_MAX points; they form twiddles by products, so a line length
+// tuned to table twiddles stays with the turned passes.  Faster than those at
+// every mix measured: 24 scenes of 128 to 1024 a side 54.7 -> 32.1 us, 40 of up
+// to 2048 303 -> 195, 16 of 4096 x 512 338 -> 321, 8 of 1024 x 1024 108 -> 77.
+bool batched_strips(const sar_params& p)
+{
+    return batched(p) && p.precision == SAR_FP32 && !p.transpose_back &&
+           std::min(p.Nr, p.Na) >= sar::BATCH_STRIP_MIN && std::max(p.Nr, p.Na) <= sar::BATCH_STRIP_MAX &&
+           !((sar::tuned_variant(sar::TK_BATCH_FUSED, p.Nr, p.precision) |
+              sar::tuned_variant(sar::TK_BATCH_FUSED, p.Na, p.precision)) & 1);
 }
 
 // Build task arrays for this buffer set and upload them (synchronous).
@@ -181,9 +197,33 @@ sar_status build(sar_batch_s* B, const void* const* raw, void* const* img, void*
         host.resize(align256(host.size()));
         return SAR_OK;
     };
-    std::vector<int> scenes;
+    auto add_strip_stage = [&](bool range_stage, const std::vector<int>& scenes) {
+        Launch L{range_stage ? 2 : 3, 0, 0, 0, 0, host.size(), 0, 0};
+        for (int i : scenes) {
+            const sar_params& p = B->params[i];
+            const sar::PlanTables tb = sar::plan_tables(B->plans[B->plan_of[i]]);
+            sar::SceneTask t{};
+            t.in = (const float2*)(range_stage ? raw[i] : A[i]);
+            t.out = (float2*)(range_stage ? A[i] : Bt[i]);
+            t.H = (const float2*)(range_stage ? tb.Hr : tb.Ha);
+            t.tw = (const float2*)(range_stage ? tb.tw_r : tb.tw_a);
+            t.n = range_stage ? p.Nr : p.Na;
+            t.other = range_stage ? p.Na : p.Nr;
+            t.group_begin = L.total;
+            L.total += range_stage ? sar::batch_range_groups(t.n, t.other) : sar::batch_strip_groups(t.n, t.other);
+            const char* b = (const char*)&t;
+            host.insert(host.end(), b, b + sizeof t);
+            ++L.ntasks;
+        }
+        if (L.ntasks) launches.push_back(L);
+        host.resize(align256(host.size()));
+    };
+    std::vector<int> scenes, strips;
     for (int i = 0; i < n; ++i)
-        if (batched(B->params[i])) scenes.push_back(i);
+        if (batched_strips(B->params[i])) strips.push_back(i);
+        else if (batched(B->params[i])) scenes.push_back(i);
+    add_strip_stage(true, strips);
+    add_strip_stage(false, strips);
     add_line_stage(true, scenes);
     sar_status st = add_turn_stage(false, scenes);
     if (st != SAR_OK) return st;
@@ -211,10 +251,15 @@ sar_status enqueue(sar_batch_s* B, const void* const* raw, void* const* img, voi
 {
     for (const Launch& L : B->launches) {
         const char* tasks = (const char*)B->dev_tasks + L.task_off;
-        hipError_t e = L.type == 0
-                           ? sar::launch_line_batch(L.kind, L.n, tasks, L.ntasks, L.total, 1.0f, L.prec,
-                                                    L.variant, s)
-                           : sar::launch_corner_turn_batch(tasks, L.ntasks, L.total, s);
+        hipError_t e;
+        switch (L.type) {
+        case 0:
+            e = sar::launch_line_batch(L.kind, L.n, tasks, L.ntasks, L.total, 1.0f, L.prec, L.variant, s);
+            break;
+        case 1: e = sar::launch_corner_turn_batch(tasks, L.ntasks, L.total, s); break;
+        case 2: e = sar::launch_batch_range(tasks, L.ntasks, L.total, s); break;
+        default: e = sar::launch_batch_strip(tasks, L.ntasks, L.total, s); break;
+        }
         if (e != hipSuccess) return sar::set_error(SAR_ERR_HIP, "batched launch: %s", hipGetErrorString(e));
     }
     for (int i : B->fallback) {

@@ -35,6 +35,18 @@ struct LineTask {
     int group_begin;
 };
 
+// One scene of a batched turn-free pass (lines of any length share the launch):
+// range lines [other][n] -> column tiles, or azimuth strips of column tiles
+// -> [other][n].
+struct SceneTask {
+    const float2* in;
+    float2* out;
+    const float2* H;
+    const float2* tw;
+    int n, other;            // line length, number of lines
+    int group_begin;
+};
+
 // One matrix of a batched corner turn (rows x cols -> cols x rows).
 struct TurnTask {
     const float2* in;
@@ -115,6 +127,15 @@ hipError_t launch_rcmc_half(int n, const void* A, const int* ex, void* out, cons
                             const void* tw, hipStream_t s);
 // Corner turn of 4-byte elements (FP16 pairs); rows, cols multiples of 64.
 hipError_t launch_corner_turn_b4(const void* in, void* out, int rows, int cols, hipStream_t s);
+
+// The two passes of the batched turn-free scenes: tasks in device memory, line
+// lengths from BATCH_STRIP_MIN to BATCH_STRIP_MAX, groups as counted by the
+// functions beside them.
+constexpr int BATCH_STRIP_MIN = 128, BATCH_STRIP_MAX = 4096;
+int batch_range_groups(int n, int lines);
+int batch_strip_groups(int n, int lines);
+hipError_t launch_batch_range(const void* tasks, int ntasks, int total, hipStream_t s);
+hipError_t launch_batch_strip(const void* tasks, int ntasks, int total, hipStream_t s);
 
 hipError_t launch_corner_turn_batch(const void* tasks, int ntasks, int total_tiles, hipStream_t s);
 int line_groups(int n, int lines);        // line groups of `lines` lines of length n

@@ -25,6 +25,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <initializer_list>
 #include <type_traits>
 
 #include "fft_line.hpp"
@@ -274,6 +275,7 @@ struct TileMap {
     int na;          // rows (azimuth samples)
     int key_mask;    // min(127, na - 1)
 };
+__host__ __device__ constexpr TileMap tile_map(int na) { return TileMap{na, na < 128 ? na - 1 : 127}; }
 constexpr int TILE_COLS = 32;
 
 // Store the points t + m*T of line line0 + sub of the [na][N] array in column
@@ -367,20 +369,29 @@ __device__ __forceinline__ void line_group(const float2* in, float2* out, int li
     store_line<N>(x, buf_rsrc(out + first, bytes), off);
 }
 
-// The range pass of the turn-free schedules: fused lines stored in column tiles.
+// The range pass of the turn-free schedules: fused lines stored in column tiles
+// (group g of LPW lines of the [na][N] array).
+template <int N>
+__device__ __forceinline__ void line_tiled_group(const float2* in, float2* out, const float2* __restrict__ H,
+                                                 const float2* __restrict__ tw, const TileMap& tm, int g,
+                                                 float2* smem)
+{
+    using L = LineLaunch<N>;
+    const int sub = threadIdx.x / L::T, t = threadIdx.x % L::T, line0 = g * L::LPW;
+    float2 x[16];
+    load_line<N>(x, buf_rsrc(in + (size_t)line0 * N, L::LPW * N * 8u), (uint32_t)(sub * N + t) * 8u);
+    line_transform<N, LK_FUSED, PREC_FP32, true>(x, smem + sub * LineGeom<N>::LDS, H, tw, 1.0f, sub, t);
+    store_line_tiled<N, L::LPW>(x, out, tm, line0, sub, t);
+}
+
 template <int N>
 __global__ __launch_bounds__((LineLaunch<N>::BLOCK))
 __attribute__((amdgpu_waves_per_eu(line_wpe<N, PREC_FP32>()))) void
 k_line_tiled(const float2* in, float2* out, const float2* __restrict__ H,
              const float2* __restrict__ tw, TileMap tm)
 {
-    using L = LineLaunch<N>;
     extern __shared__ __align__(16) float2 smem[];
-    const int sub = threadIdx.x / L::T, t = threadIdx.x % L::T, line0 = blockIdx.x * L::LPW;
-    float2 x[16];
-    load_line<N>(x, buf_rsrc(in + (size_t)line0 * N, L::LPW * N * 8u), (uint32_t)(sub * N + t) * 8u);
-    line_transform<N, LK_FUSED, PREC_FP32, true>(x, smem + sub * LineGeom<N>::LDS, H, tw, 1.0f, sub, t);
-    store_line_tiled<N, L::LPW>(x, out, tm, line0, sub, t);
+    line_tiled_group<N>(in, out, H, tw, tm, blockIdx.x, smem);
 }
 
 // ---------------------------------------------------------- column strips
@@ -427,24 +438,23 @@ __device__ __forceinline__ StripSrc strip_source(const float2* in, const TileMap
     return s;
 }
 
+// Strip g of the scene, by the C T threads u = 0 .. C T - 1; a strip beyond the
+// last column (g uniform per wave) reads zeros and stores nothing.
 // BACK: the lines leave as they came, C samples of every row of out [N][cols]
 // (the back-turned image), regrouped through LDS once more.
-template <int N, int KIND, int CW = 0, bool BACK = false>
-__global__ __launch_bounds__((StripLaunch<N, CW>::BLOCK))
-__attribute__((amdgpu_waves_per_eu(N == 512 ? 7 : 8))) void      // 512 points spill at 64 registers
-k_line_strip(const float2* __restrict__ in, float2* __restrict__ out, int cols, TileMap tm,
-             const float2* __restrict__ H, const float2* __restrict__ tw, float scale)
+template <int N, int KIND, int CW, bool BACK>
+__device__ __forceinline__ void strip_group(const float2* __restrict__ in, float2* __restrict__ out,
+                                            int cols, const TileMap& tm, const float2* __restrict__ H,
+                                            const float2* __restrict__ tw, float scale, int g, int u,
+                                            float* smem)
 {
     using S = StripLaunch<N, CW>;
     constexpr int T = S::T, C = S::C;
     constexpr uint32_t ROW = TILE_COLS * 8u;      // bytes between rows of a tile
-    extern __shared__ __align__(16) float2 smem2[];
-    float* smem = (float*)smem2;
-    const int g = xcd_group(blockIdx.x, cols / C);
-    const int n0 = g * C;
-    const int u = threadIdx.x;
+    const bool here = g * C < cols;
+    const int n0 = here ? g * C : 0;
     const StripSrc src = strip_source(in, tm, cols, n0);
-    const __amdgpu_buffer_rsrc_t ib = buf_rsrc(src.base, src.bytes);
+    const __amdgpu_buffer_rsrc_t ib = buf_rsrc(src.base, here ? src.bytes : 0u);
     // 16-byte loads: lanes take pairs of adjacent columns, C / 2 lanes per row,
     // rows m0 + 2 T p; the row's exclusive or splits into the lane's and the
     // load's part because m0 < 2 T
@@ -491,7 +501,7 @@ k_line_strip(const float2* __restrict__ in, float2* __restrict__ out, int cols, 
         }
     }
     if constexpr (!BACK) {
-        store_line<N>(x, buf_rsrc(out + (size_t)n0 * N, C * N * 8u), (uint32_t)(sub * N + t) * 8u);
+        store_line<N>(x, buf_rsrc(out + (size_t)n0 * N, here ? C * N * 8u : 0u), (uint32_t)(sub * N + t) * 8u);
     } else {
 #pragma unroll
         for (int m = 0; m < 16; ++m) lds[half_in<T, 0>(t, m)] = x[m].x;
@@ -505,7 +515,7 @@ k_line_strip(const float2* __restrict__ in, float2* __restrict__ out, int cols, 
 #pragma unroll
         for (int m = 0; m < 16; ++m) lds[half_in<T, 0>(t, m)] = x[m].y;
         wg_barrier();
-        const __amdgpu_buffer_rsrc_t ob = buf_rsrc(out + n0, (uint32_t)(N * cols - n0) * 8u);
+        const __amdgpu_buffer_rsrc_t ob = buf_rsrc(out + n0, here ? (uint32_t)(N * cols - n0) * 8u : 0u);
         const uint32_t off = (uint32_t)(m0 * cols + 2 * q) * 8u;
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
@@ -514,6 +524,18 @@ k_line_strip(const float2* __restrict__ in, float2* __restrict__ out, int cols, 
             buf_st4(ob, off, (uint32_t)(2 * T * p * cols) * 8u, v[p]);
         }
     }
+}
+
+template <int N, int KIND, int CW = 0, bool BACK = false>
+__global__ __launch_bounds__((StripLaunch<N, CW>::BLOCK))
+__attribute__((amdgpu_waves_per_eu(N == 512 ? 7 : 8))) void      // 512 points spill at 64 registers
+k_line_strip(const float2* __restrict__ in, float2* __restrict__ out, int cols, TileMap tm,
+             const float2* __restrict__ H, const float2* __restrict__ tw, float scale)
+{
+    extern __shared__ __align__(16) float2 smem[];
+    strip_group<N, KIND, CW, BACK>(in, out, cols, tm, H, tw, scale,
+                                   xcd_group(blockIdx.x, cols / StripLaunch<N, CW>::C), threadIdx.x,
+                                   (float*)smem);
 }
 
 template <int N, int KIND, int PREC, bool TWP, bool SPLIT = false, int X = 1>
@@ -596,8 +618,8 @@ k_line_pipe(const float2* in, float2* out, int lines, const float2* __restrict__
 // groups gg = blockIdx.x, + gridDim.x, ...; the task of a group is found by
 // binary search over the tasks' first-group indices (sorted).
 // The task owning line group gg (tasks sorted by group_begin; uniform).
-__device__ __forceinline__ const LineTask& find_task(const LineTask* __restrict__ tasks, int ntasks,
-                                                      int gg)
+template <class Task>
+__device__ __forceinline__ const Task& find_task(const Task* __restrict__ tasks, int ntasks, int gg)
 {
     int lo = 0, hi = ntasks - 1;
     while (lo < hi) {
@@ -630,6 +652,91 @@ k_line_batch(const LineTask* __restrict__ tasks, int ntasks, int total_groups, f
         }
     }
 }
+
+#if SAR_PART == 4
+// Batched turn-free scenes: the two passes of every scene, whatever its line
+// length, are two launches.  The groups of a pass are independent and as large
+// as each other (4096 points of range lines, 8192 of strips), so a switch on the
+// task's length serves all of them with the same threads and LDS.
+// What bounds them: memory, once the launch is long enough.  Before, each line
+// length had its own launch per pass and a corner turn lay between, all too short
+// to fill the chip or to hide their start and end: 24 scenes of 128 to 1024 points
+// a side (78 MB moved per pass) took 54.7 us in nine launches, 32.1 in these two.
+// (64-point strips are left out: eight of them side by side take 66 KiB of LDS,
+// two workgroups per CU for every scene of the launch.)
+#define SAR_BATCH_LENGTHS(X) X(128) X(256) X(512) X(1024) X(2048) X(4096)
+
+constexpr int BATCH_RANGE_BLOCK = 256;
+#define SAR_LDS(N) LineLaunch<N>::LDS_BYTES,
+constexpr int batch_max(std::initializer_list<int> l)
+{
+    int m = 0;
+    for (int v : l) m = v > m ? v : m;
+    return m;
+}
+constexpr int BATCH_RANGE_LDS = batch_max({SAR_BATCH_LENGTHS(SAR_LDS)});
+#undef SAR_LDS
+
+__global__ __launch_bounds__(BATCH_RANGE_BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
+k_batch_range(const SceneTask* __restrict__ tasks, int ntasks)
+{
+    extern __shared__ __align__(16) float2 smem[];
+    const SceneTask& tk = find_task(tasks, ntasks, blockIdx.x);
+    const int g = blockIdx.x - tk.group_begin;
+    const TileMap tm = tile_map(tk.other);
+    switch (tk.n) {
+#define SAR_CASE(N)                                                              \
+    case N:                                                                      \
+        static_assert(LineLaunch<N>::BLOCK == BATCH_RANGE_BLOCK, "one block size"); \
+        line_tiled_group<N>(tk.in, tk.out, tk.H, tk.tw, tm, g, smem);            \
+        break;
+        SAR_BATCH_LENGTHS(SAR_CASE)
+#undef SAR_CASE
+    }
+}
+
+// 512 threads: strips as wide as they take up to the default width, several side
+// by side for short lines (whole waves each, so a strip's base is wave-uniform).
+constexpr int BATCH_STRIP_BLOCK = 512;
+template <int N> struct BatchStrip {
+    static constexpr int T = LineGeom<N>::T, D = StripLaunch<N>::C_DEFAULT;
+    static constexpr int C = BATCH_STRIP_BLOCK / T < D ? BATCH_STRIP_BLOCK / T : D;
+    static constexpr int PER_WG = BATCH_STRIP_BLOCK / (C * T);
+    static constexpr int LDS_BYTES = PER_WG * StripLaunch<N, C>::LDS_BYTES;
+    static_assert(C * T % 64 == 0, "whole waves per strip");
+};
+#define SAR_LDS(N) BatchStrip<N>::LDS_BYTES,
+constexpr int BATCH_STRIP_LDS = batch_max({SAR_BATCH_LENGTHS(SAR_LDS)});
+#undef SAR_LDS
+
+template <int N>
+__device__ __forceinline__ void batch_strip_group(const SceneTask& tk, int g, float* smem)
+{
+    using B = BatchStrip<N>;
+    using S = StripLaunch<N, B::C>;
+    const int k = __builtin_amdgcn_readfirstlane(threadIdx.x / S::BLOCK);
+    strip_group<N, LK_FUSED, B::C, false>(tk.in, tk.out, tk.other, tile_map(N), tk.H, tk.tw, 1.0f,
+                                          g * B::PER_WG + k, threadIdx.x % S::BLOCK,
+                                          smem + k * (S::LDS_BYTES / 4));
+}
+
+__global__ __launch_bounds__(BATCH_STRIP_BLOCK) __attribute__((amdgpu_waves_per_eu(6))) void
+k_batch_strip(const SceneTask* __restrict__ tasks, int ntasks, int total)
+{
+    extern __shared__ __align__(16) float2 smem[];
+    const int gg = xcd_group(blockIdx.x, total);
+    const SceneTask& tk = find_task(tasks, ntasks, gg);
+    const int g = gg - tk.group_begin;
+    switch (tk.n) {
+#define SAR_CASE(N)                                \
+    case N:                                        \
+        batch_strip_group<N>(tk, g, (float*)smem); \
+        break;
+        SAR_BATCH_LENGTHS(SAR_CASE)
+#undef SAR_CASE
+    }
+}
+#endif  // SAR_PART == 4
 
 #if SAR_PART == 0
 // out[r][k] = in[r][k] * H[k]  (unfused comparator's multiply dispatch)
@@ -2156,7 +2263,6 @@ hipError_t launch_line_fp32(LineOp op, int n, const float2* i, float2* o, int li
     return launch_line_prec<PREC_FP32>(op, n, i, o, lines, h, w, scale, ra, taps, v, s);
 }
 #elif SAR_PART == 4
-static TileMap tile_map(int na) { return TileMap{na, na < 128 ? na - 1 : 127}; }
 
 template <int N>
 static hipError_t launch_range_tiled_n(const float2* in, float2* out, int na, const float2* H,
@@ -2269,6 +2375,40 @@ hipError_t launch_line_strip(StripOp op, int n, const void* in, void* out, int c
     case 4096: return launch_strip_n<4096>(op, i, o, cols, h, w, scale, variant, s);
     default: return hipErrorInvalidValue;
     }
+}
+
+int batch_range_groups(int n, int lines)
+{
+    const int lpw = BATCH_RANGE_BLOCK * 16 / n;
+    return (lines + lpw - 1) / lpw;
+}
+
+int batch_strip_groups(int n, int lines)
+{
+    switch (n) {
+#define SAR_CASE(N) case N: return (lines + BatchStrip<N>::C * BatchStrip<N>::PER_WG - 1) / (BatchStrip<N>::C * BatchStrip<N>::PER_WG);
+        SAR_BATCH_LENGTHS(SAR_CASE)
+#undef SAR_CASE
+    default: return 0;
+    }
+}
+
+hipError_t launch_batch_range(const void* tasks, int ntasks, int total, hipStream_t s)
+{
+    static_assert(BATCH_RANGE_LDS <= 64 * 1024, "needs no LDS attribute");
+    if (total == 0) return hipSuccess;
+    SAR_LAUNCH(k_batch_range, dim3(total), dim3(BATCH_RANGE_BLOCK), BATCH_RANGE_LDS, s,
+               (const SceneTask*)tasks, ntasks);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_strip(const void* tasks, int ntasks, int total, hipStream_t s)
+{
+    static_assert(BATCH_STRIP_LDS <= 64 * 1024, "needs no LDS attribute");
+    if (total == 0) return hipSuccess;
+    SAR_LAUNCH(k_batch_strip, dim3(total), dim3(BATCH_STRIP_BLOCK), BATCH_STRIP_LDS, s,
+               (const SceneTask*)tasks, ntasks, total);
+    return hipGetLastError();
 }
 
 template <const void* (*KERNEL)(), int BYTES>
