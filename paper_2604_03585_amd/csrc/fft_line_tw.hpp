@@ -7,6 +7,7 @@
 // last-bit change moves a few values by a whole FP16 step (2^-11 relative;
 // 2.3e-5 relative L2 of a 4096^2 image, against 2.5e-4 from the FP16 rounding
 // itself), so those two passes keep this form, whose stored bits callers have.
+// So does the trailing pass of the split-BF16 lines (see mfma_fft.hpp).
 // They are bound by memory, not by the instruction count (range pass of
 // 4096^2: 66 us against 54 us for a plain copy of its FP32 input and output).
 #pragma once

@@ -32,13 +32,27 @@
 // FP32 between passes, on the output side of a pass (where a lane holds
 // complete complex values), already for the next pass.
 //
-// LDS holds the WG's lines as complex values (float2), one pad slot per 16
-// entries: the exchange layout of the FP32 path.
+// Between passes LDS holds the WG's lines as complex values (float2), at the
+// slots of mf_slot.  A line of 1024 points and more belongs to whole waves, whose
+// lanes can take their operands of the first pass straight from the caller: the
+// operand layout, point tm + 16 gi + h T in x[4 gi + h] (mf_point; 16 consecutive
+// points per load and quarter wave).  At 4096 = 16^3 points the last pass leaves
+// the outputs in that same layout, so forward transform, filter and inverse
+// follow each other without an exchange.
+//
+// What bounds it: VALU issue (splitting, twiddles and scaling; 93 instructions per
+// point of a fused line), memory for single transforms.  4096 fused lines of 4096
+// points took 111 us with every transform entered and left through LDS, one pad
+// slot per 16 entries (eight accesses per point and transform, two-way bank
+// conflicts in most) and 167 instructions per point at two waves per SIMD; 95 us
+// with four accesses, free of conflicts, at four waves; 78 us with the slots split
+// into a lane's part and constants and uniform twiddle rows.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include "fft_line.hpp"
+#include "fft_line_tw.hpp"
 
 namespace sar {
 
@@ -139,7 +153,53 @@ __device__ __forceinline__ DftOperands<PREC> dft16_operands(int lane)
     return d;
 }
 
-__device__ __forceinline__ int mf_pad(int i) { return i + (i >> 4); }
+// Slot of point e of a line (N slots; no pads).  LDS serves 8-byte accesses 32
+// lanes at a time from 32 slots' worth of banks, and the 32 lanes must differ in
+// the slot's low five bits.  They are 16 butterflies c and the low bit of q (or
+// 32 consecutive points, which any exclusive or of higher bits keeps apart):
+//   reads              e = .. + c + q N/4     (bits 0-3, the bit N/4)
+//   writes of pass 0   e = .. + 16 c + 4 q    (bits 4-7, bit 2)
+//   writes of pass 1   e = .. + c + 64 q      (bits 0-3, bit 6)
+//   writes of pass 2   e = .. + c + 1024 q    (bits 0-3, bit 10)
+// so bits 5, 6, 7 go into bits 0, 1, 3 (pass 0) and the bits 6, 10 and N/4 into
+// bit 4.  Shorter lines, whose slots do not split into a lane's part and constants
+// because a wave works on several, keep one pad slot per 16: forming the exclusive
+// ors costs them more than the conflicts (512 x 1024 scene 22.5 us with pads, 25.0
+// without).
+//
+// From 1024 points mf_slot is linear over exclusive or and changes the low five
+// bits alone: a point whose bits are those of a lane's part and of a constant has
+// the slot mf_at(slot of the part, slot of the constant), one exclusive or for the
+// constant's low bits and an instruction offset for the others.
+template <int N> __host__ __device__ constexpr int mf_slot(int e)
+{
+    if constexpr (N < 1024) return e + (e >> 4);
+    constexpr int LT = ilog2(N / 4);
+    int four = e >> 6;
+    if constexpr (N > 4096) four ^= e >> 10;
+    four ^= e >> LT;
+    return e ^ ((e >> 5) & 1) ^ ((e >> 5) & 2) ^ ((e >> 4) & 8) ^ ((four & 1) << 4);
+}
+
+__device__ __forceinline__ int mf_at(int lane_slot, int const_slot)
+{
+    return (lane_slot ^ (const_slot & 63)) + (const_slot & ~63);
+}
+
+// Register layouts of a line's 16 points per thread: point base + mf_step(m) of
+// x[m].  MF: the operand layout (see above), else the strided one, t + m T.
+template <int N, bool MF> __device__ __forceinline__ int mf_point(int t)
+{
+    if constexpr (!MF) return t;
+    return (t & ~63) + (t & 15) + 4 * ((t >> 4) & 3) * LineGeom<N>::T;
+}
+template <int N, bool MF> __host__ __device__ constexpr int mf_step(int m)
+{
+    return MF ? 16 * (m >> 2) + (m & 3) * LineGeom<N>::T : m * LineGeom<N>::T;
+}
+// Layouts in which a transform can take its input, and leaves its output.
+template <int N, int PREC> constexpr bool mf_in() { return PREC != PREC_FP32 && N >= 1024; }
+template <int N, int PREC> constexpr bool mf_out() { return PREC != PREC_FP32 && N == 4096; }
 
 // Exponent e of a line whose largest component is amax: amax * 2^-e lies in
 // [2^14, 2^15); zero, non-finite and empty lines keep e = 0.
@@ -151,9 +211,8 @@ __device__ __forceinline__ int mfma_line_exponent(float amax)
 
 // The line's exponent, from the largest |re|, |im| over its T threads: lane
 // segments of a wave when T <= 64, else whole waves combined through the
-// line's LDS pad slots (entries 17 w + 16 of its line, which the passes never
-// touch since mf_pad skips them).  On entry no wave may still read the
-// workgroup's LDS (the callers end every earlier LDS use with a barrier).
+// line's LDS beyond its N slots, which the passes never touch: the barrier here
+// also ends every read that the workgroup has issued of its lines before.
 template <int T, int LL>
 __device__ __forceinline__ int mfma_line_scale_exp(const float2 (&x)[16], float2* __restrict__ lds,
                                                    int sub)
@@ -166,14 +225,14 @@ __device__ __forceinline__ int mfma_line_scale_exp(const float2 (&x)[16], float2
     for (int off = 1; off < W; off <<= 1) m = fmaxf(m, __shfl_xor(m, off));
     if constexpr (T > 64) {
         constexpr int WPL = T / 64;               // waves per line
-        static_assert(17 * (WPL - 1) + 16 < LL, "pad slots of the line");
+        static_assert(T * 16 + WPL <= LL, "slots beyond the line");
         const int lane = threadIdx.x & 63, wl = (threadIdx.x >> 6) % WPL;
-        float2* slots = lds + sub * LL;
-        if (lane == 0) slots[17 * wl + 16].x = m;
-        __syncthreads();
+        float* slots = (float*)(lds + sub * LL + T * 16);
+        if (lane == 0) slots[wl] = m;
+        wg_barrier();
         m = 0.f;
 #pragma unroll
-        for (int w = 0; w < WPL; ++w) m = fmaxf(m, slots[17 * w + 16].x);
+        for (int w = 0; w < WPL; ++w) m = fmaxf(m, slots[w]);
     }
     const int e = mfma_line_exponent(m);
     // a wave holds one line when T >= 64: the exponent is wave-uniform
@@ -183,13 +242,16 @@ __device__ __forceinline__ int mfma_line_scale_exp(const float2 (&x)[16], float2
 
 // All radix-16 passes of the lines of one workgroup on MFMA, followed by the
 // trailing smaller pass (if any) in FP32.  On entry each thread holds its
-// line's x in the strided register layout (see fft_line.hpp); on exit it
-// holds the transform (scaled back to the plain unnormalised DFT).
+// line's x in the strided register layout (see fft_line.hpp), with IN_MF in the
+// operand layout; on exit it holds the transform (scaled back to the plain
+// unnormalised DFT), in the operand layout where mf_out, else strided.
 //   lds:   the workgroup's LDS (LPW lines, N + N/16 float2 each)
 //   sub:   this thread's line within the workgroup, t its index in the line
 //   before_last: runs as the last MFMA pass starts (callers issue the loads
 //          they need right after the transform there, e.g. a filter)
-template <int N, bool INV, int PREC, int LPW, int BLOCK, class Pre = NoOp>
+// On entry no wave may still read the lines' LDS unless it was the previous
+// transform's (mf_out leaves without a barrier, see mfma_line_scale_exp).
+template <int N, bool INV, int PREC, int LPW, int BLOCK, bool IN_MF, class Pre = NoOp>
 __device__ __forceinline__ void fft_line_mfma(float2 (&x)[16], float2* __restrict__ lds,
                                               const float2* __restrict__ tw, int sub, int t,
                                               Pre&& before_last = Pre())
@@ -204,16 +266,45 @@ __device__ __forceinline__ void fft_line_mfma(float2 (&x)[16], float2* __restric
     constexpr int WAVES = BLOCK / 64;
     constexpr int GPW = GROUPS / WAVES;          // groups per wave
     static_assert(GROUPS % WAVES == 0 && GPW >= 1, "group split");
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-
+    // formed anew in each transform: its LDS slots kept across the multiply take
+    // 90 registers
+    if constexpr (T >= 64) t = fresh(t);
+    const int tid = T >= 64 ? sub * T + t : (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, q = lane >> 4;
+    // Butterfly j of the line for group gi.  LINES: the wave's groups belong to one
+    // line, j = j0 + 16 gi, and the bits of every point are a lane's part and a
+    // constant (a third fewer instructions than by the general form).
+    constexpr bool LINES = T >= 64 && GPW == 4;
+    const int wl = LINES ? __builtin_amdgcn_readfirstlane(t >> 6) : 0;
+    const int j0 = 64 * wl + c;
+    float2* const own = lds + sub * LL;
+    auto in_slot = [&](int gi, int h) -> float2* {     // point j + (4q + h) N/16
+        if constexpr (LINES) return own + mf_at(mf_slot<N>(j0 + 4 * q * NB), mf_slot<N>(16 * gi + h * NB));
+        const int b = (wave * GPW + gi) * 16 + c;
+        return lds + b / NB * LL + mf_slot<N>(b % NB + (4 * q + h) * NB);
+    };
+    auto out_slot = [&](int NS, int gi, int i) -> float2* {
+        if constexpr (LINES) {
+            const int part = (j0 / NS) * NS * 16 + (j0 & (NS - 1)) + 4 * q * NS;
+            return own + mf_at(mf_slot<N>(part), mf_slot<N>((NS <= 16 ? 256 : 16) * gi + i * NS));
+        }
+        const int b = (wave * GPW + gi) * 16 + c, j = b % NB;
+        return lds + b / NB * LL + mf_slot<N>((j / NS) * NS * 16 + (j & (NS - 1)) + (4 * q + i) * NS);
+    };
 
-    // registers -> LDS, scaled by the line's 2^-ex
+    constexpr bool OUT_MF = mf_out<N, PREC>();
+    static_assert(!IN_MF || (T >= 64 && GPW == 4), "operand layout: whole waves per line");
+    static_assert(!OUT_MF || (T > 64 && GPW == 4 && G::NP == NMF), "outputs where the inputs were");
+
+    // scaled by the line's 2^-ex; strided inputs go to LDS
     const int ex = mfma_line_scale_exp<T, LL>(x, lds, sub);
 #pragma unroll
-    for (int m = 0; m < 16; ++m)
-        lds[sub * LL + mf_pad(t + m * T)] = make_float2(ldexpf(x[m].x, -ex), ldexpf(x[m].y, -ex));
-    __syncthreads();
+    for (int m = 0; m < 16; ++m) {
+        const float2 v = make_float2(ldexpf(x[m].x, -ex), ldexpf(x[m].y, -ex));
+        if constexpr (IN_MF) x[m] = v;
+        else own[LINES ? mf_at(mf_slot<N>(t), mf_slot<N>(m * T)) : mf_slot<N>(t + m * T)] = v;
+    }
+    if constexpr (!IN_MF) wg_barrier();
 
     const DftOperands<PREC> F = dft16_operands<PREC, INV>(lane);
 
@@ -236,9 +327,15 @@ __device__ __forceinline__ void fft_line_mfma(float2 (&x)[16], float2* __restric
             const float2* tab = tw + G::tw_off(p + 1);
 #pragma unroll
             for (int gi = 0; gi < GPW; ++gi) {
-                const int b = (wave * GPW + gi) * 16 + c;
-                const int j = b % NB, jm = j & (NS - 1);
-                const int i2 = ((j / NS) * NS * 16 + jm + 4 * q * NS) / NB;
+                int i2, jm;
+                if constexpr (LINES && NB >= 256) {    // uniform
+                    i2 = (1024 * wl + 256 * gi) / NB;
+                    jm = c & (NS - 1);
+                } else {
+                    const int j = ((wave * GPW + gi) * 16 + c) % NB;
+                    jm = j & (NS - 1);
+                    i2 = ((j / NS) * NS * 16 + jm + 4 * q * NS) / NB;
+                }
                 const float2* row = tab + (i2 > 0 ? i2 - 1 : 0) * (NS * 16);
                 w0[gi] = row[jm + 4 * q * NS];
                 wst[gi] = row[NS];
@@ -248,13 +345,10 @@ __device__ __forceinline__ void fft_line_mfma(float2 (&x)[16], float2* __restric
         float2 y[GPW][4];
 #pragma unroll
         for (int gi = 0; gi < GPW; ++gi) {
-            const int b = (wave * GPW + gi) * 16 + c;          // butterfly in the WG
-            const int s = b / NB, j = b % NB;
-            const float2* src = lds + s * LL;
             float v[8];
 #pragma unroll
             for (int h = 0; h < 4; ++h) {
-                const float2 u = src[mf_pad(j + (4 * q + h) * NB)];
+                const float2 u = IN_MF && p == 0 ? x[4 * gi + h] : *in_slot(gi, h);
                 v[2 * h] = u.x;
                 v[2 * h + 1] = u.y;
             }
@@ -267,49 +361,62 @@ __device__ __forceinline__ void fft_line_mfma(float2 (&x)[16], float2* __restric
             ai = MfmaT<PREC>::mma(F.ih, bh, ai);
             ai = MfmaT<PREC>::mma(F.ih, bl, ai);
             ai = MfmaT<PREC>::mma(F.il, bh, ai);
-            float2 w = w0[gi], d = wst[gi];
-            if (INV) {
-                w.y = -w.y;
-                d.y = -d.y;
+            float2 w = make_float2(1.f, 0.f), d = w;
+            if (next_mfma && won[gi]) {
+                w = make_float2(w0[gi].x, INV ? -w0[gi].y : w0[gi].y);
+                d = make_float2(wst[gi].x, INV ? -wst[gi].y : wst[gi].y);
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 float2 o = make_float2(ar[i], ai[i]);
                 if (next_mfma) {                  // pre-twiddle for the next radix-16 pass
-                    const float2 ow = c_mul(o, w);
-                    o = won[gi] ? ow : o;
+                    o = c_mul(o, w);
                     if (i < 3) w = c_mul(w, d);
                 }
                 y[gi][i] = o;
             }
         }
-        __syncthreads();                          // every read of this pass is done
+        if (OUT_MF && p == NMF - 1) {
 #pragma unroll
-        for (int gi = 0; gi < GPW; ++gi) {
-            const int b = (wave * GPW + gi) * 16 + c;
-            const int s = b / NB, j = b % NB;
-            const int base = (j / NS) * NS * 16 + (j & (NS - 1));
+            for (int gi = 0; gi < GPW; ++gi)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) lds[s * LL + mf_pad(base + (4 * q + i) * NS)] = y[gi][i];
+                for (int i = 0; i < 4; ++i) x[4 * gi + i] = y[gi][i];
+            break;
         }
-        __syncthreads();
+        if (!IN_MF || p > 0) wg_barrier();        // every read of this pass is done
+#pragma unroll
+        for (int gi = 0; gi < GPW; ++gi)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) *out_slot(NS, gi, i) = y[gi][i];
+        wg_barrier();
     }
 
     // LDS -> registers, undo the 1/16 per MFMA pass and the line's scale
     const int undo = ex + 4 * NMF;
 #pragma unroll
     for (int m = 0; m < 16; ++m) {
-        const float2 u = lds[sub * LL + mf_pad(t + m * T)];
+        float2 u = x[m];
+        if constexpr (!OUT_MF) u = own[LINES ? mf_at(mf_slot<N>(t), mf_slot<N>(m * T)) : mf_slot<N>(t + m * T)];
         x[m] = make_float2(ldexpf(u.x, undo), ldexpf(u.y, undo));
     }
-    __syncthreads();                              // LDS free for the caller's next use
+    if constexpr (!OUT_MF) wg_barrier();          // LDS free for the caller's next use
     if constexpr (G::NP > NMF) {
-        // trailing radix-2/4/8 pass in FP32 (its twiddles applied on input)
-        TwReads<N, G::NP - 1, false> rd;
-        TwSet pt;
-        tw_issue<N, G::NP - 1, false>(rd, tw, t);
-        tw_form<N, G::NP - 1, false>(pt, rd);
-        fft_pass<N, G::NP - 1, INV>(x, (float2*)nullptr, pt, t);
+        // trailing radix-2/4/8 pass in FP32
+        if constexpr (PREC == PREC_BF16) {
+            // in the form whose last bits callers have: what follows splits its
+            // operands to 16 significand bits, where a change of the last FP32 bit
+            // moves some values by 2^-17 and the passes after it spread that (8192 x
+            // 8192 LFM image: 4e-6 relative L2, 8.2e-4 of the rms at one sample)
+            tw_first::PassTw<N, G::NP - 1> pt;
+            tw_first::load_tw<N, G::NP - 1>(pt, tw, t);
+            tw_first::fft_pass<N, G::NP - 1, INV>(x, (float2*)nullptr, pt, t);
+        } else {
+            TwReads<N, G::NP - 1, false> rd;
+            TwSet pt;
+            tw_issue<N, G::NP - 1, false>(rd, tw, t);
+            tw_form<N, G::NP - 1, false>(pt, rd);
+            fft_pass<N, G::NP - 1, INV>(x, (float2*)nullptr, pt, t);
+        }
     }
 }
 

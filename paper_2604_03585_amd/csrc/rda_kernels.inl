@@ -9,16 +9,22 @@
 // Kernels (paper: arXiv 2604.03585):
 //   k_gen_*          FP64 plan-time tables (twiddles, matched filters with
 //                    the IFFT's 1/N folded in, hyperbolic per-bin tables).
-//   k_line_fused     FFT -> x H -> IFFT per line, one HBM read and one write
+//   k_line           FFT -> x H -> IFFT per line, one HBM read and one write
 //                    (Sec. II.B; range compression and LFM azimuth
-//                    compression, Sec. IV.A steps 1 and 4).
-//   k_line_fft       FFT or IFFT only (azimuth FFT of Sec. IV.A step 2; the
-//                    first/last dispatch of the unfused comparator, Fig. 1).
+//                    compression, Sec. IV.A steps 1 and 4), or the FFT or IFFT
+//                    alone (azimuth FFT of Sec. IV.A step 2; the first/last
+//                    dispatch of the unfused comparator, Fig. 1); k_line_pipe
+//                    its persistent form for long lines.
+//   k_line_tiled,    the range pass into column tiles and the azimuth pass
+//   k_line_strip     over strips of them (no corner turn); k_batch_range and
+//                    k_batch_strip the same for many scenes.
+//   k_line_batch     k_line's lines of many scenes.
 //   k_rowmul         the unfused comparator's separate filter multiply.
 //   k_corner_turn    LDS-tiled [rows][cols] -> [cols][rows] transpose
 //                    (Sec. IV.B).
-//   k_rcmc_az        RCMC (8-tap Kaiser-sinc) + exact-geometry azimuth phase
-//                    + IFFT per output range line, fused (Sec. IV.A steps 3-4).
+//   k_rcmc_az,       RCMC (8-tap Kaiser-sinc) + exact-geometry azimuth phase
+//   k_rcmc_az2,      + IFFT, fused (Sec. IV.A steps 3-4): one, two and four
+//   k_rcmc_rows      output range lines per group of threads.
 //   k_rcmc_interp,   the same two steps as separate dispatches for the
 //   k_az_phase       unfused comparator.
 #include <hip/hip_ext.h>
@@ -139,20 +145,23 @@ template <int N, int X = 1> struct LineLaunch {
     static constexpr int LDS_BYTES = LPW * LineGeom<N>::LDS * (int)sizeof(float2);
 };
 
-// Minimum waves per SIMD requested for the line kernels: 4 for the FP32
-// kernels of 1024 to 4096 points (as many workgroups as LDS allows); 2 for the split-precision
-// (MFMA) kernels (left to itself the fused 4096-point one takes 268 VGPRs,
-// one wave per SIMD); no request otherwise.
+// Minimum waves per SIMD requested for the line kernels: 4 for 1024 points and
+// more (FP32 up to 4096, as many workgroups as LDS allows; the split-precision
+// ones take 112 to 128 VGPRs; split BF16 below 4096 points 3, for the reads of its
+// trailing pass's twiddles), else 2 in the split precisions (130 VGPRs; held to
+// 128 they spill) and no request in FP32.
 template <int N, int PREC> constexpr int line_wpe()
 {
     if constexpr (PREC == 0) return N >= 1024 && N <= 4096 ? 4 : 1;
-    else return 2;     // four waves (128 VGPRs) spill in the split transforms, measured slower
+    else return N >= 4096 || (N >= 1024 && PREC == 1) ? 4 : (N >= 1024 ? 3 : 2);
 }
 
 // Line transform in the requested butterfly precision: FP32 VALU passes, or
 // split FP16 / BF16 radix-16 passes on MFMA (twiddles and filters in FP32).
+// IN_MF: the input is in the operand layout (split precisions; the output is
+// where mf_out).
 template <int N, bool INV, int PREC, bool TWP = true, bool SPLIT = false, class F = NoOp,
-          bool AHEAD = false, int FRESH = 0>
+          bool AHEAD = false, int FRESH = 0, bool IN_MF = false>
 __device__ __forceinline__ void fft_any(float2 (&x)[line_e(N)], float2* __restrict__ lds,
                                         const float2* __restrict__ tw, int sub, int t,
                                         F&& before_last = F())
@@ -163,7 +172,7 @@ __device__ __forceinline__ void fft_any(float2 (&x)[line_e(N)], float2* __restri
         fft_line<N, INV, TWP, SPLIT, FRESH>(x, lds, tw, t, before_last);
     } else {
         using L = LineLaunch<N>;
-        fft_line_mfma<N, INV, PREC, L::LPW, L::BLOCK>(x, lds - sub * LineGeom<N>::LDS, tw, sub,
+        fft_line_mfma<N, INV, PREC, L::LPW, L::BLOCK, IN_MF>(x, lds - sub * LineGeom<N>::LDS, tw, sub,
                                                       t, before_last);
     }
 }
@@ -216,36 +225,36 @@ __device__ __forceinline__ void buf_st4(__amdgpu_buffer_rsrc_t r, uint32_t voff,
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4_t, v), r, voff, soff, 0);
 }
 
-// Points t + m*T of a line; `off` is the byte offset of point t from the
-// resource's base.
-template <int N>
+// Points t + m*T of a line, or those of the operand layout (MF); `off` is the
+// byte offset of the thread's first point from the resource's base.
+template <int N, bool MF = false>
 __device__ __forceinline__ void load_line(float2 (&x)[line_e(N)], __amdgpu_buffer_rsrc_t src,
                                           uint32_t off)
 {
 #pragma unroll
-    for (int m = 0; m < line_e(N); ++m) x[m] = buf_ld(src, off, m * LineGeom<N>::T * 8u);
+    for (int m = 0; m < line_e(N); ++m) x[m] = buf_ld(src, off, mf_step<N, MF>(m) * 8u);
 }
 
-template <int N>
+template <int N, bool MF = false>
 __device__ __forceinline__ void store_line(const float2 (&x)[line_e(N)], __amdgpu_buffer_rsrc_t dst,
                                            uint32_t off)
 {
 #pragma unroll
-    for (int m = 0; m < line_e(N); ++m) buf_st(dst, off, m * LineGeom<N>::T * 8u, x[m]);
+    for (int m = 0; m < line_e(N); ++m) buf_st(dst, off, mf_step<N, MF>(m) * 8u, x[m]);
 }
 
 // The RCMC pass's stores of its image lines pass by the caches (non-temporal):
 // the rows that are still gathered then stay in an XCD's L2 (8192 points: 212 ->
 // 188 us per 32 Mpx, 2048 x 4096 hyperbolic scene 95.8 -> 91.1), and the image is
 // not read again.  CACHED: the exception, see rcmc_image_cached.
-template <int N, bool CACHED = false>
+template <int N, bool CACHED = false, bool MF = false>
 __device__ __forceinline__ void store_image_line(const float2 (&x)[line_e(N)], __amdgpu_buffer_rsrc_t dst,
                                                  uint32_t off)
 {
 #pragma unroll
     for (int m = 0; m < line_e(N); ++m) {
-        if constexpr (CACHED) buf_st(dst, off, m * LineGeom<N>::T * 8u, x[m]);
-        else buf_st_nt(dst, off, m * LineGeom<N>::T * 8u, x[m]);
+        if constexpr (CACHED) buf_st(dst, off, mf_step<N, MF>(m) * 8u, x[m]);
+        else buf_st_nt(dst, off, mf_step<N, MF>(m) * 8u, x[m]);
     }
 }
 
@@ -316,8 +325,9 @@ enum LineKind { LK_FUSED = 0, LK_FWD = 1, LK_INV = 2 };
 // twiddles by products (true) or straight table reads (false), chosen per
 // line length by the autotuner; SPLIT (FP32 forward / inverse): the split
 // real/imaginary exchange layout.
-// The transform of one line held by its T threads (thread t: points t + m*T)
-// with `lds` its exchange buffer: FFT * H * IFFT, FFT or IFFT (see line_group).
+// The transform of one line held by its T threads (thread t: points t + m*T;
+// split precisions: in the layout of mf_in, left in that of mf_out) with `lds`
+// its exchange buffer: FFT * H * IFFT, FFT or IFFT (see line_group).
 template <int N, int KIND, int PREC, bool TWP, bool SPLIT = false>
 __device__ __forceinline__ void line_transform(float2 (&x)[line_e(N)], float2* __restrict__ lds,
                                                const float2* __restrict__ H,
@@ -326,6 +336,7 @@ __device__ __forceinline__ void line_transform(float2 (&x)[line_e(N)], float2* _
 {
     using L = LineLaunch<N>;
     constexpr int E = line_e(N);
+    constexpr bool IN = mf_in<N, PREC>(), OUT = mf_out<N, PREC>();
     if constexpr (KIND == LK_FUSED) {
         // the filter is requested just before the last forward pass; lines of
         // 4096 points and more read their twiddles one pass ahead, shorter
@@ -333,13 +344,13 @@ __device__ __forceinline__ void line_transform(float2 (&x)[line_e(N)], float2* _
         constexpr bool AHEAD = N >= 4096;
         float2 h[E];
         const __amdgpu_buffer_rsrc_t hb = buf_rsrc(H, N * 8u);
-        auto filter = [&] { load_line<N>(h, hb, (uint32_t)t * 8u); };
-        fft_any<N, false, PREC, TWP, false, decltype(filter)&, AHEAD>(x, lds, tw, sub, t, filter);
+        auto filter = [&] { load_line<N, OUT>(h, hb, (uint32_t)mf_point<N, OUT>(t) * 8u); };
+        fft_any<N, false, PREC, TWP, false, decltype(filter)&, AHEAD, 0, IN>(x, lds, tw, sub, t, filter);
 #pragma unroll
         for (int m = 0; m < E; ++m) x[m] = c_mul(x[m], h[m]);
-        fft_any<N, true, PREC, TWP, false, NoOp, AHEAD, L::FRESH_INV>(x, lds, tw, sub, t);
+        fft_any<N, true, PREC, TWP, false, NoOp, AHEAD, L::FRESH_INV, OUT>(x, lds, tw, sub, t);
     } else {
-        fft_any<N, KIND == LK_INV, PREC, TWP, SPLIT, NoOp, true>(x, lds, tw, sub, t);
+        fft_any<N, KIND == LK_INV, PREC, TWP, SPLIT, NoOp, true, 0, IN>(x, lds, tw, sub, t);
         if (scale != 1.0f) {
 #pragma unroll
             for (int m = 0; m < E; ++m) x[m] = c_scale(x[m], scale);
@@ -361,12 +372,12 @@ __device__ __forceinline__ void line_group(const float2* in, float2* out, int li
     const size_t first = (size_t)g * L::LPW * N;
     const int here = lines - g * L::LPW;
     const uint32_t bytes = (uint32_t)((here < L::LPW ? here : L::LPW) * N) * 8u;
-    const uint32_t off = (uint32_t)(sub * N + t) * 8u;
+    constexpr bool IN = mf_in<N, PREC>(), OUT = mf_out<N, PREC>();
     float2* lds = smem + sub * LineGeom<N>::LDS;
     float2 x[E];
-    load_line<N>(x, buf_rsrc(in + first, bytes), off);
+    load_line<N, IN>(x, buf_rsrc(in + first, bytes), (uint32_t)(sub * N + mf_point<N, IN>(t)) * 8u);
     line_transform<N, KIND, PREC, TWP, SPLIT>(x, lds, H, tw, scale, sub, t);
-    store_line<N>(x, buf_rsrc(out + first, bytes), off);
+    store_line<N, OUT>(x, buf_rsrc(out + first, bytes), (uint32_t)(sub * N + mf_point<N, OUT>(t)) * 8u);
 }
 
 // The range pass of the turn-free schedules: fused lines stored in column tiles
@@ -1330,7 +1341,9 @@ k_rcmc_az(const float2* __restrict__ A, float2* __restrict__ out, RcmcArgs ra,
     if constexpr (TAPS != 0) __syncthreads();     // table reads done before LDS reuse
     fft_any<N, true, PREC>(x, lds, tw, sub, t);
     const uint32_t bytes = (uint32_t)(min(L::LPW, lines - g * L::LPW) * N) * 8u;   // absent lines dropped
-    store_line<N>(x, buf_rsrc(out + (size_t)g * L::LPW * N, bytes), (uint32_t)(sub * N + t) * 8u);
+    constexpr bool OUT = mf_out<N, PREC>();
+    store_line<N, OUT>(x, buf_rsrc(out + (size_t)g * L::LPW * N, bytes),
+                       (uint32_t)(sub * N + mf_point<N, OUT>(t)) * 8u);
 }
 
 // Two output rows n, n+1 per line slot.  For each column their 8-tap
@@ -1425,14 +1438,15 @@ __device__ __forceinline__ void rcmc_pair_combine(float2& ya, float2& yb, const 
     yb = c_mul(rcmc_combine(c.xb, tab, tb), c.pb);
 }
 
-// Columns t + m * S (m < C) of rows n, n+1 of A (FP32 rows, or HalfRows).
-template <int N, bool EDGE, int C = line_e(N), int S = LineGeom<N>::T, class Src = const float2*>
+// Columns t + m * S (m < C) of rows n, n+1 of A (FP32 rows, or HalfRows); MF: the
+// columns of the operand layout, t the thread's first.
+template <int N, bool EDGE, int C = line_e(N), int S = LineGeom<N>::T, class Src = const float2*, bool MF = false>
 __device__ __forceinline__ void rcmc_rows2(float2 (&xa)[C], float2 (&xb)[C], Src A,
                                            const RcmcArgs& ra, int n, int t,
                                            const float* __restrict__ tab)
 {
-    constexpr int T = S;
     constexpr int E = C;
+    auto col = [&](int m) { return t + (MF ? mf_step<N, MF>(m) : m * S); };
     static_assert(E % 2 == 0, "columns are processed in pairs");
     constexpr float scale = 1.0f / (float)N;
     // two named buffers, alternated by column parity (no register copies)
@@ -1441,14 +1455,14 @@ __device__ __forceinline__ void rcmc_rows2(float2 (&xa)[C], float2 (&xb)[C], Src
     rcmc_gather10<N, EDGE>(w0, A, t, c0.i0, ra.nr);
 #pragma unroll
     for (int m = 0; m < E; m += 2) {
-        c1 = col_pair(ra, n, t + (m + 1) * T, N, scale);
-        rcmc_gather10<N, EDGE>(w1, A, t + (m + 1) * T, c1.i0, ra.nr);
+        c1 = col_pair(ra, n, col(m + 1), N, scale);
+        rcmc_gather10<N, EDGE>(w1, A, col(m + 1), c1.i0, ra.nr);
         __builtin_amdgcn_sched_barrier(0);
         rcmc_pair_combine<N, EDGE>(xa[m], xb[m], c0, w0, tab);
         __builtin_amdgcn_sched_barrier(0);
         if (m + 2 < E) {
-            c0 = col_pair(ra, n, t + (m + 2) * T, N, scale);
-            rcmc_gather10<N, EDGE>(w0, A, t + (m + 2) * T, c0.i0, ra.nr);
+            c0 = col_pair(ra, n, col(m + 2), N, scale);
+            rcmc_gather10<N, EDGE>(w0, A, col(m + 2), c0.i0, ra.nr);
         }
         __builtin_amdgcn_sched_barrier(0);
         rcmc_pair_combine<N, EDGE>(xa[m + 1], xb[m + 1], c1, w1, tab);
@@ -1467,6 +1481,7 @@ k_rcmc_az2(const void* __restrict__ A_, float2* __restrict__ out, RcmcArgs ra,
     if constexpr (HIN) A = HalfRows{(const h2_t*)A_, ra.row_exp};
     else A = (const float2*)A_;
     using L = LineLaunch<N>;
+    constexpr bool IN = mf_in<N, PREC>(), OUT = mf_out<N, PREC>();
     constexpr int E = line_e(N);
     extern __shared__ __align__(16) float2 smem[];
     float* tab = (float*)smem;                    // shares LDS with the line buffers
@@ -1488,19 +1503,19 @@ k_rcmc_az2(const void* __restrict__ A_, float2* __restrict__ out, RcmcArgs ra,
     } else {
         const double smax = (ra.r_near + (double)n + 1.0) * ra.stretch_max;
         if (n >= 3 && (double)n + 1.0 + smax + 6.0 <= (double)(ra.nr - 1))
-            rcmc_rows2<N, false, line_e(N), LineGeom<N>::T, SrcT>(xa, xb, A, ra, n, t, tab);
+            rcmc_rows2<N, false, line_e(N), LineGeom<N>::T, SrcT, IN>(xa, xb, A, ra, n, mf_point<N, IN>(t), tab);
         else
-            rcmc_rows2<N, true, line_e(N), LineGeom<N>::T, SrcT>(xa, xb, A, ra, n, t, tab);
+            rcmc_rows2<N, true, line_e(N), LineGeom<N>::T, SrcT, IN>(xa, xb, A, ra, n, mf_point<N, IN>(t), tab);
     }
     __syncthreads();                              // table reads done before LDS reuse
-    fft_any<N, true, PREC, true, false, NoOp, true>(xa, lds, tw, sub, t);
+    fft_any<N, true, PREC, true, false, NoOp, true, 0, IN>(xa, lds, tw, sub, t);
     // the group's pairs of rows (absent ones are not stored)
     const uint32_t bytes = (uint32_t)(min(L::LPW, pairs - g * L::LPW) * 2 * N) * 8u;
     const __amdgpu_buffer_rsrc_t ob = buf_rsrc(out + (size_t)(2 * g * L::LPW) * N, bytes);
-    const uint32_t off = (uint32_t)(2 * sub * N + t) * 8u;
-    store_image_line<N, N == 4096>(xa, ob, off);
-    fft_any<N, true, PREC, true, false, NoOp, true>(xb, lds, tw, sub, t);
-    store_image_line<N, N == 4096>(xb, ob, off + N * 8u);
+    const uint32_t off = (uint32_t)(2 * sub * N + mf_point<N, OUT>(t)) * 8u;
+    store_image_line<N, N == 4096, OUT>(xa, ob, off);
+    fft_any<N, true, PREC, true, false, NoOp, true, 0, IN>(xb, lds, tw, sub, t);
+    store_image_line<N, N == 4096, OUT>(xb, ob, off + N * 8u);
 }
 
 // Four output rows n .. n + 3 per group of threads (FP32 butterflies), for
@@ -1656,8 +1671,10 @@ __device__ __forceinline__ void rcmc_rows_columns(float2 (&y)[RcmcRows<N>::SIDE]
 }
 
 // HIN: A holds FP16 rows with per-row exponents ra.row_exp (half storage).
-template <int N, bool HIN = false>
-__global__ __launch_bounds__(RcmcRows<N>::BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
+// PREC: butterflies of the IFFT.
+template <int N, bool HIN = false, int PREC = PREC_FP32>
+__global__ __launch_bounds__(RcmcRows<N>::BLOCK)
+__attribute__((amdgpu_waves_per_eu(4))) void
 k_rcmc_rows(const void* __restrict__ A, float2* __restrict__ out, RcmcArgs ra,
             const float2* __restrict__ tw)
 {
@@ -1691,16 +1708,22 @@ k_rcmc_rows(const void* __restrict__ A, float2* __restrict__ out, RcmcArgs ra,
                 for (int m = 0; m < L::C; ++m) lines[(gi * SIDE + j) * LL + lds_in<S, 0>(u, m)] = y[j][m];
             wg_barrier();
         }
+        constexpr bool IN = mf_in<N, PREC>(), OUT = mf_out<N, PREC>();
         float2 x[16];
+        const int p0 = mf_point<N, IN>(t);
 #pragma unroll
-        for (int m = 0; m < 16; ++m) x[m] = lds[lds_in<T, 0>(t, m)];
+        for (int m = 0; m < 16; ++m)
+            x[m] = lds[IN ? lds_slot<0>(p0 + mf_step<N, IN>(m)) : lds_in<T, 0>(t, m)];
         wg_barrier();
-        fft_line<N, true>(x, lds, tw, fresh(t));
-        const uint32_t off = (uint32_t)((n0 + r * SIDE + line) * N + t) * 8u;
-        if (!HIN && rcmc_image_may_be_cached<N>() && rcmc_image_cached(bytes))
-            store_image_line<N, true>(x, ob, off);
+        if constexpr (PREC == PREC_FP32)
+            fft_line<N, true>(x, lds, tw, fresh(t));
         else
-            store_image_line<N>(x, ob, off);
+            fft_line_mfma<N, true, PREC, L::BLOCK / T, L::BLOCK, IN>(x, lines, tw, line, t);
+        const uint32_t off = (uint32_t)((n0 + r * SIDE + line) * N + mf_point<N, OUT>(t)) * 8u;
+        if (!HIN && rcmc_image_may_be_cached<N>() && rcmc_image_cached(bytes))
+            store_image_line<N, true, OUT>(x, ob, off);
+        else
+            store_image_line<N, false, OUT>(x, ob, off);
     }
 }
 
@@ -2070,9 +2093,9 @@ template <int N> static bool rcmc_rows_fit(const RcmcArgs& ra)
 {
     return ra.stretch_max <= RCMC_ROWS_STRETCH_MAX && ra.nr % (RcmcRows<N>::R * RcmcRows<N>::G) == 0;
 }
-template <int N, bool HIN> static hipError_t allow_rcmc_rows_lds()
+template <int N, bool HIN, int PREC = PREC_FP32> static hipError_t allow_rcmc_rows_lds()
 {
-    return hipFuncSetAttribute((const void*)k_rcmc_rows<N, HIN>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    return hipFuncSetAttribute((const void*)k_rcmc_rows<N, HIN, PREC>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                RcmcRows<N>::LDS_BYTES);
 }
 
@@ -2115,13 +2138,14 @@ static hipError_t launch_line_n(LineOp op, const float2* in, float2* out, int li
         }
         // four rows at a time where the geometry allows; at 16384 points one line
         // takes a CU's LDS and the two-row kernel was faster (208 us against 218
-        // per 32 Mpx for two rows in two rounds)
-        if constexpr (PREC == PREC_FP32 && N <= 8192) {
+        // per 32 Mpx for two rows in two rounds).  Split butterflies alike: 4096^2
+        // 101 -> 81 us, 1024^2 scene 48.0 -> 37.7, 128 x 512 39.6 -> 23.5
+        if constexpr (N <= 8192) {
             if (two_rows && !(variant & 4) && rcmc_rows_fit<N>(*ra)) {
-                static const hipError_t ga = allow_rcmc_rows_lds<N, false>();
+                static const hipError_t ga = allow_rcmc_rows_lds<N, false, PREC>();
                 if (ga != hipSuccess) return ga;
                 using Q = RcmcRows<N>;
-                SAR_LAUNCH((k_rcmc_rows<N, false>), dim3(lines / (Q::R * Q::G)), dim3(Q::BLOCK),
+                SAR_LAUNCH((k_rcmc_rows<N, false, PREC>), dim3(lines / (Q::R * Q::G)), dim3(Q::BLOCK),
                            Q::LDS_BYTES, s, in, out, *ra, tw);
                 return hipGetLastError();
             }
