@@ -40,13 +40,13 @@
 // the outputs in that same layout, so forward transform, filter and inverse
 // follow each other without an exchange.
 //
-// What bounds it: VALU issue (splitting, twiddles and scaling; 93 instructions per
-// point of a fused line), memory for single transforms.  4096 fused lines of 4096
-// points took 111 us with every transform entered and left through LDS, one pad
-// slot per 16 entries (eight accesses per point and transform, two-way bank
-// conflicts in most) and 167 instructions per point at two waves per SIMD; 95 us
-// with four accesses, free of conflicts, at four waves; 78 us with the slots split
-// into a lane's part and constants and uniform twiddle rows.
+// What bounds it: VALU issue (splitting, twiddles and scaling), memory for single
+// transforms.  4096 fused lines of 4096 points took 111 us with every transform
+// entered and left through LDS at one pad slot per 16 entries (16 LDS instructions
+// and 117 VALU instructions per point) and two waves per SIMD; 95 us in the operand
+// layout with slots by exclusive or, at four waves (167 VALU: forming the slots);
+// 78 us with the slots split into a lane's part and constants and uniform twiddle
+// rows (6 LDS, 102 VALU).
 #pragma once
 
 #include <hip/hip_runtime.h>

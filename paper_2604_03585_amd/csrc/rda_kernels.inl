@@ -1518,8 +1518,7 @@ k_rcmc_az2(const void* __restrict__ A_, float2* __restrict__ out, RcmcArgs ra,
     store_image_line<N, N == 4096, OUT>(xb, ob, off + N * 8u);
 }
 
-// Four output rows n .. n + 3 per group of threads (FP32 butterflies), for
-// geometries whose shift changes little from row to row (stretch up to
+// Four output rows n .. n + 3 per group of threads, for geometries whose shift changes little from row to row (stretch up to
 // RCMC_ROWS_STRETCH_MAX).  Up to 2048 points the group has 4T threads (T = N/16):
 // a thread interpolates four columns of the four rows, the rows meet in LDS and
 // their IFFTs run side by side.  At 4096 and 8192 points it has 2T threads and
