@@ -28,6 +28,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstdint>
+
 namespace sar {
 
 // Workgroup barrier for LDS exchanges.  The compiler models the barrier and
@@ -52,6 +54,19 @@ __device__ __forceinline__ float2 c_mul(float2 a, float2 b)
 __device__ __forceinline__ float2 c_scale(float2 a, float s) { return make_float2(a.x * s, a.y * s); }
 __device__ __forceinline__ float2 c_conj(float2 a) { return make_float2(a.x, -a.y); }
 
+// Buffer resource over `bytes` bytes (less than 4 GiB) from a wave-uniform base:
+// reads beyond its end return zero and writes there are dropped.  A buffer
+// access takes a vector offset plus a scalar one, so the 16 accesses of a line
+// share one address register instead of 16 64-bit sums.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ float2 buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
+{
+    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
+}
+
 // a * (-j) for the forward transform, a * (+j) for the inverse.
 template <bool INV>
 __device__ __forceinline__ float2 c_mul_mj(float2 a)
@@ -68,15 +83,112 @@ __device__ __forceinline__ float2 c_mul_w8(float2 a)
                : make_float2(r * (a.x + a.y), r * (a.y - a.x));
 }
 
-// ---------------------------------------------------------- butterflies
-// A thread's 16 points are transformed as radix-2 levels whose twiddles ride
-// inside the fused multiply-adds: (a, b) -> (a + w b, a - w b) takes four FMAs
-// for t = a + w b and two for 2 a - t.  A pass of radix R on inputs
-// v_i = x_i w^i is the evaluation of sum_i x_i z^i at z = w W_R^k, level by
-// level (even and odd powers), so the input twiddles cost nothing of their
-// own: 12 FMAs per point and radix-16 pass, where a radix-16 butterfly after
-// fifteen twiddle multiplies took 10.5 + 3.8 instructions, and eight distinct
-// twiddles per pass instead of fifteen.
+// a * exp(-+ j 3pi/4) = a * (-1 -+ j)/sqrt(2)
+template <bool INV>
+__device__ __forceinline__ float2 c_mul_w8_3(float2 a)
+{
+    constexpr float r = 0.70710678118654752440f;
+    return INV ? make_float2(-r * (a.x + a.y), r * (a.x - a.y))
+               : make_float2(r * (a.y - a.x), -r * (a.x + a.y));
+}
+
+// a * (c, -+ s)
+template <bool INV>
+__device__ __forceinline__ float2 c_mul_cs(float2 a, float c, float s)
+{
+    return c_mul(a, make_float2(c, INV ? s : -s));
+}
+
+// ---------------------------------------------------------- small DFTs
+// All take natural-order input in v[] and leave natural-order output.
+template <bool INV>
+__device__ __forceinline__ void dft2(float2& a, float2& b)
+{
+    float2 t = a;
+    a = c_add(t, b);
+    b = c_sub(t, b);
+}
+
+template <bool INV>
+__device__ __forceinline__ void dft4(float2& a0, float2& a1, float2& a2, float2& a3)
+{
+    float2 s0 = c_add(a0, a2), d0 = c_sub(a0, a2);
+    float2 s1 = c_add(a1, a3), d1 = c_mul_mj<INV>(c_sub(a1, a3));
+    a0 = c_add(s0, s1);
+    a2 = c_sub(s0, s1);
+    a1 = c_add(d0, d1);
+    a3 = c_sub(d0, d1);
+}
+
+template <int R, bool INV> struct Dft;
+
+template <bool INV> struct Dft<2, INV> {
+    __device__ __forceinline__ static void run(float2* v) { dft2<INV>(v[0], v[1]); }
+};
+
+template <bool INV> struct Dft<4, INV> {
+    __device__ __forceinline__ static void run(float2* v) { dft4<INV>(v[0], v[1], v[2], v[3]); }
+};
+
+// DFT8 = DFT2 (stride 4) x twiddle W8^{n2 k1} x DFT4.
+template <bool INV> struct Dft<8, INV> {
+    __device__ __forceinline__ static void run(float2* v)
+    {
+        dft2<INV>(v[0], v[4]);
+        dft2<INV>(v[1], v[5]);
+        dft2<INV>(v[2], v[6]);
+        dft2<INV>(v[3], v[7]);
+        v[5] = c_mul_w8<INV>(v[5]);
+        v[6] = c_mul_mj<INV>(v[6]);
+        v[7] = c_mul_w8_3<INV>(v[7]);
+        // y[n2][k1] sits in v[n2 + 4 k1]; DFT4 over n2 gives X[k1 + 2 k2]
+        float2 a0 = v[0], a1 = v[1], a2 = v[2], a3 = v[3];
+        float2 b0 = v[4], b1 = v[5], b2 = v[6], b3 = v[7];
+        dft4<INV>(a0, a1, a2, a3);
+        dft4<INV>(b0, b1, b2, b3);
+        v[0] = a0; v[2] = a1; v[4] = a2; v[6] = a3;
+        v[1] = b0; v[3] = b1; v[5] = b2; v[7] = b3;
+    }
+};
+
+// DFT16 = DFT4 (stride 4) x twiddle W16^{n2 k1} x DFT4.
+template <bool INV> struct Dft<16, INV> {
+    __device__ __forceinline__ static void run(float2* v)
+    {
+        constexpr float c1 = 0.92387953251128675613f;   // cos(pi/8)
+        constexpr float s1 = 0.38268343236508977173f;   // sin(pi/8)
+#pragma unroll
+        for (int n2 = 0; n2 < 4; ++n2) dft4<INV>(v[n2], v[n2 + 4], v[n2 + 8], v[n2 + 12]);
+        // y[n2][k1] is in v[n2 + 4 k1]
+        v[5] = c_mul_cs<INV>(v[5], c1, s1);     // n2=1 k1=1: W16^1
+        v[9] = c_mul_w8<INV>(v[9]);             // n2=1 k1=2: W16^2
+        v[13] = c_mul_cs<INV>(v[13], s1, c1);   // n2=1 k1=3: W16^3
+        v[6] = c_mul_w8<INV>(v[6]);             // n2=2 k1=1: W16^2
+        v[10] = c_mul_mj<INV>(v[10]);           // n2=2 k1=2: W16^4
+        v[14] = c_mul_w8_3<INV>(v[14]);         // n2=2 k1=3: W16^6
+        v[7] = c_mul_cs<INV>(v[7], s1, c1);     // n2=3 k1=1: W16^3
+        v[11] = c_mul_w8_3<INV>(v[11]);         // n2=3 k1=2: W16^6
+        v[15] = c_mul_cs<INV>(v[15], -c1, -s1); // n2=3 k1=3: W16^9 = (-c1, +s1)
+        float2 o[16];
+#pragma unroll
+        for (int k1 = 0; k1 < 4; ++k1) {
+            float2 a0 = v[4 * k1], a1 = v[4 * k1 + 1], a2 = v[4 * k1 + 2], a3 = v[4 * k1 + 3];
+            dft4<INV>(a0, a1, a2, a3);
+            o[k1] = a0; o[k1 + 4] = a1; o[k1 + 8] = a2; o[k1 + 12] = a3;
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = o[i];
+    }
+};
+
+// ------------------------------------------------------ FMA butterflies
+// Radix-2 levels whose twiddles ride inside the fused multiply-adds: (a, b) ->
+// (a + w b, a - w b) takes four FMAs for t = a + w b and two for 2 a - t.  A pass
+// of radix R on inputs v_i = x_i w^i is the evaluation of sum_i x_i z^i at
+// z = w W_R^k, level by level (even and odd powers), so the input twiddles cost
+// nothing of their own: 12 FMAs per point and radix-16 pass, where a radix-16
+// butterfly after fifteen twiddle multiplies takes 10.5 + 3.8 instructions and
+// 3.3 more to form the twiddles from two table reads.
 template <bool INV>
 __device__ __forceinline__ void bfly(float2& a, float2& b, float2 w)
 {
@@ -107,31 +219,6 @@ __device__ __forceinline__ void bfly_mj(float2& a, float2& b, float2 w)
     u.y = fmaf(2.0f, a.y, -t.y);
     a = t;
     b = u;
-}
-
-// Butterfly with the constant twiddle W16^M (M = 0..7): additions only for
-// M = 0 and 4, one rotation by 45 degrees for M = 2 and 6.
-template <bool INV, int M>
-__device__ __forceinline__ void bfly_c(float2& a, float2& b)
-{
-    constexpr float c1 = 0.92387953251128675613f;   // cos(pi/8)
-    constexpr float s1 = 0.38268343236508977173f;   // sin(pi/8)
-    constexpr float r2 = 0.70710678118654752440f;
-    if constexpr (M == 0 || M == 4) {
-        const float2 t = M == 0 ? b : c_mul_mj<INV>(b);
-        b = c_sub(a, t);
-        a = c_add(a, t);
-    } else if constexpr (M == 2 || M == 6) {
-        // W8 b = r2 (x + y, y - x) forward, r2 (x - y, y + x) inverse
-        float2 t = INV ? make_float2(b.x - b.y, b.y + b.x) : make_float2(b.x + b.y, b.y - b.x);
-        if (M == 6) t = c_mul_mj<INV>(t);
-        b = make_float2(fmaf(-r2, t.x, a.x), fmaf(-r2, t.y, a.y));
-        a = make_float2(fmaf(r2, t.x, a.x), fmaf(r2, t.y, a.y));
-    } else if constexpr (M == 1 || M == 3) {
-        bfly<INV>(a, b, M == 1 ? make_float2(c1, -s1) : make_float2(s1, -c1));
-    } else {
-        bfly_mj<INV>(a, b, M == 5 ? make_float2(c1, -s1) : make_float2(s1, -c1));
-    }
 }
 
 // ------------------------------------------------------------ pass plan
@@ -191,10 +278,126 @@ template <int NS, int P> __device__ __forceinline__ int lds_out(int base, int i)
     return lds_slot<P>(base) + i * NS + lds_pads<P>() * (i * NS / 32);
 }
 
-// The twiddles of one thread in one pass.  The thread's 16 / R butterflies of
-// a radix-R pass (q = 0 .. 16/R - 1, j = t + q T) and their levels need
-// w^e W16^(e r), e a power of two below R, r < 8 / e; with -j factored out
-// (r >= 4 / e) eight values remain: w W16^r, w^2 W8^r, w^4, w^8, where w is
+// ------------------------------------------------------------- twiddles
+// Where a pass's twiddles enter, chosen so that no transform is further from its
+// value in 64 bits than with twiddles ahead of every butterfly and the powers of
+// radix-16 passes as products of two table entries (tw_first).  Relative L2 of
+// Gaussian noise, 1e-7, here (there): 64 points 0.80 (0.81), 256 1.12 (1.15), 512
+// 1.18 (1.21), 1024 1.23 (1.26), 2048 1.29 (1.32), 4096 1.46 (1.53), 8192 1.52
+// (1.58), 16384 1.57 (1.62).
+//   NONE  pass 0 has none; its butterflies are plain DFTs (the FMA butterflies'
+//         u = 2a - t carries t's rounding: 0.82 at 64 points);
+//   FMA   radix-16 passes: inside the butterflies, w, w^2, w^4 and w^8 read from
+//         the table (with w^2 and w^8 as squares 4096 points have 1.61, with one
+//         of them 1.55 and 1.53);
+//   PRE   trailing passes of up to 4096 points: every twiddle from the table,
+//         ahead of the butterfly (ROT there: 1.26 at 1024 points, 1.33 at 2048);
+//   ROT   those of longer lines: inside the butterflies, butterfly q's w W16^q
+//         from the table too (as products 1.66 at 16384 points; PRE's twelve
+//         twiddles would spill in the persistent kernel).
+// Against squares and products in every pass (0.99 at 64 points, 1.46 at 1024, 1.62
+// at 4096) this costs two reads more per radix-16 pass and up to thirteen in a
+// trailing one: 3001 lines of 1024 points 9.6 -> 10.0 us, 1024 x 2048 azimuth step
+// 19.9 -> 20.6, 4096 x 4096 hyperbolic scene 180.7 -> 182.3.
+enum PassForm { PASS_NONE, PASS_FMA, PASS_PRE, PASS_ROT };
+template <int N, int P> __host__ __device__ constexpr PassForm pass_form()
+{
+    if (P >= LineGeom<N>::NP || LineGeom<N>::span(P) == 1) return PASS_NONE;
+    if (LineGeom<N>::radix(P) == 16) return PASS_FMA;
+    return N <= 4096 ? PASS_PRE : PASS_ROT;
+}
+
+// Twiddles ahead of the butterflies of pass P: for butterfly q (j = t + q*T) and
+// i = 1..R-1, exp(-2 pi i * (j mod Ns) * i / (Ns * R)), read from this N's
+// table (entry tw_off(P) + (i-1)*Ns + (j mod Ns)); passes with Ns == 1 need
+// none.
+template <int N, int P> struct PassTw {
+    using G = LineGeom<N>;
+    static constexpr bool ANY = P < G::NP && G::span(P) > 1;
+    static constexpr int PER = ANY ? G::radix(P) - 1 : 0;      // per butterfly
+    static constexpr int COUNT = ANY ? line_e(N) / G::radix(P) * PER : 1;
+    float2 w[COUNT];
+};
+
+// Entry jm + k (k a constant) of pass P's part of the table.
+template <int N, int P>
+__device__ __forceinline__ float2 tw_ld(const float2* __restrict__ tw, int jm, int k)
+{
+    constexpr int OFF = LineGeom<N>::tw_off(P);
+    return buf_ld(buf_rsrc(tw, LineGeom<N>::TW_SIZE * 8u), (uint32_t)jm * 8u, (uint32_t)(OFF + k) * 8u);
+}
+
+// The twiddles of butterfly q.
+template <int N, int P>
+__device__ __forceinline__ void read_tw(PassTw<N, P>& pt, const float2* __restrict__ tw, int t, int q)
+{
+    using G = LineGeom<N>;
+    constexpr int R = G::radix(P), NS = G::span(P), PER = PassTw<N, P>::PER;
+    // radix 16: one butterfly, one of NS twiddle sets; trailing passes: j = t + q T < NS
+    const int jm = R == 16 ? t & (NS - 1) : t, at = R == 16 ? 0 : q * G::T;
+#pragma unroll
+    for (int i = 0; i < PER; ++i) pt.w[q * PER + i] = tw_ld<N, P>(tw, jm, at + i * NS);
+}
+
+template <int N, int P>
+__device__ __forceinline__ void read_tw(PassTw<N, P>& pt, const float2* __restrict__ tw, int t)
+{
+    if constexpr (PassTw<N, P>::ANY) {
+#pragma unroll
+        for (int q = 0; q < 16 / LineGeom<N>::radix(P); ++q) read_tw<N, P>(pt, tw, t, q);
+    }
+}
+
+// Butterfly q of pass P with its twiddles (if any) ahead of it.
+template <int N, int P, bool INV>
+__device__ __forceinline__ void tw_butterfly(float2 (&x)[16], const PassTw<N, P>& pt, int q)
+{
+    constexpr int R = LineGeom<N>::radix(P), B = 16 / R;
+    float2 v[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) v[i] = x[q + i * B];
+    if constexpr (PassTw<N, P>::ANY) {
+#pragma unroll
+        for (int i = 1; i < R; ++i) {
+            float2 w = pt.w[q * (R - 1) + i - 1];
+            if (INV) w.y = -w.y;
+            v[i] = c_mul(v[i], w);
+        }
+    }
+    Dft<R, INV>::run(v);
+#pragma unroll
+    for (int i = 0; i < R; ++i) x[q + i * B] = v[i];
+}
+
+template <int N, int P, bool INV>
+__device__ __forceinline__ void tw_butterflies(float2 (&x)[16], const PassTw<N, P>& pt)
+{
+#pragma unroll
+    for (int q = 0; q < 16 / LineGeom<N>::radix(P); ++q) tw_butterfly<N, P, INV>(x, pt, q);
+}
+
+// The same in little room: the butterflies take turns, six to eight twiddles read
+// at a time (all of them together would spill in the strips' 64 registers, one
+// butterfly at a time waits too often: batch of 24 scenes 33.8 us against 34.6).
+template <int N, int P, bool INV>
+__device__ __forceinline__ void tw_butterflies_in_turn(float2 (&x)[16], const float2* __restrict__ tw, int t)
+{
+    constexpr int R = LineGeom<N>::radix(P), TURN = R == 2 ? 8 : (R == 4 ? 2 : 1);
+    PassTw<N, P> pt;
+#pragma unroll
+    for (int q = 0; q < 16 / R; q += TURN) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < TURN; ++i) read_tw<N, P>(pt, tw, t, q + i);
+#pragma unroll
+        for (int i = 0; i < TURN; ++i) tw_butterfly<N, P, INV>(x, pt, q + i);
+    }
+}
+
+// The twiddles of one thread inside the butterflies of one pass.  The thread's
+// 16 / R butterflies of a radix-R pass (q = 0 .. 16/R - 1, j = t + q T) and their
+// levels need w^e W16^(e r), e a power of two below R, r < 8 / e; with -j factored
+// out (r >= 4 / e) eight values remain: w W16^r, w^2 W8^r, w^4, w^8, where w is
 // the twiddle of butterfly q = 0 (in a trailing pass the span is N / R, so
 // butterfly q's is w W16^q).
 struct TwSet {
@@ -203,68 +406,71 @@ struct TwSet {
     float2 w4, w8;
 };
 
-__device__ __forceinline__ float2 c_sqr(float2 a)
-{
-    return make_float2(fmaf(a.x, a.x, -a.y * a.y), 2.0f * a.x * a.y);
-}
-
-// The constant multiples of w and w^2 (set r[0], s[0] first).
-template <int R>
-__device__ __forceinline__ void tw_rotate(TwSet& p)
-{
-    constexpr float c1 = 0.92387953251128675613f;
-    constexpr float s1 = 0.38268343236508977173f;
-    const float2 w = p.r[0];
-    p.r[1] = c_mul(w, make_float2(c1, -s1));
-    p.r[2] = c_mul_w8<false>(w);
-    p.r[3] = c_mul(w, make_float2(s1, -c1));
-    if constexpr (R >= 4) p.s[1] = c_mul_w8<false>(p.s[0]);
-}
-
-// Twiddle table reads of pass P of virtual thread t (one of N / 16): w, and
-// for radix 8 and 16 w^4 (TWP: the other powers are squares of these two) or
-// w^2, w^4 and w^8 as well (!TWP: table reads instead of squares).  Row i - 1
+// Twiddle table reads of pass P of virtual thread t (one of N / 16); row i - 1
 // of the pass's table holds w^i.
-template <int N, int P, bool TWP> struct TwReads {
-    using G = LineGeom<N>;
-    static constexpr bool ANY = P < G::NP && G::span(P) > 1;
-    static constexpr int R = ANY ? G::radix(P) : 1;
-    float2 w1, w2, w4, w8;
+//   FMA: w, w^2, w^4, w^8;  ROT: w W16^q (q < 4), for radix 4 also w^2 W8^q
+//   (q < 2), the others being -j times these;  PRE: see PassTw.
+template <int N, int P, PassForm F = pass_form<N, P>()> struct TwReads {
+    static constexpr int COUNT = F == PASS_FMA ? 4 : F == PASS_ROT ? (LineGeom<N>::radix(P) == 2 ? 4 : 6) : 0;
+    float2 w[COUNT ? COUNT : 1];
 };
+template <int N, int P> struct TwReads<N, P, PASS_PRE> : PassTw<N, P> {};
 
-template <int N, int P, bool TWP>
-__device__ __forceinline__ void tw_issue(TwReads<N, P, TWP>& a, const float2* __restrict__ tw, int t)
+template <int N, int P>
+__device__ __forceinline__ void tw_issue(TwReads<N, P>& a, const float2* __restrict__ tw, int t)
 {
-    using Rd = TwReads<N, P, TWP>;
-    if constexpr (Rd::ANY) {
-        using G = LineGeom<N>;
-        constexpr int NS = G::span(P), OFF = G::tw_off(P), R = Rd::R;
+    using G = LineGeom<N>;
+    constexpr PassForm F = pass_form<N, P>();
+    if constexpr (F == PASS_FMA) {
+        constexpr int NS = G::span(P);
         const int jm = t & (NS - 1);
-        a.w1 = tw[OFF + jm];
-        if constexpr (R >= 8) a.w4 = tw[OFF + 3 * NS + jm];
-        if constexpr (!TWP && R >= 4) a.w2 = tw[OFF + NS + jm];
-        if constexpr (!TWP && R >= 16) a.w8 = tw[OFF + 7 * NS + jm];
+        a.w[0] = tw_ld<N, P>(tw, jm, 0);
+        a.w[1] = tw_ld<N, P>(tw, jm, NS);
+        a.w[2] = tw_ld<N, P>(tw, jm, 3 * NS);
+        a.w[3] = tw_ld<N, P>(tw, jm, 7 * NS);
+    } else if constexpr (F == PASS_ROT) {
+        constexpr int NS = G::span(P);
+        static_assert(G::radix(P) <= 4 && 4 * G::T <= NS, "w W16^q lie in the first row");
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a.w[q] = tw_ld<N, P>(tw, t, q * G::T);
+        if constexpr (G::radix(P) == 4) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) a.w[4 + q] = tw_ld<N, P>(tw, t, NS + q * G::T);
+        }
+    } else if constexpr (F == PASS_PRE) {
+        read_tw<N, P>(a, tw, t);
     }
 }
 
-template <int N, int P, bool TWP>
-__device__ __forceinline__ void tw_form(TwSet& p, const TwReads<N, P, TWP>& a)
+template <int N, int P>
+__device__ __forceinline__ void tw_form(TwSet& p, const TwReads<N, P>& a)
 {
-    using Rd = TwReads<N, P, TWP>;
-    if constexpr (Rd::ANY) {
-        constexpr int R = Rd::R;
-        p.r[0] = a.w1;
-        if constexpr (R >= 4) p.s[0] = TWP ? c_sqr(a.w1) : a.w2;
-        if constexpr (R >= 8) p.w4 = a.w4;
-        if constexpr (R >= 16) p.w8 = TWP ? c_sqr(a.w4) : a.w8;
-        tw_rotate<R>(p);
+    if constexpr (pass_form<N, P>() == PASS_FMA) {
+        constexpr float c1 = 0.92387953251128675613f;
+        constexpr float s1 = 0.38268343236508977173f;
+        const float2 w = a.w[0];
+        p.r[0] = w;
+        p.r[1] = c_mul(w, make_float2(c1, -s1));
+        p.r[2] = c_mul_w8<false>(w);
+        p.r[3] = c_mul(w, make_float2(s1, -c1));
+        p.s[0] = a.w[1];
+        p.s[1] = c_mul_w8<false>(a.w[1]);
+        p.w4 = a.w[2];
+        p.w8 = a.w[3];
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) p.r[q] = a.w[q];
+        if constexpr (LineGeom<N>::radix(P) == 4) {
+            p.s[0] = a.w[4];
+            p.s[1] = a.w[5];
+        }
     }
 }
 
 // Level E (inputs E apart within a butterfly) of a thread's 16 / R butterflies
 // of radix R: point i of butterfly q, partial output k, sits at
 // q + (16 / R) (i + 2 E k) before and q + (16 / R) (i + E k) after.
-template <int R, int E, bool INV, bool TW>
+template <int R, int E, bool INV>
 __device__ __forceinline__ void fft_level(float2 (&v)[16], const TwSet& p)
 {
     constexpr int B = 16 / R, K = R / (2 * E);
@@ -275,25 +481,12 @@ __device__ __forceinline__ void fft_level(float2 (&v)[16], const TwSet& p)
         for (int k = 0; k < K; ++k) {
             constexpr int J = 4 / E > 0 ? 4 / E : 1;      // r >= J carries the factor -j
             const int r = q + k * B;
+            const float2 w = E == 8 ? p.w8 : E == 4 ? p.w4 : E == 2 ? p.s[r & 1] : p.r[r & 3];
 #pragma unroll
             for (int i = 0; i < E; ++i) {
                 float2 a = v[q + B * (i + 2 * E * k)], b = v[q + B * (i + E + 2 * E * k)];
-                if constexpr (TW) {
-                    const float2 w = E == 8 ? p.w8 : E == 4 ? p.w4 : E == 2 ? p.s[r & 1] : p.r[r & 3];
-                    if (E < 8 && r >= J) bfly_mj<INV>(a, b, w);
-                    else bfly<INV>(a, b, w);
-                } else {
-                    switch (E * r) {
-                    case 0: bfly_c<INV, 0>(a, b); break;
-                    case 1: bfly_c<INV, 1>(a, b); break;
-                    case 2: bfly_c<INV, 2>(a, b); break;
-                    case 3: bfly_c<INV, 3>(a, b); break;
-                    case 4: bfly_c<INV, 4>(a, b); break;
-                    case 5: bfly_c<INV, 5>(a, b); break;
-                    case 6: bfly_c<INV, 6>(a, b); break;
-                    default: bfly_c<INV, 7>(a, b); break;
-                    }
-                }
+                if (E < 8 && r >= J) bfly_mj<INV>(a, b, w);
+                else bfly<INV>(a, b, w);
                 o[q + B * (i + E * k)] = a;
                 o[q + B * (i + E * (k + K))] = b;
             }
@@ -304,55 +497,66 @@ __device__ __forceinline__ void fft_level(float2 (&v)[16], const TwSet& p)
 
 // All butterflies of pass P of one virtual thread, in registers.
 template <int N, int P, bool INV>
-__device__ __forceinline__ void pass_butterflies(float2 (&x)[16], const TwSet& p)
+__device__ __forceinline__ void pass_butterflies(float2 (&x)[16], const TwReads<N, P>& a)
+{
+    constexpr PassForm F = pass_form<N, P>();
+    if constexpr (F == PASS_NONE) {
+        Dft<16, INV>::run(x);
+    } else if constexpr (F == PASS_PRE) {
+        tw_butterflies<N, P, INV>(x, a);
+    } else {
+        constexpr int R = LineGeom<N>::radix(P);
+        TwSet p;
+        tw_form<N, P>(p, a);
+        if constexpr (R >= 16) fft_level<R, 8, INV>(x, p);
+        if constexpr (R >= 16) fft_level<R, 4, INV>(x, p);
+        if constexpr (R >= 4) fft_level<R, 2, INV>(x, p);
+        fft_level<R, 1, INV>(x, p);
+    }
+}
+
+// The LDS exchange after radix-16 pass P: outputs of the butterflies to the
+// strided layout.
+// SPLIT: real and imaginary parts in two float arrays of the line's LDS
+// (re[0, LDS), im[LDS, 2 LDS)), two 4-byte accesses per point instead of one
+// 8-byte access, so that the two layouts can be compared.
+template <int N, int P, bool SPLIT>
+__device__ __forceinline__ void line_exchange(float2 (&x)[16], float2* __restrict__ lds, int t)
 {
     using G = LineGeom<N>;
-    constexpr int R = G::radix(P);
-    constexpr bool TW = G::span(P) > 1;
-    if constexpr (R >= 16) fft_level<R, 8, INV, TW>(x, p);
-    if constexpr (R >= 8) fft_level<R, 4, INV, TW>(x, p);
-    if constexpr (R >= 4) fft_level<R, 2, INV, TW>(x, p);
-    fft_level<R, 1, INV, TW>(x, p);
+    static_assert(G::radix(P) == 16, "only the last pass is smaller than radix 16");
+    constexpr int NS = G::span(P);
+    const int base = (t / NS) * NS * 16 + (t & (NS - 1));
+    if constexpr (SPLIT) {
+        float* re = (float*)lds;
+        float* im = re + G::LDS;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            re[lds_out<NS, P>(base, i)] = x[i].x;
+            im[lds_out<NS, P>(base, i)] = x[i].y;
+        }
+        wg_barrier();
+#pragma unroll
+        for (int m = 0; m < 16; ++m)
+            x[m] = make_float2(re[lds_in<G::T, P>(t, m)], im[lds_in<G::T, P>(t, m)]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) lds[lds_out<NS, P>(base, i)] = x[i];
+        wg_barrier();
+#pragma unroll
+        for (int m = 0; m < 16; ++m) x[m] = lds[lds_in<G::T, P>(t, m)];
+    }
+    wg_barrier();
 }
 
 // One Stockham pass P of an N-point line (see the header comment), with its
-// twiddles already formed.
-// SPLIT: the exchange keeps real and imaginary parts in two float arrays of
-// the line's LDS (re[0, LDS), im[LDS, 2 LDS)), two 4-byte accesses per point
-// instead of one 8-byte access, so that the two layouts can be compared.
+// twiddles already read.
 template <int N, int P, bool INV, bool SPLIT = false>
 __device__ __forceinline__ void fft_pass(float2 (&x)[16], float2* __restrict__ lds,
-                                         const TwSet& p, int t)
+                                         const TwReads<N, P>& a, int t)
 {
-    using G = LineGeom<N>;
-    constexpr int R = G::radix(P);
-    constexpr int NS = G::span(P);
-    constexpr int B = 16 / R;
-    pass_butterflies<N, P, INV>(x, p);
-    if constexpr (P < G::NP - 1) {
-        static_assert(B == 1, "only the last pass is smaller than radix 16");
-        const int base = (t / NS) * NS * R + (t & (NS - 1));
-        if constexpr (SPLIT) {
-            float* re = (float*)lds;
-            float* im = re + G::LDS;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                re[lds_out<NS, P>(base, i)] = x[i].x;
-                im[lds_out<NS, P>(base, i)] = x[i].y;
-            }
-            wg_barrier();
-#pragma unroll
-            for (int m = 0; m < 16; ++m)
-                x[m] = make_float2(re[lds_in<G::T, P>(t, m)], im[lds_in<G::T, P>(t, m)]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 16; ++i) lds[lds_out<NS, P>(base, i)] = x[i];
-            wg_barrier();
-#pragma unroll
-            for (int m = 0; m < 16; ++m) x[m] = lds[lds_in<G::T, P>(t, m)];
-        }
-        wg_barrier();
-    }
+    pass_butterflies<N, P, INV>(x, a);
+    if constexpr (P < LineGeom<N>::NP - 1) line_exchange<N, P, SPLIT>(x, lds, t);
 }
 
 // Passes P.. of the line.  `before_last` runs just before the last pass
@@ -369,49 +573,48 @@ struct NoOp {
 // FRESH: bit P set = pass P's twiddles are read and formed anew even where an
 // earlier transform of the same thread has them (its index is hidden from the
 // compiler); a bit left clear lets the compiler keep them in registers.
-template <int N, bool INV, bool TWP, int P, bool SPLIT, bool AHEAD, int FRESH, class F>
+template <int N, bool INV, int P, bool SPLIT, bool AHEAD, int FRESH, class F>
 __device__ __forceinline__ void fft_from(float2 (&x)[16], float2* __restrict__ lds,
                                          const float2* __restrict__ tw, int t, F&& before_last,
-                                         const TwReads<N, P, TWP>& ahead)
+                                         const TwReads<N, P>& ahead)
 {
     if constexpr (P < LineGeom<N>::NP) {
-        if constexpr (P == LineGeom<N>::NP - 1) before_last();
-        TwSet cur;
-        TwReads<N, P + 1, TWP> next;
+        TwReads<N, P + 1> next;
         int ti = t;
         constexpr int READ = AHEAD ? P + 1 : P;           // the pass whose reads are issued here
         if constexpr ((FRESH >> READ) & 1) asm volatile("" : "+v"(ti));
         if constexpr (AHEAD) {
-            tw_form<N, P, TWP>(cur, ahead);
-            tw_issue<N, P + 1, TWP>(next, tw, ti);
+            if constexpr (P == LineGeom<N>::NP - 1) before_last();
+            tw_issue<N, P + 1>(next, tw, ti);
+            fft_pass<N, P, INV, SPLIT>(x, lds, ahead, t);
         } else {
-            TwReads<N, P, TWP> now;
-            tw_issue<N, P, TWP>(now, tw, ti);
-            tw_form<N, P, TWP>(cur, now);
+            TwReads<N, P> now;
+            tw_issue<N, P>(now, tw, ti);
+            // after the reads that the pass waits for, so that it need not wait for these
+            if constexpr (P == LineGeom<N>::NP - 1) before_last();
+            fft_pass<N, P, INV, SPLIT>(x, lds, now, t);
         }
-        fft_pass<N, P, INV, SPLIT>(x, lds, cur, t);
-        fft_from<N, INV, TWP, P + 1, SPLIT, AHEAD, FRESH>(x, lds, tw, t, before_last, next);
+        fft_from<N, INV, P + 1, SPLIT, AHEAD, FRESH>(x, lds, tw, t, before_last, next);
     }
 }
 
-// TWP selects twiddles by products (fewer loads, more VALU) or table reads;
-// SPLIT the split real/imaginary exchange layout (see fft_pass).
-template <int N, bool INV, bool TWP = true, bool SPLIT = false, int FRESH = 0, class F = NoOp>
+// SPLIT: the split real/imaginary exchange layout (see line_exchange).
+template <int N, bool INV, bool SPLIT = false, int FRESH = 0, class F = NoOp>
 __device__ __forceinline__ void fft_line(float2 (&x)[line_e(N)], float2* __restrict__ lds,
                                          const float2* __restrict__ tw, int t, F&& before_last = F())
 {
-    TwReads<N, 0, TWP> first;
-    fft_from<N, INV, TWP, 0, SPLIT, false, FRESH>(x, lds, tw, t, before_last, first);
+    TwReads<N, 0> first;
+    fft_from<N, INV, 0, SPLIT, false, FRESH>(x, lds, tw, t, before_last, first);
 }
 
 // The same transform with every pass's table reads issued one pass ahead.
-template <int N, bool INV, bool TWP = true, bool SPLIT = false, int FRESH = 0, class F = NoOp>
+template <int N, bool INV, bool SPLIT = false, int FRESH = 0, class F = NoOp>
 __device__ __forceinline__ void fft_line_ahead(float2 (&x)[line_e(N)], float2* __restrict__ lds,
                                                const float2* __restrict__ tw, int t,
                                                F&& before_last = F())
 {
-    TwReads<N, 0, TWP> first;
-    fft_from<N, INV, TWP, 0, SPLIT, true, FRESH>(x, lds, tw, t, before_last, first);
+    TwReads<N, 0> first;
+    fft_from<N, INV, 0, SPLIT, true, FRESH>(x, lds, tw, t, before_last, first);
 }
 
 // The value is in its registers here: a pending load has been waited for, and
@@ -439,25 +642,23 @@ __device__ __forceinline__ int fresh(int t)
     return t;
 }
 
-// The twiddle reads of every pass (at most five values), held in registers by a
-// thread that transforms line after line: the transforms between then read
+// The twiddle reads of every pass (at most fourteen values), held in registers by
+// a thread that transforms line after line: the transforms between then read
 // nothing from memory, so no wait of theirs covers loads of the next line.
 template <int N> struct TwAll {
-    TwReads<N, 1, true> p1;
-    TwReads<N, 2, true> p2;
-    TwReads<N, 3, true> p3;
+    TwReads<N, 1> p1;
+    TwReads<N, 2> p2;
+    TwReads<N, 3> p3;
     __device__ __forceinline__ void read(const float2* __restrict__ tw, int t)
     {
-        tw_issue<N, 1, true>(p1, tw, t);
-        tw_issue<N, 2, true>(p2, tw, t);
-        tw_issue<N, 3, true>(p3, tw, t);
+        tw_issue<N, 1>(p1, tw, t);
+        tw_issue<N, 2>(p2, tw, t);
+        tw_issue<N, 3>(p3, tw, t);
     }
-    template <int P> static __device__ __forceinline__ void pin_pass(TwReads<N, P, true>& r)
+    template <int P> static __device__ __forceinline__ void pin_pass(TwReads<N, P>& r)
     {
-        if constexpr (TwReads<N, P, true>::ANY) {
-            pin(r.w1);
-            if constexpr (TwReads<N, P, true>::R >= 8) pin(r.w4);
-        }
+#pragma unroll
+        for (int i = 0; i < TwReads<N, P>::COUNT; ++i) pin(r.w[i]);
     }
     __device__ __forceinline__ void hold()
     {
@@ -475,11 +676,10 @@ __device__ __forceinline__ void fft_held_from(float2 (&x)[16], float2* __restric
         // ahead of the last radix-16 pass (its butterflies and exchange cover
         // the latency of the loads; a trailing smaller pass is too short)
         if constexpr (P == LineGeom<N>::NFULL - 1) before_last();
-        TwSet cur;
-        if constexpr (P == 1) tw_form<N, 1, true>(cur, tw.p1);
-        if constexpr (P == 2) tw_form<N, 2, true>(cur, tw.p2);
-        if constexpr (P == 3) tw_form<N, 3, true>(cur, tw.p3);
-        fft_pass<N, P, INV>(x, lds, cur, t);
+        if constexpr (P == 0) fft_pass<N, 0, INV>(x, lds, TwReads<N, 0>(), t);
+        if constexpr (P == 1) fft_pass<N, 1, INV>(x, lds, tw.p1, t);
+        if constexpr (P == 2) fft_pass<N, 2, INV>(x, lds, tw.p2, t);
+        if constexpr (P == 3) fft_pass<N, 3, INV>(x, lds, tw.p3, t);
         fft_held_from<N, INV, P + 1>(x, lds, tw, t, before_last);
     }
 }
@@ -545,11 +745,13 @@ __device__ __forceinline__ void fft_half_from(float2 (&x)[16], float* __restrict
                                               const float2* __restrict__ tw, int t)
 {
     if constexpr (P < LineGeom<N>::NP) {
-        TwReads<N, P, true> now;
-        tw_issue<N, P, true>(now, tw, fresh(t));
-        TwSet cur;
-        tw_form<N, P, true>(cur, now);
-        pass_butterflies<N, P, INV>(x, cur);
+        if constexpr (pass_form<N, P>() == PASS_PRE) {
+            tw_butterflies_in_turn<N, P, INV>(x, tw, fresh(t));
+        } else {
+            TwReads<N, P> now;
+            tw_issue<N, P>(now, tw, fresh(t));
+            pass_butterflies<N, P, INV>(x, now);
+        }
         if constexpr (P < LineGeom<N>::NP - 1) half_exchange<N, P>(x, lds, t);
         fft_half_from<N, INV, P + 1>(x, lds, tw, t);
     }

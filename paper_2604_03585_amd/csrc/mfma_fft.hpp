@@ -52,7 +52,6 @@
 #include <hip/hip_runtime.h>
 
 #include "fft_line.hpp"
-#include "fft_line_tw.hpp"
 
 namespace sar {
 
@@ -401,22 +400,11 @@ __device__ __forceinline__ void fft_line_mfma(float2 (&x)[16], float2* __restric
     }
     if constexpr (!OUT_MF) wg_barrier();          // LDS free for the caller's next use
     if constexpr (G::NP > NMF) {
-        // trailing radix-2/4/8 pass in FP32
-        if constexpr (PREC == PREC_BF16) {
-            // in the form whose last bits callers have: what follows splits its
-            // operands to 16 significand bits, where a change of the last FP32 bit
-            // moves some values by 2^-17 and the passes after it spread that (8192 x
-            // 8192 LFM image: 4e-6 relative L2, 8.2e-4 of the rms at one sample)
-            tw_first::PassTw<N, G::NP - 1> pt;
-            tw_first::load_tw<N, G::NP - 1>(pt, tw, t);
-            tw_first::fft_pass<N, G::NP - 1, INV>(x, (float2*)nullptr, pt, t);
-        } else {
-            TwReads<N, G::NP - 1, false> rd;
-            TwSet pt;
-            tw_issue<N, G::NP - 1, false>(rd, tw, t);
-            tw_form<N, G::NP - 1, false>(pt, rd);
-            fft_pass<N, G::NP - 1, INV>(x, (float2*)nullptr, pt, t);
-        }
+        // trailing radix-2/4/8 pass in FP32, its twiddles from the table and
+        // ahead of the butterflies (see PassForm)
+        PassTw<N, G::NP - 1> pt;
+        read_tw<N, G::NP - 1>(pt, tw, t);
+        tw_butterflies<N, G::NP - 1, INV>(x, pt);
     }
 }
 

@@ -166,10 +166,13 @@ __device__ __forceinline__ void fft_any(float2 (&x)[line_e(N)], float2* __restri
                                         const float2* __restrict__ tw, int sub, int t,
                                         F&& before_last = F())
 {
-    if constexpr (PREC == PREC_FP32 && AHEAD) {
-        fft_line_ahead<N, INV, TWP, SPLIT, FRESH>(x, lds, tw, t, before_last);
+    if constexpr (PREC == PREC_FP32 && !TWP) {
+        if constexpr (FRESH != 0) t = fresh(t);   // the forward passes' would spill
+        tw_first::fft_line<N, INV, true, SPLIT>(x, lds, tw, t, before_last);
+    } else if constexpr (PREC == PREC_FP32 && AHEAD) {
+        fft_line_ahead<N, INV, SPLIT, FRESH>(x, lds, tw, t, before_last);
     } else if constexpr (PREC == PREC_FP32) {
-        fft_line<N, INV, TWP, SPLIT, FRESH>(x, lds, tw, t, before_last);
+        fft_line<N, INV, SPLIT, FRESH>(x, lds, tw, t, before_last);
     } else {
         using L = LineLaunch<N>;
         fft_line_mfma<N, INV, PREC, L::LPW, L::BLOCK, IN_MF>(x, lds - sub * LineGeom<N>::LDS, tw, sub,
@@ -191,18 +194,6 @@ __device__ __forceinline__ float2 ld_off(const float2* __restrict__ base, uint32
     return *(const float2*)((const char*)base + byte_off);
 }
 
-// Buffer resource over `bytes` bytes (less than 4 GiB) from a wave-uniform base:
-// reads beyond its end return zero and writes there are dropped.  A buffer
-// access takes a vector offset plus a scalar one, so the 16 accesses of a line
-// share one address register instead of 16 64-bit sums.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* base, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00020000);
-}
-__device__ __forceinline__ float2 buf_ld(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
-{
-    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
-}
 __device__ __forceinline__ float4 buf_ld4(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff)
 {
     return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
@@ -326,13 +317,12 @@ enum LineKind { LK_FUSED = 0, LK_FWD = 1, LK_INV = 2 };
 
 //  LK_FUSED: out = IFFT(FFT(in) * H)      (H carries the 1/N)
 //  LK_FWD:   out = FFT(in) * scale;  LK_INV: out = IFFT_unscaled(in) * scale
-// One group of LPW lines starting at line g * LPW of `in` / `out`.  TWP:
-// twiddles by products (true) or straight table reads (false), chosen per
-// line length by the autotuner; SPLIT (FP32 forward / inverse): the split
-// real/imaginary exchange layout.
 // The transform of one line held by its T threads (thread t: points t + m*T;
 // split precisions: in the layout of mf_in, left in that of mf_out) with `lds`
-// its exchange buffer: FFT * H * IFFT, FFT or IFFT (see line_group).
+// its exchange buffer: FFT * H * IFFT, FFT or IFFT.  TWP: the default transform
+// (fft_line), or every twiddle from the table and ahead of the butterflies
+// (false), chosen per line length by the autotuner; SPLIT (FP32 forward /
+// inverse): the split real/imaginary exchange layout.
 template <int N, int KIND, int PREC, bool TWP, bool SPLIT = false>
 __device__ __forceinline__ void line_transform(float2 (&x)[line_e(N)], float2* __restrict__ lds,
                                                const float2* __restrict__ H,
@@ -363,6 +353,7 @@ __device__ __forceinline__ void line_transform(float2 (&x)[line_e(N)], float2* _
     }
 }
 
+// One group of LPW lines starting at line g * LPW of `in` / `out`.
 template <int N, int KIND, int PREC, bool TWP, bool SPLIT = false, int X = 1>
 __device__ __forceinline__ void line_group(const float2* in, float2* out, int lines,
                                            const float2* __restrict__ H,
