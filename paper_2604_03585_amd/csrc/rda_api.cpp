@@ -469,7 +469,7 @@ sar_status sar_plan(const sar_params* p, void* stream, sar_plan_t* out)
     const size_t o_ha = off;  off = align_up(off + (hyper ? 0 : sizeof(float2) * (size_t)Na), A);
     const size_t o_st = off;  off = align_up(off + (hyper ? sizeof(double) * (size_t)Na : 0), A);
     const size_t o_rt = off;  off = align_up(off + (hyper ? sizeof(double) * (size_t)Na : 0), A);
-    const size_t o_tb = off;  off = align_up(off + (hyper ? sizeof(float) * (size_t)sar::rcmc_table_floats() : 0), A);
+    const size_t o_tb = off;  off = align_up(off + (hyper ? sizeof(float) * (size_t)sar::rcmc_all_floats() : 0), A);
     e = hipMalloc(&P->block, off);
     if (e != hipSuccess) {
         delete P;

@@ -59,7 +59,7 @@ struct TurnTask {
 struct RcmcHost {
     const double* stretch;   // device, Na doubles: 1/D_k - 1
     const double* rate;      // device, Na doubles: 2 D_k / lambda
-    const float* table;      // device, rcmc_table_floats() weight coefficients
+    const float* table;      // device, rcmc_all_floats() weight coefficients
     double r_near;
     double stretch_max;      // largest stretch_k (at |f| = 1/2)
     double x_per_bin;        // lambda / (2 v Na)
@@ -162,7 +162,8 @@ hipError_t launch_gen_twiddles(void* tw, int n, hipStream_t s);
 hipError_t launch_gen_chirp_filter(void* H, int n, int len, double K, int sign, double scale,
                                    hipStream_t s);
 hipError_t launch_gen_rcmc_table(float* tab, double beta, hipStream_t s);
-int rcmc_table_floats();
+int rcmc_table_floats();      // quadratics on 128 intervals (table 4 of sar_plan_get_table)
+int rcmc_all_floats();        // and the cubics of the four-row kernel behind them
 hipError_t launch_gen_hyper_tables(double* stretch, double* rate, int na, double lam, double v,
                                    hipStream_t s);
 

@@ -37,6 +37,7 @@
 #include "fft_line.hpp"
 #include "fft_line_tw.hpp"
 #include "mfma_fft.hpp"
+#include "rcmc_fit.hpp"
 #include "rda_internal.h"
 
 // Every kernel launch of the library.  When sar_time_next_launch has armed
@@ -961,93 +962,24 @@ __global__ __launch_bounds__(256) void k_corner_turn_batch(const TurnTask* __res
 #endif  // SAR_PART == 0
 
 // ===================================================== RCMC
-// The 8-tap Kaiser-windowed sinc (taps t = -3..4 about floor(p), x = p -
-// floor(p), weights normalised to unit sum) depends on x alone.  Its eight
-// weight functions w_t(x) are smooth on [0, 1), so the plan stores them as
-// piecewise quadratics: RCMC_INTERVALS intervals, on each a degree-2
-// Chebyshev interpolant of the exact FP64 weights, in monomial form in the
-// local variable u = x * RCMC_INTERVALS - b in [0, 1].  Layout (interval-
-// major, 24 floats = 96 bytes per interval, read as six 16-byte vectors):
-//     tab[b * 24 + t * 3 + j] = coefficient of u^j, tap t.
-// The interpolation error is 2.2e-8 in FP64 (below the FP32 rounding of the
-// coefficients; tested against the oracle's weights); the kernels copy the
-// 12 KiB table into LDS (14 KiB there, see RCMC_LDS_STRIDE).
-constexpr int RCMC_INTERVALS = 128;
-constexpr int RCMC_PER_INTERVAL = 24;
-constexpr int RCMC_TAB = RCMC_INTERVALS * RCMC_PER_INTERVAL;
-// The LDS copy places the intervals 7 vectors (28 floats) apart: the lanes of
-// a wave read random intervals, and with an odd stride in 16-byte units the
-// same vector of different intervals falls into every bank group, where a
-// stride of 6 reaches only half of them (twice the bank conflicts).  The
-// seventh vector of each interval is padding and never read.
+// (weights and their tables: rcmc_fit.hpp)
+// The kernels copy the 12 KiB table of quadratics into LDS with the intervals 7
+// vectors (28 floats) apart: the lanes of a wave read random intervals, and with an
+// odd stride in 16-byte units the same vector of different intervals falls into
+// every bank group, where a stride of 6 reaches only half of them (twice the bank
+// conflicts).  The seventh vector of each interval is padding and never read.
 constexpr int RCMC_LDS_STRIDE = 28;
 constexpr int RCMC_LDS_FLOATS = RCMC_INTERVALS * RCMC_LDS_STRIDE;
 
 #if SAR_PART == 0
-__device__ double i0_fp64(double y)
-{
-    const double q = 0.25 * y * y;
-    double term = 1.0, sum = 1.0;
-    for (int k = 1; k < 200; ++k) {
-        term *= q / ((double)k * (double)k);
-        sum += term;
-        if (term < 1e-17 * sum) break;
-    }
-    return sum;
-}
-
-// Exact normalised weights at x (FP64): K(z) = sinc(z) I0(beta sqrt(1-(z/4)^2)).
-__device__ void kaiser_weights_fp64(double x, double beta, double* w)
-{
-    double sum = 0.0;
-    for (int i = 0; i < 8; ++i) {
-        const double z = (double)(i - 3) - x;
-        const double r = z / 4.0;
-        const double sc = (z == 0.0) ? 1.0 : sinpi(z) / (3.14159265358979323846 * z);
-        const double arg = 1.0 - r * r;
-        w[i] = (arg > 0.0 ? sc * i0_fp64(beta * sqrt(arg)) : 0.0);
-        sum += w[i];
-    }
-    for (int i = 0; i < 8; ++i) w[i] /= sum;
-}
-
-// One thread per interval b: three Chebyshev nodes, exact weights, 3x3
-// solve per tap for the monomial coefficients in u.
+// One thread per interval: block 0 the quadratics, block 1 the cubics.
 __global__ void k_gen_rcmc_table(float* __restrict__ tab, double beta)
 {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= RCMC_INTERVALS) return;
-    double u[3], w[3][8];
-    for (int j = 0; j < 3; ++j) {
-        u[j] = 0.5 * (1.0 + cospi((2.0 * j + 1.0) / 6.0));
-        kaiser_weights_fp64(((double)b + u[j]) / RCMC_INTERVALS, beta, w[j]);
-    }
-    for (int t = 0; t < 8; ++t) {
-        double M[3][4];
-        for (int j = 0; j < 3; ++j) {
-            M[j][0] = 1.0;
-            M[j][1] = u[j];
-            M[j][2] = u[j] * u[j];
-            M[j][3] = w[j][t];
-        }
-        for (int c = 0; c < 3; ++c) {             // Gaussian elimination, partial pivot
-            int piv = c;
-            for (int r = c + 1; r < 3; ++r)
-                if (fabs(M[r][c]) > fabs(M[piv][c])) piv = r;
-            for (int q = 0; q < 4; ++q) { double tmp = M[c][q]; M[c][q] = M[piv][q]; M[piv][q] = tmp; }
-            for (int r = c + 1; r < 3; ++r) {
-                const double f = M[r][c] / M[c][c];
-                for (int q = c; q < 4; ++q) M[r][q] -= f * M[c][q];
-            }
-        }
-        double cf[3];
-        for (int c = 2; c >= 0; --c) {
-            double acc = M[c][3];
-            for (int q = c + 1; q < 3; ++q) acc -= M[c][q] * cf[q];
-            cf[c] = acc / M[c][c];
-        }
-        for (int j = 0; j < 3; ++j) tab[b * RCMC_PER_INTERVAL + t * 3 + j] = (float)cf[j];
-    }
+    const int b = threadIdx.x;
+    if (blockIdx.x == 0 && b < RCMC_INTERVALS)
+        rcmc_fit<2>(tab + b * RCMC_PER_INTERVAL, b, RCMC_INTERVALS, 0.0, beta);
+    if (blockIdx.x == 1 && b < RROWS_INTERVALS)
+        rcmc_fit<3>(tab + RCMC_TAB + b * RROWS_PER_INTERVAL, b, RROWS_INTERVALS, RROWS_MARGIN, beta);
 }
 
 #endif  // SAR_PART == 0
@@ -1055,7 +987,7 @@ __global__ void k_gen_rcmc_table(float* __restrict__ tab, double beta)
 struct RcmcArgs {
     const double* stretch;   // 1/D_k - 1 per Doppler bin
     const double* rate;      // 2 D_k / lambda per Doppler bin
-    const float* table;      // RCMC_TAB weight coefficients (global)
+    const float* table;      // RCMC_TAB + RROWS_TAB weight coefficients (global)
     double r_near;
     double stretch_max;      // max_k stretch_k (|f| = 1/2)
     double x_per_bin;        // lambda / (2 v Na): x_k = signed bin * x_per_bin
@@ -1103,17 +1035,16 @@ __global__ void k_gen_hyper_tables(double* __restrict__ stretch, double* __restr
 }
 #endif
 
-// Global table (24 floats per interval) -> LDS (RCMC_LDS_STRIDE floats per
-// interval); lds_tab holds RCMC_LDS_FLOATS floats.
-template <int STRIDE = RCMC_LDS_STRIDE>
+// Global table (PER floats per interval) -> LDS (STRIDE floats per interval);
+// lds_tab holds INTERVALS * STRIDE floats.
+template <int STRIDE = RCMC_LDS_STRIDE, int PER = RCMC_PER_INTERVAL, int INTERVALS = RCMC_INTERVALS>
 __device__ __forceinline__ void load_rcmc_table(float* __restrict__ lds_tab,
                                                 const float* __restrict__ tab, int tid, int nthreads,
                                                 float scale = 1.0f)
 {
-    static_assert(RCMC_PER_INTERVAL == 24 && STRIDE % 4 == 0, "16-byte copies");
-    constexpr int V = RCMC_PER_INTERVAL / 4, VS = STRIDE / 4;
-    for (int i = tid; i < RCMC_TAB / 4; i += nthreads)
-    {
+    static_assert(PER % 4 == 0 && STRIDE % 4 == 0, "16-byte copies");
+    constexpr int V = PER / 4, VS = STRIDE / 4;
+    for (int i = tid; i < INTERVALS * V; i += nthreads) {
         const float4 v = ((const float4*)tab)[i];
         ((float4*)lds_tab)[(i / V) * VS + i % V] =
             make_float4(v.x * scale, v.y * scale, v.z * scale, v.w * scale);
@@ -1121,14 +1052,13 @@ __device__ __forceinline__ void load_rcmc_table(float* __restrict__ lds_tab,
 }
 
 // sum_t w_t(x) a_t with the weights from the LDS table.
-template <int STRIDE = RCMC_LDS_STRIDE>
 __device__ __forceinline__ float2 rcmc_combine(float x, const float* __restrict__ tab,
                                                const float2 (&a)[8])
 {
     const float xf = x * (float)RCMC_INTERVALS;
     const int b = min((int)xf, RCMC_INTERVALS - 1);
     const float u = xf - (float)b;
-    const float4* p = (const float4*)(tab + __mul24(b, STRIDE));
+    const float4* p = (const float4*)(tab + __mul24(b, RCMC_LDS_STRIDE));
     float2 acc = make_float2(0.f, 0.f);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {                 // taps 4h .. 4h+3: three vectors
@@ -1522,10 +1452,8 @@ k_rcmc_az2(const void* __restrict__ A_, float2* __restrict__ out, RcmcArgs ra,
 // the others wait in registers.  The FP64 geometry, the gathers and the table
 // reads are shared by four samples:
 //   * twelve rows i0 - 3 .. i0 + 8 cover the four windows;
-//   * the shifts s + j stretch, j < 4, lie within 0.2 table intervals, so one
-//     interval (that of their middle) serves all rows, its quadratics being
-//     evaluated at u in [-0.1, 1.1] (fit error 2.2e-8 there at most x 2.8, the
-//     size of the FP32 rounding of the weights);
+//   * the shifts s + j stretch, j < 4, lie close together, so one interval (that
+//     of their middle) of a table fitted for it serves all rows (RROWS_MARGIN);
 //   * where a shift crosses a cell boundary between the rows (a wave vote; one
 //     wave in ten) the rows take their own windows and intervals.
 // Rows beyond the scene read as zero by the buffer's bounds; only the first
@@ -1538,7 +1466,6 @@ k_rcmc_az2(const void* __restrict__ A_, float2* __restrict__ out, RcmcArgs ra,
 // times the table reads per sample), alone, from HBM: 4096^2 101 -> 74 us, 8192
 // x 4096 212 -> 162, 2048 x 1024 20.6 -> 11.8, 1024 x 4096 25 -> 17, 256 x 4096
 // 23 -> 7.8.  (At 4096 points one workgroup of 1024 threads per CU took 79.)
-constexpr double RCMC_ROWS_STRETCH_MAX = 5e-4;   // 3 x 5e-4 x 128 = 0.19 intervals
 
 template <int N> struct RcmcRows {
     static constexpr int T = LineGeom<N>::T;
@@ -1551,10 +1478,9 @@ template <int N> struct RcmcRows {
     static constexpr int G = S >= 256 ? 1 : 256 / S;             // groups per workgroup
     static constexpr int BLOCK = S * G;
     static constexpr int LINES = SIDE * G * LineGeom<N>::LDS * (int)sizeof(float2);
-    // intervals as in the plan (24 floats apart): at 4096 points two workgroups
-    // then take a CU's 160 KiB to the byte
-    static constexpr int STRIDE = RCMC_PER_INTERVAL;
-    static constexpr int TABLE = RCMC_INTERVALS * STRIDE * (int)sizeof(float);
+    // intervals an odd number of 16-byte units apart, see RCMC_LDS_STRIDE
+    static constexpr int STRIDE = RROWS_PER_INTERVAL + 4;
+    static constexpr int TABLE = RROWS_INTERVALS * STRIDE * (int)sizeof(float);
     // one round: the table shares LDS with the lines, which are written after
     // its last read; two: the first round's rows go to LDS as they are formed
     static constexpr int LDS_BYTES = ROUNDS == 2 ? LINES + TABLE : (LINES > TABLE ? LINES : TABLE);
@@ -1585,6 +1511,29 @@ __device__ __forceinline__ void rcmc_gather_rows(float2 (&w)[ROWS], const RcmcSr
     }
 }
 
+__device__ __forceinline__ float rrows_weight(float4 cf, float v)
+{
+    return fmaf(fmaf(fmaf(cf.w, v, cf.z), v, cf.y), v, cf.x);
+}
+
+// sum_t w_t(x) a_t, x on its own interval.
+template <int STRIDE>
+__device__ __forceinline__ float2 rrows_combine(float x, const float* tab, const float2 (&a)[8])
+{
+    const float xf = x * (float)RROWS_INTERVALS;
+    const int b = min((int)xf, RROWS_INTERVALS - 1);
+    const float v = xf - (float)b;
+    const float4* q = (const float4*)(tab + __mul24(b, STRIDE));
+    float2 acc = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+        const float wt = rrows_weight(q[t], v);
+        acc.x = fmaf(wt, a[t].x, acc.x);
+        acc.y = fmaf(wt, a[t].y, acc.y);
+    }
+    return acc;
+}
+
 // The samples of columns u + m * S: the last SIDE rows' in y, the first round's
 // (of two) in the line buffers `lines`.
 template <int N, bool EDGE, bool HIN>
@@ -1613,31 +1562,25 @@ __device__ __forceinline__ void rcmc_rows_columns(float2 (&y)[RcmcRows<N>::SIDE]
         float2 acc[R];
         if (__builtin_amdgcn_ballot_w64(x[R - 1] >= 1.0f) == 0) {
             // one interval for all rows
-            const int b = min((int)(0.5f * (x[0] + x[R - 1]) * (float)RCMC_INTERVALS), RCMC_INTERVALS - 1);
+            const int b = min((int)(0.5f * (x[0] + x[R - 1]) * (float)RROWS_INTERVALS), RROWS_INTERVALS - 1);
             const float fb = (float)b;
             float v[R];
 #pragma unroll
             for (int j = 0; j < R; ++j) {
-                v[j] = fmaf(x[j], (float)RCMC_INTERVALS, -fb);
+                v[j] = fmaf(x[j], (float)RROWS_INTERVALS, -fb);
                 acc[j] = make_float2(0.f, 0.f);
             }
             const float4* q = (const float4*)(tab + __mul24(b, L::STRIDE));
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {         // taps 4h .. 4h+3: three vectors
-                float cf[12];
+            for (int h = 0; h < 2; ++h) {         // taps 4h .. 4h+3
+                float4 cf[4];
 #pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    const float4 g = q[3 * h + i];
-                    cf[4 * i] = g.x;
-                    cf[4 * i + 1] = g.y;
-                    cf[4 * i + 2] = g.z;
-                    cf[4 * i + 3] = g.w;
-                }
+                for (int i = 0; i < 4; ++i) cf[i] = q[4 * h + i];
 #pragma unroll
                 for (int j = 0; j < R; ++j)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const float wt = fmaf(fmaf(cf[3 * i + 2], v[j], cf[3 * i + 1]), v[j], cf[3 * i]);
+                        const float wt = rrows_weight(cf[i], v[j]);
                         const float2 a = w[4 * h + i + j];
                         acc[j].x = fmaf(wt, a.x, acc[j].x);
                         acc[j].y = fmaf(wt, a.y, acc[j].y);
@@ -1651,7 +1594,7 @@ __device__ __forceinline__ void rcmc_rows_columns(float2 (&y)[RcmcRows<N>::SIDE]
                 float2 a[8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) a[i] = d ? w[i + j + 1 < ROWS ? i + j + 1 : 0] : w[i + j];
-                acc[j] = rcmc_combine<L::STRIDE>(d ? x[j] - 1.0f : x[j], tab, a);
+                acc[j] = rrows_combine<L::STRIDE>(d ? x[j] - 1.0f : x[j], tab, a);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -1686,7 +1629,8 @@ k_rcmc_rows(const void* __restrict__ A, float2* __restrict__ out, RcmcArgs ra,
     ab.rows = buf_rsrc(A, HIN ? bytes / 2 : bytes);
     if constexpr (HIN) ab.exponents = buf_rsrc(ra.row_exp, (uint32_t)ra.nr * 4u);
     // the weights carry the IFFT's 1/N (a power of two: exact)
-    load_rcmc_table<L::STRIDE>(tab, ra.table, threadIdx.x, L::BLOCK, 1.0f / (float)N);
+    load_rcmc_table<L::STRIDE, RROWS_PER_INTERVAL, RROWS_INTERVALS>(tab, ra.table + RCMC_TAB, threadIdx.x,
+                                                                    L::BLOCK, 1.0f / (float)N);
     float2 y[SIDE][L::C];
     if (n0 >= 4) rcmc_rows_columns<N, false, HIN>(y, ab, ra, n, u, tab, lines);
     else rcmc_rows_columns<N, true, HIN>(y, ab, ra, n, u, tab, lines);
@@ -2716,11 +2660,13 @@ hipError_t launch_gen_chirp_filter(void* H, int n, int len, double K, int sign, 
 
 hipError_t launch_gen_rcmc_table(float* tab, double beta, hipStream_t s)
 {
-    SAR_LAUNCH(k_gen_rcmc_table, dim3(1), dim3(RCMC_INTERVALS), 0, s, tab, beta);
+    static_assert(RROWS_INTERVALS <= RCMC_INTERVALS, "one thread per interval");
+    SAR_LAUNCH(k_gen_rcmc_table, dim3(2), dim3(RCMC_INTERVALS), 0, s, tab, beta);
     return hipGetLastError();
 }
 
 int rcmc_table_floats() { return RCMC_TAB; }
+int rcmc_all_floats() { return RCMC_TAB + RROWS_TAB; }
 
 hipError_t launch_gen_hyper_tables(double* stretch, double* rate, int na, double lam, double v,
                                    hipStream_t s)
