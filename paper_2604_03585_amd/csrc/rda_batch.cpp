@@ -197,7 +197,7 @@ sar_status build(sar_batch_s* B, const void* const* raw, void* const* img, void*
         host.resize(align256(host.size()));
         return SAR_OK;
     };
-    auto add_strip_stage = [&](bool range_stage, const std::vector<int>& scenes) {
+    auto add_strip_stage = [&](bool range_stage, const std::vector<int>& scenes) -> sar_status {
         Launch L{range_stage ? 2 : 3, 0, 0, 0, 0, host.size(), 0, 0};
         for (int i : scenes) {
             const sar_params& p = B->params[i];
@@ -209,6 +209,9 @@ sar_status build(sar_batch_s* B, const void* const* raw, void* const* img, void*
             t.tw = (const float2*)(range_stage ? tb.tw_r : tb.tw_a);
             t.n = range_stage ? p.Nr : p.Na;
             t.other = range_stage ? p.Na : p.Nr;
+            if (((uintptr_t)t.in | (uintptr_t)t.out) & 15u)      // the strips load 16 bytes at a time
+                return sar::set_error(SAR_ERR_BAD_PARAM, "scene %d: batched strips need 16-byte aligned "
+                                      "buffers", i);
             t.group_begin = L.total;
             L.total += range_stage ? sar::batch_range_groups(t.n, t.other) : sar::batch_strip_groups(t.n, t.other);
             const char* b = (const char*)&t;
@@ -217,16 +220,17 @@ sar_status build(sar_batch_s* B, const void* const* raw, void* const* img, void*
         }
         if (L.ntasks) launches.push_back(L);
         host.resize(align256(host.size()));
+        return SAR_OK;
     };
     std::vector<int> scenes, strips;
     for (int i = 0; i < n; ++i)
         if (batched_strips(B->params[i])) strips.push_back(i);
         else if (batched(B->params[i])) scenes.push_back(i);
-    add_strip_stage(true, strips);
-    add_strip_stage(false, strips);
-    add_line_stage(true, scenes);
-    sar_status st = add_turn_stage(false, scenes);
+    sar_status st = add_strip_stage(true, strips);
+    if (st == SAR_OK) st = add_strip_stage(false, strips);
     if (st != SAR_OK) return st;
+    add_line_stage(true, scenes);
+    if ((st = add_turn_stage(false, scenes)) != SAR_OK) return st;
     add_line_stage(false, scenes);
     if ((st = add_turn_stage(true, scenes)) != SAR_OK) return st;
 
