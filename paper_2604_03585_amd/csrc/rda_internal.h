@@ -96,6 +96,9 @@ hipError_t launch_range_tiled(int n, const void* in, void* out, int na, const vo
 enum class StripOp { Fused, Forward, FusedBack };
 hipError_t launch_line_strip(StripOp op, int n, const void* in, void* out, int cols,
                              const void* H, const void* tw, float scale, int variant, hipStream_t s);
+// Whether the strip's width is the tuner's to choose (with few range cells it is
+// given by their number, whatever the variant).
+bool strip_width_open(int n, int cols);
 
 // Batched launches (kind: 0 fused, 1 forward, 2 inverse; tasks in device memory).
 //  variant bits 0 (twiddles) and 2-3 (grid: one workgroup per line group, or

@@ -2299,11 +2299,13 @@ static hipError_t launch_strip_c(StripOp op, const float2* in, float2* out, int 
     return hipErrorInvalidValue;
 }
 
-// Twiddles by products only.  The strip width is the default one where that
-// makes a workgroup per CU, else half of it, else the narrowest of whole waves
-// (two lines from 512 points): with few range cells the chip would stand idle
-// (2048 x 256 scene: 24.0 us with 32 strips of 8, 17.4 with 128 of 2).  Variant
-// 1: half the default width always.
+// The strip width is the default one where that makes a workgroup per CU, else half
+// of it, else the narrowest of whole waves (two lines from 512 points): with few
+// range cells the chip would stand idle (2048 x 256 scene: 24.0 us with 32 strips of
+// 8, 17.4 with 128 of 2).  Variant 1, tuned per line length whatever the number of
+// range cells: half in place of the default width, not in place of a narrower one.
+constexpr int CUS = 256;                          // MI355X
+
 template <int N>
 static hipError_t launch_strip_n(StripOp op, const float2* in, float2* out, int cols,
                                  const float2* H, const float2* tw, float scale, int variant,
@@ -2311,14 +2313,24 @@ static hipError_t launch_strip_n(StripOp op, const float2* in, float2* out, int 
 {
     constexpr int C = StripLaunch<N>::C_DEFAULT, HALF = C / 2;
     constexpr int LEAST = 64 / StripLaunch<N>::T > 2 ? 64 / StripLaunch<N>::T : 2;
-    if (variant == 1) return launch_strip_c<N, HALF>(op, in, out, cols, H, tw, scale, s);
     if constexpr (LEAST < HALF) {
-        if (cols / HALF < 256) return launch_strip_c<N, LEAST>(op, in, out, cols, H, tw, scale, s);
+        if (cols / HALF < CUS) return launch_strip_c<N, LEAST>(op, in, out, cols, H, tw, scale, s);
     }
     if constexpr (LEAST <= HALF) {
-        if (cols / C < 256) return launch_strip_c<N, HALF>(op, in, out, cols, H, tw, scale, s);
+        if (cols / C < CUS) return launch_strip_c<N, HALF>(op, in, out, cols, H, tw, scale, s);
     }
+    if (variant == 1) return launch_strip_c<N, HALF>(op, in, out, cols, H, tw, scale, s);
     return launch_strip_c<N, C>(op, in, out, cols, H, tw, scale, s);
+}
+
+bool strip_width_open(int n, int cols)
+{
+    switch (n) {
+#define SAR_CASE(N) case N: return StripLaunch<N>::T < 8 || cols / StripLaunch<N>::C_DEFAULT >= CUS;
+        SAR_CASE(64) SAR_CASE(128) SAR_CASE(256) SAR_CASE(512) SAR_CASE(1024) SAR_CASE(2048) SAR_CASE(4096)
+#undef SAR_CASE
+    default: return false;
+    }
 }
 
 hipError_t launch_line_strip(StripOp op, int n, const void* in, void* out, int cols,

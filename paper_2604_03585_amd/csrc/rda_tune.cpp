@@ -460,14 +460,15 @@ sar_status sar_autotune(const sar_params* p, const char* cache_path)
         if (st == SAR_OK && p->transpose_back) st = tune_turn(Nr, Na);
         if (st != SAR_OK) return done(st);
     }
-    // the turn-free azimuth strips
-    if (p->schedule == SAR_TURN_FREE && fp32 && Na <= 4096) {
+    // the turn-free azimuth strips, where there are range cells enough to leave
+    // their width open
+    if (p->schedule == SAR_TURN_FREE && fp32 && Na <= 4096 && sar::strip_width_open(Na, Nr)) {
         std::vector<Candidate> cs{{0, 0.f}, {1, 0.f}};
         st = time_candidates(
             cs,
             [&](int v) {
-                return sar::launch_line_strip(hyper ? sar::StripOp::Forward : sar::StripOp::Fused, Na, in, out, Nr, hyper ? nullptr : tb.Ha,
-                                              tb.tw_a, 1.f, v, s);
+                return sar::launch_line_strip(hyper ? sar::StripOp::Forward : sar::StripOp::Fused, Na, in, out,
+                                              Nr, hyper ? nullptr : tb.Ha, tb.tw_a, 1.f, v, s);
             },
             s);
         if (st != SAR_OK) return done(st);
