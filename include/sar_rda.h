@@ -109,12 +109,17 @@ typedef enum { SAR_FUSED = 0, SAR_UNFUSED = 1, SAR_TURN_FREE = 2 } sar_schedule;
  *                  sar_rda_execute's azimuth kernel reads strips of adjacent
  *                  azimuth lines straight from the range pass's [Na][Nr]
  *                  output (FP32, Na <= 4096, transpose_back = 0; else
- *                  SAR_ERR_UNSUPPORTED).  Images are bit-identical to
- *                  SAR_FUSED's; the step entry points behave as for
- *                  SAR_FUSED.  sar_rda_execute runs SAR_FUSED plans the same
- *                  way where those kernels cover them (FP32, Na <= 4096, no
- *                  tuned table twiddles): the corner turn then falls away,
- *                  the image stays the same bit for bit.
+ *                  SAR_ERR_UNSUPPORTED).  sar_rda_execute runs SAR_FUSED
+ *                  plans the same way where those kernels cover them and
+ *                  there are range cells enough (FP32, Na <= 4096; from Na =
+ *                  2048 at least 512 range cells, 256 for the hyperbolic
+ *                  model or with transpose_back): the corner turn then falls
+ *                  away.  Images of the two schedules are bit-identical, and
+ *                  so are those of the step entry points, which behave as
+ *                  for SAR_FUSED, unless the autotuner gives a line length
+ *                  table twiddles: these are for the step entry points and
+ *                  the schedule that keeps its corner turn, whose last bits
+ *                  they change.
  *  transpose_back  0: sar_rda_execute leaves the image as [Nr][Na];
  *                  1: it is turned back to [Na][Nr].
  */
@@ -253,9 +258,8 @@ sar_status sar_plan_get_table(sar_plan_t plan, int32_t which, void* host_dst,
  * azimuth and the fused schedule share launches, each a grid over all their
  * line groups or tiles (task lists in device memory): FP32 scenes with lines
  * of 128 to 4096 points and no back-turn two launches in all (range lines into
- * column tiles, azimuth strips; line lengths tuned to table twiddles excepted),
- * the rest one line launch per (pass, line length, precision) and one
- * corner-turn launch per turn.  Every
+ * column tiles, azimuth strips), the rest one line launch per (pass, line length,
+ * precision, twiddle scheme) and one corner-turn launch per turn.  Every
  * other scene (hyperbolic, unfused, half storage, and any scene of 2^22
  * pixels or more, which fills the GPU with its own launches) runs as
  * sar_rda_execute in the same stream, in scene order, after the shared
@@ -299,8 +303,8 @@ void sar_batch_destroy(sar_batch_t batch);
  * Kernel variants are chosen per (kind, line length N, precision); every
  * variant computes the same result, they differ in scheduling only:
  *   kind 0 fused FFT*H*IFFT, 1 forward FFT, 2 inverse FFT line kernels:
- *          variant bit 0 = twiddles read from the table (else by products
- *          of two table loads per radix-16 pass; FP32 butterflies only);
+ *          variant bit 0 = every twiddle read from the table (else four per
+ *          radix-16 pass; FP32 butterflies only);
  *          kinds 1 and 2 (FP32): bit 1 = real and imaginary parts exchanged
  *          through LDS as two float arrays (the split layout of the MFMA
  *          passes; else one array of complex pairs); bit 2 (FP32, N <= 8192)
@@ -310,15 +314,19 @@ void sar_batch_destroy(sar_batch_t batch);
  *          output row per line slot (else two rows sharing their gathers),
  *          bit 2 = the two rows on two line slots' threads instead of one's
  *          (FP32 and Na = 4096 or 8192 only);
- *   kind 4 batched fused line kernel: bit 0 as above, bits 2-3 = grid
- *          (0: one workgroup per line group; 1, 2, 3: a persistent grid of
- *          1x, 2x, 4x the resident workgroups);
+ *   kind 4 batched fused line kernel: bits 2-3 = grid (0: one workgroup per
+ *          line group; 1, 2, 3: a persistent grid of 1x, 2x, 4x the resident
+ *          workgroups); bit 0 is accepted and has no effect (a batch takes
+ *          the twiddles of kind 0, as the scene run alone);
  *   kind 5 corner turn, keyed by the row length of the matrix it turns
  *          (precision 0): variant 0 = a grid of five workgroups per CU,
  *          1 = four per CU, 2 = one workgroup per 64 x 64 tile;
  *   kind 6 turn-free azimuth strips, keyed by the azimuth line length
  *          (precision 0): variant 0 = the default strip width, 1 = half of
- *          it (half the LDS and threads per workgroup, shorter row runs).
+ *          it (half the LDS and threads per workgroup, shorter row runs) for
+ *          scenes of range cells enough for a default strip per CU.
+ * Kinds 0 to 2, 4 and 5 are kernels of the step entry points and of schedules
+ * that keep the corner turn; a scene that runs in strips takes kinds 3 and 6.
  * The process-wide table starts with every variant 0.  A plan copies the
  * table's choices for its sizes when it is created (sar_plan, sar_batch_plan);
  * the first plan of the process loads $SAR_AUTOTUNE_CACHE if that is set.

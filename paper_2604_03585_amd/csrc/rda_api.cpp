@@ -172,12 +172,32 @@ HalfLayout half_layout(int Na, int Nr)
     h.total = h.e2 + al(4 * (size_t)Nr);
     return h;
 }
+// Whether sar_rda_execute runs without the corner turn: always for the turn-free
+// schedule, and for the fused one where the strip kernels cover the plan (FP32,
+// azimuth lines of up to 4096).  Long lines over few range cells keep the turn: a
+// strip is one workgroup of up to 1024 threads, and 256 range cells make only 128 of
+// them (4096 x 256 LFM: 20.8 us turned, 22.2 in strips; 4096 x 512: 30.5 and 27.4).
+// Elsewhere the strips were faster at every size measured, 64 x 256 to 4096 x 8192
+// (1.1 to 1.5 times: 4096^2 hyperbolic 187 us against 225, 1024 x 2048 LFM 24 against
+// 32).  Sizes alone decide: a tuned variant of a line kernel is a few percent of that
+// kernel, which the strips do not run.
+bool runs_strips(const sar_plan_s* P)
+{
+    const sar_params& p = P->p;
+    if (p.schedule == SAR_TURN_FREE) return true;
+    const bool lfm = p.az_model == SAR_AZ_LFM;
+    const int least_nr = p.Na < 2048 ? 0 : (lfm && !p.transpose_back ? 512 : 256);
+    return p.schedule == SAR_FUSED && p.precision == SAR_FP32 && p.Na <= 4096 && p.Nr >= least_nr;
+}
+
 }  // namespace
 
 namespace sar {
 PlanTables plan_tables(const sar_plan_s* P)
 {
-    return PlanTables{P->Hr, P->Ha, P->tw_r, P->tw_a};
+    const bool turned = !runs_strips(P);
+    return PlanTables{P->Hr, P->Ha, P->tw_r, P->tw_a, turned ? P->var_r[TK_FUSED] & 1 : 0,
+                      turned ? P->var_a[TK_FUSED] & 1 : 0};
 }
 }  // namespace sar
 
@@ -340,25 +360,6 @@ sar_status step_azimuth(const sar_plan_s* P, const void* in, void* out, void* wo
                 "azimuth IFFT launch");
     }
     return SAR_OK;
-}
-
-// Whether sar_rda_execute runs without the corner turn: always for the turn-free
-// schedule, and for the fused one where the strip kernels cover the plan (FP32,
-// azimuth lines of up to 4096) and compute the same bits: they form twiddles by
-// products, so a plan tuned to table twiddles keeps its corner turn.  Long lines
-// over few range cells keep it too: a strip is one workgroup of up to 1024
-// threads, and 256 range cells make only 128 of them (4096 x 256 LFM: 20.8 us
-// turned, 22.2 in strips; 4096 x 512: 30.5 and 27.4).  Elsewhere the strips were
-// faster at every size measured, 64 x 256 to 4096 x 8192 (1.1 to 1.5 times: 4096^2
-// hyperbolic 187 us against 225, 1024 x 2048 LFM 24 against 32).
-bool runs_strips(const sar_plan_s* P)
-{
-    const sar_params& p = P->p;
-    if (p.schedule == SAR_TURN_FREE) return true;
-    const bool lfm = p.az_model == SAR_AZ_LFM;
-    const int least_nr = p.Na < 2048 ? 0 : (lfm && !p.transpose_back ? 512 : 256);
-    return p.schedule == SAR_FUSED && p.precision == SAR_FP32 && p.Na <= 4096 && p.Nr >= least_nr &&
-           !((P->var_r[sar::TK_FUSED] | P->var_a[lfm ? sar::TK_FUSED : sar::TK_FWD]) & 1);
 }
 
 // No corner turn: the azimuth pass reads strips of adjacent azimuth lines

@@ -101,16 +101,13 @@ bool batched(const sar_params& p)
 // Batched scenes that run without the corner turn: two launches for all of
 // them, the range lines into column tiles and the azimuth strips (the kernels of
 // sar_rda_execute's own turn-free schedule, so the same bits).  FP32 lines of
-// BATCH_STRIP_MIN to BATCH_STRIP_MAX points; they form twiddles by products, so a line length
-// tuned to table twiddles stays with the turned passes.  Faster than those at
-// every mix measured: 24 scenes of 128 to 1024 a side 54.7 -> 32.1 us, 40 of up
-// to 2048 303 -> 195, 16 of 4096 x 512 338 -> 321, 8 of 1024 x 1024 108 -> 77.
-bool batched_strips(const sar_params& p)
+// BATCH_STRIP_MIN to BATCH_STRIP_MAX points, unless the scene alone would take
+// table twiddles.  Faster than the turned passes at every mix measured: 24 scenes of 128 to 1024 a side 54.7 -> 33.8 us, 40 of up to 2048 303 ->
+// 195, 16 of 4096 x 512 338 -> 321, 8 of 1024 x 1024 108 -> 77.
+bool batched_strips(const sar_params& p, const sar::PlanTables& tb)
 {
-    return batched(p) && p.precision == SAR_FP32 && !p.transpose_back &&
-           std::min(p.Nr, p.Na) >= sar::BATCH_STRIP_MIN && std::max(p.Nr, p.Na) <= sar::BATCH_STRIP_MAX &&
-           !((sar::tuned_variant(sar::TK_BATCH_FUSED, p.Nr, p.precision) |
-              sar::tuned_variant(sar::TK_BATCH_FUSED, p.Na, p.precision)) & 1);
+    return batched(p) && p.precision == SAR_FP32 && !p.transpose_back && !tb.tab_r && !tb.tab_a &&
+           std::min(p.Nr, p.Na) >= sar::BATCH_STRIP_MIN && std::max(p.Nr, p.Na) <= sar::BATCH_STRIP_MAX;
 }
 
 // Build task arrays for this buffer set and upload them (synchronous).
@@ -130,15 +127,17 @@ sar_status build(sar_batch_s* B, const void* const* raw, void* const* img, void*
         if (!batched(B->params[i])) B->fallback.push_back(i);
     }
     auto add_line_stage = [&](bool range_stage, const std::vector<int>& scenes) {
-        // group the scenes by (line length, precision)
-        std::map<std::pair<int, int>, std::vector<int>> groups;
+        // group the scenes by (line length, precision, twiddle scheme): the grid is
+        // the batch's own choice, the twiddles are those of the scene run alone
+        std::map<std::tuple<int, int, int>, std::vector<int>> groups;
         for (int i : scenes) {
+            const sar::PlanTables tb = sar::plan_tables(B->plans[B->plan_of[i]]);
             const int len = range_stage ? B->params[i].Nr : B->params[i].Na;
-            groups[{len, B->params[i].precision}].push_back(i);
+            groups[{len, B->params[i].precision, range_stage ? tb.tab_r : tb.tab_a}].push_back(i);
         }
         for (auto& kv : groups) {
-            Launch L{0, 0, kv.first.first, kv.first.second,
-                     sar::tuned_variant(sar::TK_BATCH_FUSED, kv.first.first, kv.first.second),
+            const auto [len, prec, tab] = kv.first;
+            Launch L{0, 0, len, prec, (sar::tuned_variant(sar::TK_BATCH_FUSED, len, prec) & ~1) | tab,
                      host.size(), 0, 0};
             for (int i : kv.second) {
                 sar_plan_t P = B->plans[B->plan_of[i]];
@@ -224,7 +223,7 @@ sar_status build(sar_batch_s* B, const void* const* raw, void* const* img, void*
     };
     std::vector<int> scenes, strips;
     for (int i = 0; i < n; ++i)
-        if (batched_strips(B->params[i])) strips.push_back(i);
+        if (batched_strips(B->params[i], sar::plan_tables(B->plans[B->plan_of[i]]))) strips.push_back(i);
         else if (batched(B->params[i])) scenes.push_back(i);
     sar_status st = add_strip_stage(true, strips);
     if (st == SAR_OK) st = add_strip_stage(false, strips);

@@ -149,6 +149,7 @@ struct PlanTables {
     const void* Ha;
     const void* tw_r;
     const void* tw_a;
+    int tab_r, tab_a;        // sar_rda_execute's fused passes take table twiddles
 };
 PlanTables plan_tables(const sar_plan_s* P);
 RcmcHost plan_rcmc(const sar_plan_s* P);   // hyperbolic plans only

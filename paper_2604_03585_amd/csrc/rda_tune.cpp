@@ -1,14 +1,17 @@
 // rda_tune.cpp -- the autotuner: measured choice of kernel variants.
 //
 // Tuned per (kernel kind, line length, precision):
-//   line kernels (fused FFT*H*IFFT, forward, inverse):  twiddles computed by
-//       products of two table loads per radix-16 pass, or read from the table
-//       (FP32 butterflies only; the MFMA variants share one scheme);
-//   RCMC + azimuth kernel: the same twiddle choice for its IFFT, and two
-//       output rows per workgroup (shared interpolation gathers; on one or
-//       on two line slots' threads) or one row;
-//   batched fused line kernel: twiddles and the grid (one workgroup per line
-//       group, or a persistent grid of 1x, 2x or 4x the resident workgroups).
+//   line kernels (fused FFT*H*IFFT, forward, inverse):  the default twiddle scheme,
+//       or every twiddle read from the table (FP32 butterflies only; the MFMA
+//       variants share one scheme);
+//   RCMC + azimuth kernel: four output rows per group of threads, or two on two
+//       line slots' threads, or one;
+//   batched fused line kernel: the grid (one workgroup per line group, or a
+//       persistent grid of 1x, 2x or 4x the resident workgroups);
+//   corner turn: its grid;  azimuth strips: their width.
+// The line and batch kernels, and the corner turn, are those of the step entry
+// points and of the schedules that keep the turn.  Scenes that run in strips take
+// neither their variants nor, for them, another schedule.
 // Every candidate computes the same result (they differ in instruction mix and
 // scheduling only); the tests check each one against the oracle.
 //
@@ -402,9 +405,8 @@ sar_status sar_autotune(const sar_params* p, const char* cache_path)
         if (hipMemcpy(task, &t, sizeof t, hipMemcpyHostToDevice) != hipSuccess)
             return sar::set_error(SAR_ERR_HIP, "task upload");
         const int groups = sar::line_groups(n, lines);
-        std::vector<Candidate> cs;
-        for (int g = 0; g < (fp32 ? 4 : 1); ++g)
-            for (int tw_tab = 0; tw_tab < (fp32 ? 2 : 1); ++tw_tab) cs.push_back({tw_tab | (g << 2), 0.f});
+        std::vector<Candidate> cs;     // grids (the twiddles are the single scenes')
+        for (int g = 0; g < (fp32 ? 4 : 1); ++g) cs.push_back({g << 2, 0.f});
         sar_status r = time_candidates(
             cs,
             [&](int v) { return sar::launch_line_batch(0, n, task, 1, groups, 1.f, prec, v, s); }, s);
