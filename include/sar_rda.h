@@ -214,9 +214,11 @@ sar_status sar_rda_execute_noalloc(sar_plan_t plan, const void* raw_dev, void* i
  * hipEvent_t the caller created with timing enabled and keeps alive until
  * they have completed.  n = 0 disarms; n outside 0..16 is SAR_ERR_BAD_SIZE,
  * a NULL array or event SAR_ERR_NULL (nothing armed then).  sar_rda_execute
- * launches 3 kernels for a hyperbolic plan without the corner turn (range,
- * azimuth strip FFT, RCMC) and 2 for LFM; with the corner turn (see the
- * schedules above) 4 and 3. */
+ * takes 4 pairs for a fused FP32 hyperbolic plan (range, corner turn, azimuth
+ * FFT, RCMC), 3 for LFM or for SAR_TURN_FREE hyperbolic, 2 for SAR_TURN_FREE
+ * LFM, and one more for the back-turn.  Where a fused plan runs without a
+ * corner turn (see the schedules above) that turn's events are recorded in its
+ * place, one right after the other. */
 sar_status sar_time_next_launches(void* const* start_events, void* const* stop_events, int32_t n);
 
 /* ---- individual steps, for step-by-step testing and the unfused path ---- */

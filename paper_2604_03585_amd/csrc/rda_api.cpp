@@ -362,6 +362,18 @@ sar_status step_azimuth(const sar_plan_s* P, const void* in, void* out, void* wo
     return SAR_OK;
 }
 
+// The corner turn that a fused plan does without in strips: a pair of events armed
+// for it (sar_time_next_launches counts the kernels of the fused schedule) is
+// recorded where it would run, with nothing between.
+sar_status absent_turn(const sar_plan_s* P, hipStream_t s)
+{
+    hipEvent_t e0, e1;
+    if (P->p.schedule != SAR_FUSED || !sar::take_launch_events(e0, e1)) return SAR_OK;
+    HIP_TRY(hipEventRecord(e0, s), "event of the absent corner turn");
+    HIP_TRY(hipEventRecord(e1, s), "event of the absent corner turn");
+    return SAR_OK;
+}
+
 // No corner turn: the azimuth pass reads strips of adjacent azimuth lines
 // straight from the range pass's output, which is kept in tiles of 32 columns
 // (TileMap in rda_kernels.inl).
@@ -374,16 +386,19 @@ sar_status execute_strips(const sar_plan_s* P, const void* raw, void* img, void*
 {
     const int Nr = P->p.Nr, Na = P->p.Na;
     const bool back = P->p.transpose_back != 0;
+    sar_status st;
     if (P->p.az_model == SAR_AZ_LFM) {
         HIP_TRY(sar::launch_range_tiled(Nr, raw, work, Na, P->Hr, P->tw_r, s), "range launch (column tiles)");
+        if ((st = absent_turn(P, s))) return st;
         HIP_TRY(sar::launch_line_strip(back ? sar::StripOp::FusedBack : sar::StripOp::Fused, Na, work, img, Nr,
                                        P->Ha, P->tw_a, 1.f, P->var_strip, s),
                 "azimuth strip launch");
-        return SAR_OK;
+        return back ? absent_turn(P, s) : SAR_OK;
     }
     void* a = back ? work : img;
     void* b = back ? img : work;
     HIP_TRY(sar::launch_range_tiled(Nr, raw, a, Na, P->Hr, P->tw_r, s), "range launch (column tiles)");
+    if ((st = absent_turn(P, s))) return st;
     HIP_TRY(sar::launch_line_strip(sar::StripOp::Forward, Na, a, b, Nr, nullptr, P->tw_a, 1.f, P->var_strip,
                                    s),
             "azimuth strip FFT launch");
