@@ -241,9 +241,17 @@ __device__ __forceinline__ void store_line(const float2 (&x)[line_e(N)], __amdgp
 }
 
 // The RCMC pass's stores of its image lines pass by the caches (non-temporal):
-// the rows that are still gathered then stay in an XCD's L2 (8192 points: 212 ->
-// 188 us per 32 Mpx, 2048 x 4096 hyperbolic scene 95.8 -> 91.1), and the image is
-// not read again.  CACHED: the exception, see rcmc_image_cached.
+// the rows that are still gathered then stay in an XCD's L2, and the image is not
+// read again.  Whole hyperbolic scenes over rotating buffers, past the caches
+// against through them, us: 1024 x 4096 48.6 v 53.0, 2048 x 4096 93.9 v 99.1, 8192 x
+// 2048 236 v 245, 8192 x 8192 952 v 969, 16384 x 1024 263 v 272; split FP16 4096 x
+// 4096 244 v 251, half storage 4096 x 8192 370 v 389: better at 40 of 41 sizes from 32
+// to 512 MiB.  CACHED: lines of 4096 points in FP32 over more than 64 MiB, where it
+// is even or worse (4096 x 2048 97.4 v 101.9, x 4096 198 v 187, x 8192 410 v 410, x
+// 16384 812 v 814; 2048 x 8192 192 v 196).  Their azimuth lines come in strips of four
+// columns, 32-byte runs, which the last-level cache has to merge, and the next
+// scene's strip FFT takes 70 us instead of 52 at 4096 x 4096 when the image went
+// past it.
 template <int N, bool CACHED = false, bool MF = false>
 __device__ __forceinline__ void store_image_line(const float2 (&x)[line_e(N)], __amdgpu_buffer_rsrc_t dst,
                                                  uint32_t off)
@@ -255,15 +263,16 @@ __device__ __forceinline__ void store_image_line(const float2 (&x)[line_e(N)], _
     }
 }
 
-// 4096-point lines over FP32 arrays of 64 to 256 MiB: the range output and the
-// range-Doppler data then fill the 256 MiB last-level cache between them, and
-// with the image written past it the next scene's strip FFT took 70 us in place
-// of 52 (4096^2: 195 against 183 us; 4096 x 2048 89 against 92, 4096 x 8192 equal,
-// half storage 170 against 176).
-template <int N> __device__ __forceinline__ constexpr bool rcmc_image_may_be_cached() { return N == 4096; }
-__device__ __forceinline__ bool rcmc_image_cached(uint32_t bytes)
+// As above, of an image of `bytes` bytes formed by kernels of precision PREC from
+// FP32 rows or (HIN) FP16 ones.
+template <int N, int PREC, bool HIN, bool MF>
+__device__ __forceinline__ void store_image_line(const float2 (&x)[line_e(N)], __amdgpu_buffer_rsrc_t dst,
+                                                 uint32_t off, uint32_t bytes)
 {
-    return bytes > (64u << 20) && bytes < (256u << 20);
+    if (N == 4096 && PREC == PREC_FP32 && !HIN && bytes > (64u << 20))
+        store_image_line<N, true, MF>(x, dst, off);
+    else
+        store_image_line<N, false, MF>(x, dst, off);
 }
 
 // Column tiles: the range output between the two passes of the turn-free
@@ -1439,9 +1448,10 @@ k_rcmc_az2(const void* __restrict__ A_, float2* __restrict__ out, RcmcArgs ra,
     const uint32_t bytes = (uint32_t)(min(L::LPW, pairs - g * L::LPW) * 2 * N) * 8u;
     const __amdgpu_buffer_rsrc_t ob = buf_rsrc(out + (size_t)(2 * g * L::LPW) * N, bytes);
     const uint32_t off = (uint32_t)(2 * sub * N + mf_point<N, OUT>(t)) * 8u;
-    store_image_line<N, N == 4096, OUT>(xa, ob, off);
+    const uint32_t image = (uint32_t)ra.nr * N * 8u;
+    store_image_line<N, PREC, HIN, OUT>(xa, ob, off, image);
     fft_any<N, true, PREC, true, false, NoOp, true, 0, IN>(xb, lds, tw, sub, t);
-    store_image_line<N, N == 4096, OUT>(xb, ob, off + N * 8u);
+    store_image_line<N, PREC, HIN, OUT>(xb, ob, off + N * 8u, image);
 }
 
 // Four output rows n .. n + 3 per group of threads, for geometries whose shift changes little from row to row (stretch up to
@@ -1659,10 +1669,7 @@ k_rcmc_rows(const void* __restrict__ A, float2* __restrict__ out, RcmcArgs ra,
         else
             fft_line_mfma<N, true, PREC, L::BLOCK / T, L::BLOCK, IN>(x, lines, tw, line, t);
         const uint32_t off = (uint32_t)((n0 + r * SIDE + line) * N + mf_point<N, OUT>(t)) * 8u;
-        if (!HIN && rcmc_image_may_be_cached<N>() && rcmc_image_cached(bytes))
-            store_image_line<N, true, OUT>(x, ob, off);
-        else
-            store_image_line<N, false, OUT>(x, ob, off);
+        store_image_line<N, PREC, HIN, OUT>(x, ob, off, bytes);
     }
 }
 
