@@ -102,8 +102,9 @@ bool batched(const sar_params& p)
 // them, the range lines into column tiles and the azimuth strips (the kernels of
 // sar_rda_execute's own turn-free schedule, so the same bits).  FP32 lines of
 // BATCH_STRIP_MIN to BATCH_STRIP_MAX points, unless the scene alone would take
-// table twiddles.  Faster than the turned passes at every mix measured: 24 scenes of 128 to 1024 a side 54.7 -> 33.8 us, 40 of up to 2048 303 ->
-// 195, 16 of 4096 x 512 338 -> 321, 8 of 1024 x 1024 108 -> 77.
+// table twiddles.  Faster than the turned passes at every mix measured: 24 scenes
+// of 128 to 1024 a side 54.7 -> 33.8 us, 40 of up to 2048 303 -> 195, 16 of 4096 x 512
+// 338 -> 321, 8 of 1024 x 1024 108 -> 77.
 bool batched_strips(const sar_params& p, const sar::PlanTables& tb)
 {
     return batched(p) && p.precision == SAR_FP32 && !p.transpose_back && !tb.tab_r && !tb.tab_a &&

@@ -3,8 +3,9 @@
 // the template instantiations build in parallel: part 0 holds the table
 // generators, the non-line kernels and the dispatcher, parts 1-3 the line
 // and RCMC kernels for FP32, split-FP16 and split-BF16 butterflies, part 4
-// the turn-free strips and the half-storage kernels.  Every kernel is written for wave64 CDNA4; lines are kept in
-// registers (16 complex64 per thread) and LDS between radix passes.
+// the turn-free strips and the half-storage kernels.  Every kernel is written for
+// wave64 CDNA4; lines are kept in registers (16 complex64 per thread) and LDS
+// between radix passes.
 //
 // Kernels (paper: arXiv 2604.03585):
 //   k_gen_*          FP64 plan-time tables (twiddles, matched filters with
@@ -455,8 +456,7 @@ __device__ __forceinline__ StripSrc strip_source(const float2* in, const TileMap
     return s;
 }
 
-// Strip g of the scene, by the C T threads u = 0 .. C T - 1; a strip beyond the
-// last column (g uniform per wave) reads zeros and stores nothing.
+// Strip g of the scene (uniform per wave), by the C T threads u = 0 .. C T - 1.
 // BACK: the lines leave as they came, C samples of every row of out [N][cols]
 // (the back-turned image), regrouped through LDS once more.
 template <int N, int KIND, int CW, bool BACK>
@@ -468,10 +468,10 @@ __device__ __forceinline__ void strip_group(const float2* __restrict__ in, float
     using S = StripLaunch<N, CW>;
     constexpr int T = S::T, C = S::C;
     constexpr uint32_t ROW = TILE_COLS * 8u;      // bytes between rows of a tile
-    const bool here = g * C < cols;
-    const int n0 = here ? g * C : 0;
+    static_assert(KIND == LK_FUSED || KIND == LK_FWD, "fused or forward");
+    const int n0 = g * C;
     const StripSrc src = strip_source(in, tm, cols, n0);
-    const __amdgpu_buffer_rsrc_t ib = buf_rsrc(src.base, here ? src.bytes : 0u);
+    const __amdgpu_buffer_rsrc_t ib = buf_rsrc(src.base, src.bytes);
     // 16-byte loads: lanes take pairs of adjacent columns, C / 2 lanes per row,
     // rows m0 + 2 T p; the row's exclusive or splits into the lane's and the
     // load's part because m0 < 2 T
@@ -511,14 +511,14 @@ __device__ __forceinline__ void strip_group(const float2* __restrict__ in, float
         for (int m = 0; m < 16; ++m) x[m] = c_mul(x[m], buf_ld(hb, (uint32_t)t * 8u, m * T * 8u));
         fft_line_half<N, true>(x, lds, tw, t);
     } else {
-        fft_line_half<N, KIND == LK_INV>(x, lds, tw, t);
+        fft_line_half<N, false>(x, lds, tw, t);
         if (scale != 1.0f) {
 #pragma unroll
             for (int m = 0; m < 16; ++m) x[m] = c_scale(x[m], scale);
         }
     }
     if constexpr (!BACK) {
-        store_line<N>(x, buf_rsrc(out + (size_t)n0 * N, here ? C * N * 8u : 0u), (uint32_t)(sub * N + t) * 8u);
+        store_line<N>(x, buf_rsrc(out + (size_t)n0 * N, C * N * 8u), (uint32_t)(sub * N + t) * 8u);
     } else {
 #pragma unroll
         for (int m = 0; m < 16; ++m) lds[half_in<T, 0>(t, m)] = x[m].x;
@@ -532,7 +532,7 @@ __device__ __forceinline__ void strip_group(const float2* __restrict__ in, float
 #pragma unroll
         for (int m = 0; m < 16; ++m) lds[half_in<T, 0>(t, m)] = x[m].y;
         wg_barrier();
-        const __amdgpu_buffer_rsrc_t ob = buf_rsrc(out + n0, here ? (uint32_t)(N * cols - n0) * 8u : 0u);
+        const __amdgpu_buffer_rsrc_t ob = buf_rsrc(out + n0, (uint32_t)(N * cols - n0) * 8u);
         const uint32_t off = (uint32_t)(m0 * cols + 2 * q) * 8u;
 #pragma unroll
         for (int p = 0; p < 8; ++p) {
@@ -721,6 +721,7 @@ template <int N> struct BatchStrip {
     static constexpr int PER_WG = BATCH_STRIP_BLOCK / (C * T);
     static constexpr int LDS_BYTES = PER_WG * StripLaunch<N, C>::LDS_BYTES;
     static_assert(C * T % 64 == 0, "whole waves per strip");
+    static_assert(BATCH_STRIP_MIN % (C * PER_WG) == 0, "no strip beyond the last column");
 };
 #define SAR_LDS(N) BatchStrip<N>::LDS_BYTES,
 constexpr int BATCH_STRIP_LDS = batch_max({SAR_BATCH_LENGTHS(SAR_LDS)});
@@ -1454,10 +1455,10 @@ k_rcmc_az2(const void* __restrict__ A_, float2* __restrict__ out, RcmcArgs ra,
     store_image_line<N, PREC, HIN, OUT>(xb, ob, off + N * 8u, image);
 }
 
-// Four output rows n .. n + 3 per group of threads, for geometries whose shift changes little from row to row (stretch up to
-// RCMC_ROWS_STRETCH_MAX).  Up to 2048 points the group has 4T threads (T = N/16):
-// a thread interpolates four columns of the four rows, the rows meet in LDS and
-// their IFFTs run side by side.  At 4096 and 8192 points it has 2T threads and
+// Four output rows n .. n + 3 per group of threads, for geometries whose shift
+// changes little from row to row (stretch up to RCMC_ROWS_STRETCH_MAX).  Up to 2048
+// points the group has 4T threads (T = N/16): a thread interpolates four columns of
+// the four rows, the rows meet in LDS and their IFFTs run side by side.  At 4096 and 8192 points it has 2T threads and
 // works in two rounds: the first two rows' samples go to LDS as they are formed,
 // the others wait in registers.  The FP64 geometry, the gathers and the table
 // reads are shared by four samples:
@@ -1476,7 +1477,6 @@ k_rcmc_az2(const void* __restrict__ A_, float2* __restrict__ out, RcmcArgs ra,
 // times the table reads per sample), alone, from HBM: 4096^2 101 -> 74 us, 8192
 // x 4096 212 -> 162, 2048 x 1024 20.6 -> 11.8, 1024 x 4096 25 -> 17, 256 x 4096
 // 23 -> 7.8.  (At 4096 points one workgroup of 1024 threads per CU took 79.)
-
 template <int N> struct RcmcRows {
     static constexpr int T = LineGeom<N>::T;
     static_assert(N <= 8192, "two lines and the table fit LDS");
@@ -1893,10 +1893,12 @@ static RcmcArgs make_rcmc_args(const RcmcHost& rh)
     return ra;
 }
 
+constexpr int CUS = 256;                          // MI355X: 8 XCDs of 32 CUs
+
 [[maybe_unused]] static int grid_for(long long work, int per_block)
 {
     long long g = (work + per_block - 1) / per_block;
-    const long long cap = 256LL * 64;   // grid-stride kernels: 64 workgroups per CU
+    const long long cap = CUS * 64LL;   // grid-stride kernels: 64 workgroups per CU
     return (int)(g < 1 ? 1 : (g > cap ? cap : g));
 }
 
@@ -1969,7 +1971,7 @@ static hipError_t launch_k_line_x(const float2* in, float2* out, int lines, cons
 // fused inside a 4096^2 scene 205.7 us against 207.8 for the scene), once there
 // are more lines than resident workgroups (below that there is no next line to
 // load: 64 lines of 16384 take 16.2 us with k_line, 18.4 with it).
-template <int N> constexpr int pipe_resident() { return 256 * (16384 / N); }
+template <int N> constexpr int pipe_resident() { return CUS * (16384 / N); }
 template <int N> static bool pipe_pays(int lines) { return lines > pipe_resident<N>(); }
 
 template <int N, int KIND, bool TILED>
@@ -2142,14 +2144,14 @@ static hipError_t launch_line_batch_t(int kind, const LineTask* tasks, int ntask
     if (attr != hipSuccess) return attr;
     if (total_groups == 0) return hipSuccess;
     // grid_sel 0: one workgroup per line group; 1, 2, 3: a persistent grid of
-    // 1x, 2x, 4x the resident workgroups (LDS-limited per CU x 256 CUs)
+    // 1x, 2x, 4x the resident workgroups (LDS-limited per CU x CUs)
     if ((grid_sel & 3) == 0) {
         launch_line_batch_k<N, PREC, TWP, false>(kind, total_groups, tasks, ntasks, total_groups,
                                                  scale, s);
         return hipGetLastError();
     }
     const int per_cu = (160 * 1024) / L::LDS_BYTES;
-    const int resident = (per_cu < 1 ? 1 : per_cu) * 256;
+    const int resident = (per_cu < 1 ? 1 : per_cu) * CUS;
     const int cap = resident << ((grid_sel & 3) - 1);
     const int grid = total_groups < cap ? total_groups : cap;
     launch_line_batch_k<N, PREC, TWP, true>(kind, grid, tasks, ntasks, total_groups, scale, s);
@@ -2311,8 +2313,6 @@ static hipError_t launch_strip_c(StripOp op, const float2* in, float2* out, int 
 // range cells the chip would stand idle (2048 x 256 scene: 24.0 us with 32 strips of
 // 8, 17.4 with 128 of 2).  Variant 1, tuned per line length whatever the number of
 // range cells: half in place of the default width, not in place of a narrower one.
-constexpr int CUS = 256;                          // MI355X
-
 template <int N>
 static hipError_t launch_strip_n(StripOp op, const float2* in, float2* out, int cols,
                                  const float2* H, const float2* tw, float scale, int variant,
@@ -2368,7 +2368,7 @@ int batch_range_groups(int n, int lines)
 int batch_strip_groups(int n, int lines)
 {
     switch (n) {
-#define SAR_CASE(N) case N: return (lines + BatchStrip<N>::C * BatchStrip<N>::PER_WG - 1) / (BatchStrip<N>::C * BatchStrip<N>::PER_WG);
+#define SAR_CASE(N) case N: return lines / (BatchStrip<N>::C * BatchStrip<N>::PER_WG);
         SAR_BATCH_LENGTHS(SAR_CASE)
 #undef SAR_CASE
     default: return 0;
@@ -2554,7 +2554,7 @@ hipError_t launch_line_batch(int kind, int n, const void* tasks, int ntasks, int
 hipError_t launch_corner_turn_batch(const void* tasks, int ntasks, int total_tiles, hipStream_t s)
 {
     if (total_tiles == 0) return hipSuccess;
-    const int grid = total_tiles < 256 * 16 ? total_tiles : 256 * 16;
+    const int grid = total_tiles < CUS * 16 ? total_tiles : CUS * 16;
     SAR_LAUNCH(k_corner_turn_batch, dim3(grid), dim3(256), 0, s, (const TurnTask*)tasks,
                        ntasks, total_tiles);
     return hipGetLastError();
