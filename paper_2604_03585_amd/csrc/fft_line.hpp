@@ -250,16 +250,18 @@ template <int N> struct LineGeom {
     static constexpr int LDS = N + N / 16;
 };
 
-// LDS slot of point i in the exchange after pass P: 1 (P = 0) or 2 (later
-// passes) pad slots every 32.  LDS serves 8-byte accesses 32 lanes at a time
-// from 32 slots' worth of banks.  The reads take 32 consecutive points, which
-// no pad splits, so they are free of conflicts; the writes of pass 0 (16
-// points apart) need an odd pad, those of pass 1 (two runs of 16 points 256
-// apart) an even one.  With one pad every 16 for all passes the reads had a
-// two-way conflict (0.5 conflict cycles per active LDS cycle).
+// LDS slot of point i in the exchange after pass P: 1 (P = 0) or 2 (later passes)
+// pad slots every 32.  LDS serves 8-byte reads 32 lanes and 8-byte writes 16 lanes at
+// a time (2 and 4 cycles per wave and instruction, SQ_LDS_IDX_ACTIVE of each pattern
+// alone), so 32 lanes of a read must differ in the slot's low five bits and 16 lanes
+// of a write in its low four.  The reads take 32 consecutive points, which no pad
+// splits, and are free of conflicts; so are the writes of pass 1 (runs of 16 points
+// 256 apart).  The writes of pass 0 (16 points apart) have a two-way conflict and
+// take 8 cycles; a pad every 16 would move it to the reads (4 + 4 cycles).
 template <int P> __host__ __device__ constexpr int lds_pads() { return P == 0 ? 1 : 2; }
 
-template <int P> __device__ __forceinline__ int lds_slot(int i)
+template <int P>
+__host__ __device__ constexpr int lds_slot(int i)
 {
     return i + lds_pads<P>() * (i >> 5);
 }
@@ -268,12 +270,14 @@ template <int P> __device__ __forceinline__ int lds_slot(int i)
 // radix-16 pass P of span NS (base = 16 t, or 16 NS (t / NS) + t % NS), as one
 // address per thread plus a constant, which becomes the instruction's offset:
 // the sums carry nothing from their low five bits into the pad term.
-template <int T, int P> __device__ __forceinline__ int lds_in(int t, int m)
+template <int T, int P>
+__host__ __device__ constexpr int lds_in(int t, int m)
 {
     if constexpr (T >= 32) return lds_slot<P>(t) + m * (T + lds_pads<P>() * (T / 32));
     else return t + (m * T + lds_pads<P>() * (m * T / 32));
 }
-template <int NS, int P> __device__ __forceinline__ int lds_out(int base, int i)
+template <int NS, int P>
+__host__ __device__ constexpr int lds_out(int base, int i)
 {
     return lds_slot<P>(base) + i * NS + lds_pads<P>() * (i * NS / 32);
 }
@@ -700,23 +704,29 @@ __device__ __forceinline__ void fft_line_held(float2 (&x)[16], float2* __restric
 // (with 64 registers per thread, 32 waves): for the column strips, whose loads
 // wait long, that is worth more.
 //
-// Slot of point i after pass P: 4-byte accesses are served 64 lanes at a time
-// from 64 banks; pass 0's writes are 16 points apart (an odd pad every 64
-// points keeps them apart), pass 1's are runs of 16 points 256 apart (a pad of
-// 4 every 64).
+// Slot of point i after pass P: 4-byte accesses are served 32 lanes at a time (2
+// cycles per wave and instruction), which must differ in the slot's low five bits.
+// The reads take consecutive points, pass 1's writes runs of 16 points 256 apart (a
+// pad of 4 every 64): free of conflicts.  Pass 0's writes are 16 points apart and with
+// a pad every 64 have a two-way conflict (4 cycles); a pad every 32 avoids it, but
+// with that and the strips' lines 32 / C apart the back-turned 1024 x 2048 scene took
+// 28.1 us instead of 27.4 and no other scene less.
 template <int P> __host__ __device__ constexpr int half_pads() { return P == 0 ? 1 : 4; }
 
-template <int P> __device__ __forceinline__ int half_slot(int i)
+template <int P>
+__host__ __device__ constexpr int half_slot(int i)
 {
     return i + half_pads<P>() * (i >> 6);
 }
 // half_slot(t + m * T), t < T, and half_slot(base + i * NS), as in lds_in / lds_out.
-template <int T, int P> __device__ __forceinline__ int half_in(int t, int m)
+template <int T, int P>
+__host__ __device__ constexpr int half_in(int t, int m)
 {
     if constexpr (T >= 64) return half_slot<P>(t) + m * (T + half_pads<P>() * (T / 64));
     else return t + (m * T + half_pads<P>() * (m * T / 64));
 }
-template <int NS, int P> __device__ __forceinline__ int half_out(int base, int i)
+template <int NS, int P>
+__host__ __device__ constexpr int half_out(int base, int i)
 {
     return half_slot<P>(base) + i * NS + half_pads<P>() * (i * NS / 64);
 }

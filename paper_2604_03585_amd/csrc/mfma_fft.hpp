@@ -152,19 +152,18 @@ __device__ __forceinline__ DftOperands<PREC> dft16_operands(int lane)
     return d;
 }
 
-// Slot of point e of a line (N slots; no pads).  LDS serves 8-byte accesses 32
-// lanes at a time from 32 slots' worth of banks, and the 32 lanes must differ in
-// the slot's low five bits.  They are 16 butterflies c and the low bit of q (or
-// 32 consecutive points, which any exclusive or of higher bits keeps apart):
+// Slot of point e of a line (N slots; no pads).  Lanes of an 8-byte access must
+// differ in the slot's low five bits, 32 at a time, if it reads, and in the low four,
+// 16 at a time, if it writes (see lds_slot).  Lanes are 16 butterflies c, then q (or
+// consecutive points, which any exclusive or of higher bits keeps apart):
 //   reads              e = .. + c + q N/4     (bits 0-3, the bit N/4)
-//   writes of pass 0   e = .. + 16 c + 4 q    (bits 4-7, bit 2)
-//   writes of pass 1   e = .. + c + 64 q      (bits 0-3, bit 6)
-//   writes of pass 2   e = .. + c + 1024 q    (bits 0-3, bit 10)
-// so bits 5, 6, 7 go into bits 0, 1, 3 (pass 0) and the bits 6, 10 and N/4 into
-// bit 4.  Shorter lines, whose slots do not split into a lane's part and constants
-// because a wave works on several, keep one pad slot per 16: forming the exclusive
-// ors costs them more than the conflicts (512 x 1024 scene 22.5 us with pads, 25.0
-// without).
+//   writes of pass 0   e = .. + 16 c + 4 q    (bits 4-7)
+//   writes of pass 1   e = .. + c + 64 q      (bits 0-3)
+//   writes of pass 2   e = .. + c + 1024 q    (bits 0-3)
+// so bits 4, 5, 6, 7 go into bits 2, 0, 1, 3 (pass 0) and the bit N/4 into bit 4.
+// Shorter lines, whose slots do not split into a lane's part and constants because
+// a wave works on several, keep one pad slot per 16: forming the exclusive ors costs
+// them more than the conflicts (512 x 1024 scene 22.5 us with pads, 25.0 without).
 //
 // From 1024 points mf_slot is linear over exclusive or and changes the low five
 // bits alone: a point whose bits are those of a lane's part and of a constant has
@@ -174,13 +173,10 @@ template <int N> __host__ __device__ constexpr int mf_slot(int e)
 {
     if constexpr (N < 1024) return e + (e >> 4);
     constexpr int LT = ilog2(N / 4);
-    int four = e >> 6;
-    if constexpr (N > 4096) four ^= e >> 10;
-    four ^= e >> LT;
-    return e ^ ((e >> 5) & 1) ^ ((e >> 5) & 2) ^ ((e >> 4) & 8) ^ ((four & 1) << 4);
+    return e ^ ((e >> 2) & 4) ^ ((e >> 5) & 3) ^ ((e >> 4) & 8) ^ (((e >> LT) & 1) << 4);
 }
 
-__device__ __forceinline__ int mf_at(int lane_slot, int const_slot)
+__host__ __device__ constexpr int mf_at(int lane_slot, int const_slot)
 {
     return (lane_slot ^ (const_slot & 63)) + (const_slot & ~63);
 }

@@ -433,8 +433,8 @@ template <int N, int CW = 0> struct StripLaunch {
     static constexpr int C_DEFAULT = (1024 / T) < 8 ? 1024 / T : (T >= 8 ? 8 : 16);
     static constexpr int C = CW ? CW : C_DEFAULT;
     static constexpr int BLOCK = C * T;
-    // lines 64 / C floats more than a multiple of 64 apart: the C samples of a
-    // row and the rows of a wave fall into different banks
+    // lines 64 / C floats more than a multiple of 64 apart, which keeps the C samples
+    // of a row apart in pairs (32 lanes are served together: two turns)
     static constexpr int STRIDE = (N + N / 16 + 63) / 64 * 64 + 64 / C;
     static constexpr int LDS_BYTES = C * STRIDE * (int)sizeof(float);
     static_assert(N <= 8192 && C >= 2 && C <= 16, "strips of two lines or more");
