@@ -55,8 +55,9 @@ def test_strips_whatever_is_tuned(tmp_path, na, nr, model, which):
         assert np.array_equal(image(cfg, raw, schedule=schedule), want), schedule
 
 
-BATCH = [(256, 512, {}), (512, 256, {"transpose_back": 1}), (64, 256, {}), (256, 256, {"transpose_back": 1}),
+BATCH = [(256, 512, {}), (1024, 256, {"transpose_back": 1}), (512, 256, {"transpose_back": 1}), (64, 256, {}), (256, 256, {"transpose_back": 1}),
          (2048, 256, {}), (8192, 128, {}), (512, 512, {})]
+# (back-turned scenes, 64-point and 8192-point lines take the line and turn launches)
 
 
 @pytest.mark.parametrize("kinds", [("fused",), ("batch_fused",), ("fused", "batch_fused")])
