@@ -242,11 +242,12 @@ __device__ __forceinline__ int mfma_line_scale_exp(const float2 (&x)[16], float2
 // unnormalised DFT), in the operand layout where mf_out, else strided.
 //   lds:   the workgroup's LDS (LPW lines, N + N/16 float2 each)
 //   sub:   this thread's line within the workgroup, t its index in the line
+//   KEEP:  LDS slots and twiddles may stay in registers for the next transform
 //   before_last: runs as the last MFMA pass starts (callers issue the loads
 //          they need right after the transform there, e.g. a filter)
 // On entry no wave may still read the lines' LDS unless it was the previous
 // transform's (mf_out leaves without a barrier, see mfma_line_scale_exp).
-template <int N, bool INV, int PREC, int LPW, int BLOCK, bool IN_MF, class Pre = NoOp>
+template <int N, bool INV, int PREC, int LPW, int BLOCK, bool IN_MF, bool KEEP = false, class Pre = NoOp>
 __device__ __forceinline__ void fft_line_mfma(float2 (&x)[16], float2* __restrict__ lds,
                                               const float2* __restrict__ tw, int sub, int t,
                                               Pre&& before_last = Pre())
@@ -261,9 +262,9 @@ __device__ __forceinline__ void fft_line_mfma(float2 (&x)[16], float2* __restric
     constexpr int WAVES = BLOCK / 64;
     constexpr int GPW = GROUPS / WAVES;          // groups per wave
     static_assert(GROUPS % WAVES == 0 && GPW >= 1, "group split");
-    // formed anew in each transform: its LDS slots kept across the multiply take
-    // 90 registers
-    if constexpr (T >= 64) t = fresh(t);
+    // formed anew in each transform: its LDS slots kept across the multiply (KEEP)
+    // take 90 registers
+    if constexpr (T >= 64 && !KEEP) t = fresh(t);
     const int tid = T >= 64 ? sub * T + t : (int)threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, q = lane >> 4;
     // Butterfly j of the line for group gi.  LINES: the wave's groups belong to one

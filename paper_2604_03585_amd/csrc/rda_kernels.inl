@@ -147,15 +147,29 @@ template <int N, int X = 1> struct LineLaunch {
     static constexpr int LDS_BYTES = LPW * LineGeom<N>::LDS * (int)sizeof(float2);
 };
 
+// One workgroup per group of LPW lines.
+enum LineKind { LK_FUSED = 0, LK_FWD = 1, LK_INV = 2 };
+
 // Minimum waves per SIMD requested for the line kernels: 4 for 1024 points and
 // more (FP32 up to 4096, as many workgroups as LDS allows; the split-precision
 // ones take 112 to 128 VGPRs; split BF16 below 4096 points 3, for the reads of its
 // trailing pass's twiddles), else 2 in the split precisions (130 VGPRs; held to
-// 128 they spill) and no request in FP32.
-template <int N, int PREC> constexpr int line_wpe()
+// 128 they spill; KEEP, see split_may_keep: 135 to 160) and no request in FP32.
+template <int N, int PREC, bool KEEP = false> constexpr int line_wpe()
 {
     if constexpr (PREC == 0) return N >= 1024 && N <= 4096 ? 4 : 1;
-    else return N >= 4096 || (N >= 1024 && PREC == 1) ? 4 : (N >= 1024 ? 3 : 2);
+    else return N >= 4096 || (N >= 1024 && PREC == 1 && !KEEP) ? 4 : (N >= 1024 && !KEEP ? 3 : 2);
+}
+
+// Split-precision fused lines of 1024 and 2048 points whose workgroups are resident
+// in one round at three waves per SIMD (TWP = false there: no table variant exists):
+// the inverse transform keeps the forward one's LDS slots and twiddles in registers.
+// With a round or less every workgroup's own latency counts (2048 x 1024 LFM scene,
+// BF16 37.6 us against 39.4, FP16 37.8 against 39.2; 1024 x 1024 25.8 against 26.8), with
+// more of them the fourth wave does (2048 x 2048 64.7 against 62.1).
+template <int N, int KIND, int PREC> constexpr bool split_may_keep()
+{
+    return PREC != PREC_FP32 && KIND == LK_FUSED && (N == 1024 || N == 2048);
 }
 
 // Line transform in the requested butterfly precision: FP32 VALU passes, or
@@ -177,8 +191,8 @@ __device__ __forceinline__ void fft_any(float2 (&x)[line_e(N)], float2* __restri
         fft_line<N, INV, SPLIT, FRESH>(x, lds, tw, t, before_last);
     } else {
         using L = LineLaunch<N>;
-        fft_line_mfma<N, INV, PREC, L::LPW, L::BLOCK, IN_MF>(x, lds - sub * LineGeom<N>::LDS, tw, sub,
-                                                      t, before_last);
+        fft_line_mfma<N, INV, PREC, L::LPW, L::BLOCK, IN_MF, !TWP && N <= 2048>(x, lds - sub * LineGeom<N>::LDS, tw, sub,
+                                                                   t, before_last);
     }
 }
 
@@ -322,9 +336,6 @@ __device__ __forceinline__ void store_line_tiled(const float2 (&x)[16], float2* 
         }
     }
 }
-
-// One workgroup per group of LPW lines.
-enum LineKind { LK_FUSED = 0, LK_FWD = 1, LK_INV = 2 };
 
 //  LK_FUSED: out = IFFT(FFT(in) * H)      (H carries the 1/N)
 //  LK_FWD:   out = FFT(in) * scale;  LK_INV: out = IFFT_unscaled(in) * scale
@@ -557,7 +568,7 @@ k_line_strip(const float2* __restrict__ in, float2* __restrict__ out, int cols, 
 
 template <int N, int KIND, int PREC, bool TWP, bool SPLIT = false, int X = 1>
 __global__ __launch_bounds__((LineLaunch<N, X>::BLOCK))
-__attribute__((amdgpu_waves_per_eu(line_wpe<N, PREC>()))) void
+__attribute__((amdgpu_waves_per_eu(line_wpe<N, PREC, split_may_keep<N, KIND, PREC>() && !TWP>()))) void
 k_line(const float2* in, float2* out, int lines, const float2* __restrict__ H,
        const float2* __restrict__ tw, float scale)
 {
@@ -2027,7 +2038,8 @@ static hipError_t launch_k_line(const float2* in, float2* out, int lines, const 
             return hipGetLastError();
         }
     }
-    if (PREC == PREC_FP32 && (variant & 1))
+    const bool keep = split_may_keep<N, KIND, PREC>() && groups <= 3 * CUS;
+    if ((PREC == PREC_FP32 && (variant & 1)) || keep)
         SAR_LAUNCH((k_line<N, KIND, PREC, false>), dim3(groups), dim3(L::BLOCK),
                            L::LDS_BYTES, s, in, out, lines, H, tw, scale);
     else
