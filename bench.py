@@ -67,7 +67,8 @@ PAPER_FUSED_MPX = 4096 * 4096 / 0.37 / 1e6   # Apple M1 fused RDA, Table II
 # filters and per-bin tables are excluded (they stay in L2).
 KERNEL_BYTES_PER_PX = {"range_fused": 16, "corner_turn": 16, "azimuth_fft": 16,
                        "azimuth_strip_fft": 16, "rcmc_azimuth": 16}
-KERNEL_SOURCES = ["rda_kernels.inl", "fft_line.hpp", "mfma_fft.hpp", "rda_part_fp32.hip"]
+KERNEL_SOURCES = ["rda_kernels.inl", "fft_line.hpp", "fft_line_tw.hpp", "mfma_fft.hpp", "rcmc_fit.hpp",
+                  "rda_part_fp32.hip"]
 GiB = 1 << 30
 
 

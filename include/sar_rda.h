@@ -312,10 +312,10 @@ void sar_batch_destroy(sar_batch_t batch);
  *          passes; else one array of complex pairs); bit 2 (FP32, N <= 8192)
  *          = twice the default lines per workgroup (8192 points per
  *          workgroup up to N = 4096, two lines at 8192);
- *   kind 3 RCMC + azimuth kernel: bit 0 as above for its IFFT, bit 1 = one
- *          output row per line slot (else two rows sharing their gathers),
- *          bit 2 = the two rows on two line slots' threads instead of one's
- *          (FP32 and Na = 4096 or 8192 only);
+ *   kind 3 RCMC + azimuth kernel: bit 1 = one output row per line slot (else
+ *          four, or two, rows sharing their gathers), bit 2 = two rows on two
+ *          line slots' threads (FP32 and Na = 4096 or 8192 only); bit 0 is
+ *          accepted and has no effect;
  *   kind 4 batched fused line kernel: bits 2-3 = grid (0: one workgroup per
  *          line group; 1, 2, 3: a persistent grid of 1x, 2x, 4x the resident
  *          workgroups); bit 0 is accepted and has no effect (a batch takes

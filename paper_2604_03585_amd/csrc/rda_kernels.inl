@@ -689,7 +689,7 @@ k_line_batch(const LineTask* __restrict__ tasks, int ntasks, int total_groups, f
 // What bounds them: memory, once the launch is long enough.  Before, each line
 // length had its own launch per pass and a corner turn lay between, all too short
 // to fill the chip or to hide their start and end: 24 scenes of 128 to 1024 points
-// a side (78 MB moved per pass) took 54.7 us in nine launches, 32.1 in these two.
+// a side (78 MB moved per pass) took 54.7 us in nine launches, 33.8 in these two.
 // (64-point strips are left out: eight of them side by side take 66 KiB of LDS,
 // two workgroups per CU for every scene of the launch.)
 #define SAR_BATCH_LENGTHS(X) X(128) X(256) X(512) X(1024) X(2048) X(4096)
